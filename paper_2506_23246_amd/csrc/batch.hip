@@ -2,7 +2,7 @@
 // persistent kernels, one per qubit-count class.  The host splits every circuit into work items
 // of whole point tiles, sized so that items cost about the same, and orders them
 // longest-processing-time first.  Workgroups pull items from an atomic counter (reset by the
-// preceding gate-table kernel, so the sequence replays inside a hipGraph without memset nodes).
+// preceding table kernel, so the sequence replays inside a hipGraph without memset nodes).
 // Each item writes its own M and loss partials, so the final fixed-order FP64 reduction per
 // circuit is deterministic no matter which workgroup ran which item.
 #include <hip/hip_runtime.h>
@@ -12,33 +12,18 @@
 #include "fused_kernel.hpp"
 #include "grads_dev.hpp"
 #include "rot_dev.hpp"
+#include "sweep_tables_dev.hpp"
 
 namespace qp {
 
-__global__ void k_batch_gates(const BatchCirc* __restrict__ circs, const BatchGate* __restrict__ gates, int ngates,
-                              int* __restrict__ counter) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g == 0)   // one work counter per segment
-    for (int i = 0; i < kNumSegs; ++i) counter[i] = 0;
-  if (g >= ngates) return;
-  const BatchGate G = gates[g];
+__global__ __launch_bounds__(kTabThreads) void k_batch_tables(const BatchCirc* __restrict__ circs,
+                                                              const BatchGate* __restrict__ blocks, int nblocks,
+                                                              int* __restrict__ counter) {
+  if (blockIdx.x == 0 && threadIdx.x < kNumSegs) counter[threadIdx.x] = 0;   // one work counter per segment
+  if ((int)blockIdx.x >= nblocks) return;
+  const BatchGate G = blocks[blockIdx.x];
   const BatchCirc& C = circs[G.circ];
-  if (G.idx == C.F) {   // identity entry used for absent gates of a round
-    float u[8];
-    set_identity(u);
-    store_gate_entry(const_cast<float*>(C.a.gtab) + G.idx * kGT, u);
-    return;
-  }
-  const QPlanDev* plan = C.a.plan;
-  const QFused* fu = reinterpret_cast<const QFused*>(reinterpret_cast<const char*>(plan) + plan->off_fused) + G.idx;
-  double u[8];
-  set_identity(u);
-  for (int c = 0; c < fu->ncomp; ++c) {
-    double s, co;
-    sincos(0.5 * (double)C.params[fu->param[c]], &s, &co);
-    left_mul_rot<double>(fu->kind[c], co, s, u);
-  }
-  store_gate_entry(const_cast<float*>(C.a.gtab) + G.idx * kGT, u);
+  sweep_tables(C.tab_plan, C.params, C.tabs, G.idx, 0);
 }
 
 // Dielectric point counts per circuit (one workgroup per circuit).
@@ -86,7 +71,7 @@ __global__ void k_batch_grads(const BatchCirc* __restrict__ circs, const BatchGa
   if (i >= npars) return;
   const BatchGate g = pars[i];
   const BatchCirc& C = circs[g.circ];
-  C.d_params[g.idx] = (float)param_grad_one(C.a.plan, C.params, C.m64, g.idx);
+  C.d_params[g.idx] = (float)param_grad_one(C.a.plan, C.params, C.m64, C.tabs, g.idx);
 }
 
 size_t batch_lds_bytes(int n, int max_cols) {   // static exchange planes + dynamic part
@@ -98,18 +83,18 @@ hipError_t launch_batch_seg(int seg, int grid, size_t dyn, hipStream_t s, const 
                             const BatchItem* items, int nitems, int* counter, float* mpart, float* lpart) {
   switch (seg) {
     case kSegLo:
-      hipLaunchKernelGGL((k_batch<3, kBatchSplit, 256, false>), dim3(grid), dim3(256), dyn, s, circs, items, nitems,
+      hipLaunchKernelGGL((k_batch<3, kBatchSplit, 256>), dim3(grid), dim3(256), dyn, s, circs, items, nitems,
                          counter, mpart, lpart);
       break;
     case kSegHi:
-      hipLaunchKernelGGL((k_batch<kBatchSplit + 1, 11, 256, false>), dim3(grid), dim3(256), dyn, s, circs, items,
+      hipLaunchKernelGGL((k_batch<kBatchSplit + 1, 11, 256>), dim3(grid), dim3(256), dyn, s, circs, items,
                          nitems, counter, mpart, lpart);
       break;
     case kSegBig:
-      hipLaunchKernelGGL((k_batch<kBatchBig, kBatchBig, 512, false>), dim3(grid), dim3(512), dyn, s, circs, items,
+      hipLaunchKernelGGL((k_batch<kBatchBig, kBatchBig, 512>), dim3(grid), dim3(512), dyn, s, circs, items,
                          nitems, counter, mpart, lpart);
       break;
-    default: return launch_batch_seg_ph(seg, grid, dyn, s, circs, items, nitems, counter, mpart, lpart);
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -118,16 +103,15 @@ hipError_t batch_prepare(int max_cols, int max_cols_big) {
   const int lds = (int)batch_dyn_lds_bytes(256, max_cols), lds_big = (int)batch_dyn_lds_bytes(512, max_cols_big);
   hipError_t e = hipSuccess;
   if (max_cols > 0) {
-    e = hipFuncSetAttribute((const void*)k_batch<3, kBatchSplit, 256, false>,
+    e = hipFuncSetAttribute((const void*)k_batch<3, kBatchSplit, 256>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_batch<kBatchSplit + 1, 11, 256, false>,
+      e = hipFuncSetAttribute((const void*)k_batch<kBatchSplit + 1, 11, 256>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   }
   if (e == hipSuccess && max_cols_big > 0)
-    e = hipFuncSetAttribute((const void*)k_batch<kBatchBig, kBatchBig, 512, false>,
+    e = hipFuncSetAttribute((const void*)k_batch<kBatchBig, kBatchBig, 512>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_big);
-  if (e == hipSuccess) e = batch_prepare_ph(max_cols, max_cols_big);
   return e;
 }
 
@@ -138,35 +122,32 @@ hipError_t launch_batch(const BatchCirc* circs, int ncirc, const BatchItem* item
                         hipStream_t aux, hipEvent_t ev_fork, hipEvent_t ev_join, hipEvent_t ev0, hipEvent_t ev1) {
   hipError_t e = hipSuccess;
   auto keep = [&](hipError_t x) { if (e == hipSuccess) e = x; };
-  hipLaunchKernelGGL(k_batch_gates, dim3(ngates > 0 ? (ngates + 127) / 128 : 1), dim3(128), 0, st,
-                     circs, gates, ngates, counter);
+  hipLaunchKernelGGL(k_batch_tables, dim3(ngates > 0 ? ngates : 1), dim3(kTabThreads), 0, st, circs, gates, ngates,
+                     counter);
   if (count_needed) hipLaunchKernelGGL(k_batch_counts, dim3(ncirc), dim3(256), 0, st, circs);
   if (ev0) keep(hipEventRecord(ev0, st));
   const BatchItem* seg_items[kNumSegs];
   for (int sg = 0, off = 0; sg < kNumSegs; off += nitems_seg[sg], ++sg) seg_items[sg] = items + off;
-  const int n_low = nitems_seg[kSegLo] + nitems_seg[kSegLoPh];
+  const int n_low = nitems_seg[kSegLo];
   int n_all = 0;
   for (int sg = 0; sg < kNumSegs; ++sg) n_all += nitems_seg[sg];
   const bool two = n_low > 0 && n_all > n_low && grid_lo > 0 && grid_hi > 0 && aux;
   auto seg = [&](int sg, hipStream_t s, int g) -> hipError_t {
     if (nitems_seg[sg] == 0 || g <= 0) return hipSuccess;
-    const size_t dyn = sg % 3 == kSegBig ? batch_dyn_lds_bytes(512, max_cols_big) : batch_dyn_lds_bytes(256, max_cols);
+    const size_t dyn = sg == kSegBig ? batch_dyn_lds_bytes(512, max_cols_big) : batch_dyn_lds_bytes(256, max_cols);
     return launch_batch_seg(sg, g, dyn, s, circs, seg_items[sg], nitems_seg[sg], counter + sg, mpart, lpart);
   };
   if (two) {
-    // the low segments on st, the others one after the other on aux, at the same time
+    // the low segment on st, the others one after the other on aux, at the same time
     keep(hipEventRecord(ev_fork, st));
     keep(hipStreamWaitEvent(aux, ev_fork, 0));
     keep(seg(kSegLo, st, grid_lo));
-    keep(seg(kSegLoPh, st, grid_lo));
     keep(seg(kSegHi, aux, grid_hi));
-    keep(seg(kSegHiPh, aux, grid_hi));
     keep(seg(kSegBig, aux, grid_big));
-    keep(seg(kSegBigPh, aux, grid_big));
     keep(hipEventRecord(ev_join, aux));
     keep(hipStreamWaitEvent(st, ev_join, 0));
   } else {
-    for (int sg = 0; sg < kNumSegs; ++sg) keep(seg(sg, st, sg % 3 == kSegBig ? grid_big : grid));
+    for (int sg = 0; sg < kNumSegs; ++sg) keep(seg(sg, st, sg == kSegBig ? grid_big : grid));
   }
   if (ev1) keep(hipEventRecord(ev1, st));
   hipLaunchKernelGGL(k_batch_reduce, dim3((ncols + 3) / 4), dim3(256), 0, st, circs, cols, ncols, mpart, lpart);

@@ -11,7 +11,9 @@
 namespace qp {
 
 struct BatchCirc {          // per circuit, device side
-  FusedArgs a;              // plan, gate table, points, RFF angles, outputs, loss description
+  FusedArgs a;              // plan, tables, points, RFF angles, outputs, loss description
+  SweepPlan tab_plan;
+  SweepTabs tabs;           // the tables as the table and gradient kernels see them
   const float* params;
   double* loss;
   float* d_params;
@@ -22,11 +24,11 @@ struct BatchCirc {          // per circuit, device side
 
 struct BatchItem { int circ, tile0, ntile, slot; };
 struct BatchCol { int circ, col; };      // col == F*8 + n_mom means the loss column
-struct BatchGate { int circ, idx; };     // fused gate (gate table) or parameter (gradients)
+struct BatchGate { int circ, idx; };     // block of a circuit's tables, or parameter (gradients)
 
 struct BatchLayout {
-  size_t counter, gtab, counts, m64, mpart, lpart, total;
-  std::vector<size_t> gtab_c, counts_c, m64_c;
+  size_t counter, counts, m64, mpart, lpart, total;
+  std::vector<size_t> tabs_c, counts_c, m64_c;
   std::vector<size_t> angles_c, jac_c;   // RFF circuits: per-point angles and Jacobian (else 0)
   std::vector<long long> mpart_c;
 };
@@ -38,19 +40,15 @@ constexpr int kBatchBig = 12;
 inline int batch_threads(int n) { return n >= kBatchBig ? 512 : 256; }
 inline int batch_points_per_tile(int n) { return batch_threads(n) >> (n - 3); }
 
-// Work-item segments, in list order: the three classes for circuits without CRZ phase stages,
-// then the same three classes for circuits with them (their own kernels, so that the phase code
-// never enters the register allocation of the others).  Each segment has its own work counter.
-enum BatchSegment { kSegLo = 0, kSegHi = 1, kSegBig = 2, kSegLoPh = 3, kSegHiPh = 4, kSegBigPh = 5, kNumSegs = 6 };
-inline int batch_segment(int n, bool phases) {
-  return (n >= kBatchBig ? kSegBig : (n > kBatchSplit ? kSegHi : kSegLo)) + (phases ? 3 : 0);
-}
+// Work-item segments, in list order: one per class.  Each segment has its own work counter.
+enum BatchSegment { kSegLo = 0, kSegHi = 1, kSegBig = 2, kNumSegs = 3 };
+inline int batch_segment(int n) { return n >= kBatchBig ? kSegBig : (n > kBatchSplit ? kSegHi : kSegLo); }
 
 // items: the segments' items back to back, nitems_seg[kNumSegs] (host) items each; counter:
-// kNumSegs work counters.  With work in a low segment (kSegLo, kSegLoPh) and in another and a
-// second stream (aux, with the events that fork it from st and join it back), the low segments
-// run on st on grid_lo workgroups while the others run on aux (high segments on grid_hi, 12-qubit
-// segments on grid_big) at the same time; otherwise every segment runs on st, on `grid`
+// kNumSegs work counters.  With work in the low segment (kSegLo) and in another and a
+// second stream (aux, with the events that fork it from st and join it back), the low segment
+// runs on st on grid_lo workgroups while the others run on aux (the high segment on grid_hi, the 12-qubit
+// segment on grid_big) at the same time; otherwise every segment runs on st, on `grid`
 // workgroups (grid_big for 12 qubits).  max_cols, max_cols_big: the largest F * 8 + n_mom of
 // the circuits below 12 qubits and of those with 12 (the dynamic LDS of the two block sizes).
 hipError_t launch_batch(const BatchCirc* circs, int ncirc, const BatchItem* items, const int* nitems_seg,
@@ -82,10 +80,9 @@ struct qp_batch {
   int grid_lo = 0, grid_hi = 0;     // grids of the low and high classes when they run at once
   int grid_big = 0;                 // grid of the 12-qubit class
   int max_cols = 0, max_cols_big = 0;   // largest F * 8 + n_mom below 12 qubits and at 12
+  int items_crz = 0;                   // work items of circuits with CRZ phase stages
   int nitems_seg[qp::kNumSegs] = {};   // work items per segment (listed in segment order)
   double work_lo = 0.0, work_rest = 0.0;   // estimated work of the low segments and of the others
-  std::vector<int> table_circs;     // circuits whose gate table comes from the fused path's kernel
-                                    // (CRZ phase stages: the table carries phase coefficients)
   std::vector<int> rff_circs;       // circuits whose RFF angles are formed before the batch kernels
   hipStream_t aux = nullptr;        // second stream: the low and the other segments run at once
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;

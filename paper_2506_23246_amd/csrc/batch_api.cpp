@@ -54,7 +54,8 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
     b->P.push_back(P[i]);
     int& mc = c->hp.n >= kBatchBig ? b->max_cols_big : b->max_cols;
     mc = std::max(mc, (int)c->hp.fused.size() * kGS + n_moments(c));
-    if (!c->hp.phases.empty()) b->table_circs.push_back(i);
+    if ((int)c->hp.sweeps.size() > kMaxSweeps)
+      return cleanup(fail(ctx, QP_EUNSUPPORTED, "qp_batch_compile: circuit %d has too many layers", i));
     if (c->hp.enc_kind == QP_ENC_RFF) b->rff_circs.push_back(i);
   }
   if ((b->max_cols > 0 && batch_lds_bytes(3, b->max_cols) > 160 * 1024) ||
@@ -84,7 +85,7 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
   // the segments in order, each longest first
   auto seg = [&](const BatchItem& x) {
     const qp_circuit* c = b->circs[x.circ];
-    return batch_segment(c->hp.n, !c->hp.phases.empty());
+    return batch_segment(c->hp.n);
   };
   std::stable_sort(b->items.begin(), b->items.end(), [&](const BatchItem& x, const BatchItem& y) {
     if (seg(x) != seg(y)) return seg(x) < seg(y);
@@ -93,8 +94,9 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
   b->work_lo = b->work_rest = 0.0;
   for (const auto& it : b->items) {
     const int k = seg(it);
+    if (!b->circs[it.circ]->hp.phases.empty()) ++b->items_crz;
     b->nitems_seg[k] += 1;
-    (k == kSegLo || k == kSegLoPh ? b->work_lo : b->work_rest) += tile_cost[it.circ] * it.ntile;
+    (k == kSegLo ? b->work_lo : b->work_rest) += tile_cost[it.circ] * it.ntile;
   }
   class_grids(b, b->grid, kStackedBias, true, &b->grid_lo, &b->grid_hi);
   b->grid_big = ctx->cu_count;   // one 512-thread workgroup per CU
@@ -102,8 +104,9 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
     const int F = (int)b->circs[i]->hp.fused.size();
     const int ncol = F * kGS + n_moments(b->circs[i]);
     for (int c = 0; c <= ncol; ++c) b->cols.push_back(BatchCol{i, c});
-    if (b->circs[i]->hp.phases.empty())   // CRZ circuits: the fused path's table kernel (run time)
-      for (int f = 0; f <= F; ++f) b->gates.push_back(BatchGate{i, f});   // f == F: identity entry
+    const auto& hp = b->circs[i]->hp;
+    for (int k = 0; k < sweep_table_blocks(hp.n, (int)hp.sweeps.size() - hp.sweep_first, !hp.phases.empty()); ++k)
+      b->gates.push_back(BatchGate{i, k});
     for (int k = 0; k < b->circs[i]->hp.K; ++k) b->pars.push_back(BatchGate{i, k});
   }
   // workspace layout
@@ -112,13 +115,12 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
   size_t off = 0;
   L.counter = off; off = al(off + kNumSegs * sizeof(int));   // one work counter per segment
   long long mp = 0;
-  L.gtab_c.resize(count); L.counts_c.resize(count); L.m64_c.resize(count); L.mpart_c.resize(count);
+  L.tabs_c.resize(count); L.counts_c.resize(count); L.m64_c.resize(count); L.mpart_c.resize(count);
   L.angles_c.assign(count, 0); L.jac_c.assign(count, 0);
   for (int i = 0; i < count; ++i) {
     const qp_circuit* c = b->circs[i];
     const int F = (int)c->hp.fused.size(), NM = n_moments(c);
-    // gate entries + identity, then the phase coefficients (as the fused path's table)
-    L.gtab_c[i] = off; off = al(off + sizeof(float) * kGT * (F + 1) + sizeof(uint32_t) * NM);
+    L.tabs_c[i] = off; off = al(off + sweep_tab_bytes(c));
     L.counts_c[i] = off; off = al(off + 2 * sizeof(int));
     L.m64_c[i] = off; off = al(off + sizeof(double) * std::max(F * kGS + NM, 1));
     if (c->hp.enc_kind == QP_ENC_RFF) {
@@ -206,11 +208,11 @@ extern "C" int64_t qp_batch_info(const qp_batch* b, int32_t what) {
     case 1: return (int64_t)b->items.size();
     case 2: return b->grid;
     case 3: return b->gexec ? 1 : 0;
-    case 4: return b->nitems_seg[kSegLo] + b->nitems_seg[kSegLoPh];
+    case 4: return b->nitems_seg[kSegLo];
     case 5: return b->grid_lo;
     case 6: return b->grid_hi;
-    case 7: return b->nitems_seg[kSegBig] + b->nitems_seg[kSegBigPh];
-    case 8: return b->nitems_seg[kSegLoPh] + b->nitems_seg[kSegHiPh] + b->nitems_seg[kSegBigPh];
+    case 7: return b->nitems_seg[kSegBig];
+    case 8: return b->items_crz;
     default: return -1;
   }
 }
@@ -253,14 +255,19 @@ static qp_status batch_bind(qp_ctx* ctx, qp_batch* b, const qp_batch_io* io, con
     const qp_batch_io& o = io[i];
     FusedArgs& a = C.a;
     a.plan = c->dplan;
-    a.gtab = reinterpret_cast<float*>(w + L.gtab_c[i]);
+    C.tab_plan = sweep_plan(c);
+    C.tabs = sweep_tabs(c, w + L.tabs_c[i]);
+    a.gtab = C.tabs.gtab;
+    a.tcoef = C.tabs.tcoef;
+    a.ptab = C.tabs.ptab;
+    a.xmask = C.tabs.xmask;
     a.points = o.points;
     const bool rff = c->hp.enc_kind == QP_ENC_RFF;
     a.angles = rff ? reinterpret_cast<const float*>(w + L.angles_c[i]) : nullptr;
     a.jac = rff ? reinterpret_cast<const float*>(w + L.jac_c[i]) : nullptr;
     a.P = b->P[i];
     a.ntiles = (int)((b->P[i] + batch_points_per_tile(c->hp.n) - 1) / batch_points_per_tile(c->hp.n));
-    a.n_fused = C.F;
+    a.n_gates = a.n_fused = C.F;
     a.out = o.out;
     a.tan = o.tan;
     a.d_out = nullptr;
@@ -292,15 +299,8 @@ static hipError_t batch_launch(qp_ctx* ctx, qp_batch* b, const qp_maxwell_desc* 
                                int g_hi) {
   char* w = static_cast<char*>(ws);
   const BatchLayout& L = b->layout;
-  // Circuits with CRZ phase stages take the fused path's gate and phase table kernels, RFF
-  // circuits the fused path's angle kernel; both write into the batch workspace before the
+  // RFF circuits take the fused path's angle kernel, which writes into the batch workspace before the
   // batch kernels read it.
-  for (int i : b->table_circs) {
-    const qp_circuit* c = b->circs[i];
-    hipError_t e = launch_gate_table(c->dplan, (int)c->hp.fused.size(), n_moments(c), b->hcirc[i].params,
-                                     reinterpret_cast<float*>(w + L.gtab_c[i]), 0, ctx->stream);
-    if (e != hipSuccess) return e;
-  }
   for (int i : b->rff_circs) {
     const FusedArgs& a = b->hcirc[i].a;
     hipError_t e = launch_rff(b->circs[i]->dplan, a.points, a.P, const_cast<float*>(a.angles),
@@ -326,7 +326,7 @@ extern "C" qp_status qp_batch_run(qp_ctx* ctx, qp_batch* b, const qp_batch_io* i
     hipEventCreate(&e1);
     struct Shape { int grid, lo, hi; };
     std::vector<Shape> shapes;
-    const int n_low = b->nitems_seg[kSegLo] + b->nitems_seg[kSegLoPh];
+    const int n_low = b->nitems_seg[kSegLo];
     const bool two = n_low > 0 && n_low < (int)b->items.size();
     for (int mult : {1, 2, 3, 4}) {
       const int g = ctx->cu_count * mult;

@@ -1,6 +1,4 @@
-// Persistent tile kernel of the uneven batch: one instantiation per qubit-count class and phase
-// flag (batch.hip holds the classes without CRZ phase stages, batch_ph.hip those with them, so
-// the two sets compile in parallel and neither's register allocation sees the other's code).
+// Persistent tile kernel of the uneven batch: one instantiation per qubit-count class.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -19,14 +17,13 @@ inline size_t batch_dyn_lds_bytes(int T, int max_cols) {
   return (size_t)(T / 64) * max_cols * sizeof(float) + (size_t)(T / 64) * 40 * sizeof(float);
 }
 
-// The tiles of one work item.  PH: the class kernel for circuits with CRZ phase stages (the tile
-// code applies them and accumulates their moments in mslots); the other kernels compile it out.
-template <int N, int NLO, int NHI, int T, bool PH>
+// The tiles of one work item.
+template <int N, int NLO, int NHI, int T>
 __device__ __forceinline__ void batch_case(const BatchCirc& C, const BatchItem& it, float2* buf, float* slots,
                                            float* mslots, float* red, float& lacc) {
   if constexpr (NLO <= N && N <= NHI) {
     for (int t = it.tile0; t < it.tile0 + it.ntile; ++t)
-      fused_tile<N, T, kBEXS, kModeMaxwell, true, false, PH>(C.a, t, buf, slots, mslots, red, lacc);
+      fused_tile<N, T, kBEXS, kModeMaxwell>(C.a, t, buf, slots, mslots, red, lacc);
   }
 }
 
@@ -34,13 +31,13 @@ __device__ __forceinline__ void batch_case(const BatchCirc& C, const BatchItem& 
 // gets its own register allocation (all counts 3..11 in one function exceeded the 256-VGPR cap
 // and spilled 128 bytes a lane, whose scratch traffic doubled the kernel's HBM bytes; 3..8 and
 // 9..11 each fit, and 12 qubits need 512 threads: a tile is one point on 512 threads).
-template <int NLO, int NHI, int T, bool PH>
+template <int NLO, int NHI, int T>
 __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ circs, const BatchItem* __restrict__ items,
                                              int nitems, int* __restrict__ counter, float* __restrict__ mpart,
                                              float* __restrict__ lpart) {
   constexpr int WAVES = T / 64;
   constexpr int PLANE = T * 8;
-  __shared__ float4 planes[kBEXS * PLANE / 2];   // exchange planes (static: one-XOR addressing)
+  __shared__ float4 planes[kBEXS * PLANE / 2];   // exchange planes (see fused_tile)
   extern __shared__ float4 smem4[];
   float2* buf = reinterpret_cast<float2*>(planes);
   float* slots = reinterpret_cast<float*>(smem4);
@@ -61,16 +58,16 @@ __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ ci
     __syncthreads();
     float lacc = 0.f;
     switch (C.n) {
-      case 3: batch_case<3, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 4: batch_case<4, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 5: batch_case<5, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 6: batch_case<6, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 7: batch_case<7, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 8: batch_case<8, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 9: batch_case<9, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 10: batch_case<10, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 11: batch_case<11, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
-      case 12: batch_case<12, NLO, NHI, T, PH>(C, it, buf, slots, mslots, red, lacc); break;
+      case 3: batch_case<3, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 4: batch_case<4, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 5: batch_case<5, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 6: batch_case<6, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 7: batch_case<7, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 8: batch_case<8, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 9: batch_case<9, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 10: batch_case<10, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 11: batch_case<11, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 12: batch_case<12, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
       default: break;
     }
     __syncthreads();
@@ -101,8 +98,4 @@ __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ ci
 // Launches the class kernel of segment `seg` (see BatchSeg) on `grid` workgroups.
 hipError_t launch_batch_seg(int seg, int grid, size_t dyn, hipStream_t s, const BatchCirc* circs,
                             const BatchItem* items, int nitems, int* counter, float* mpart, float* lpart);
-hipError_t launch_batch_seg_ph(int seg, int grid, size_t dyn, hipStream_t s, const BatchCirc* circs,
-                               const BatchItem* items, int nitems, int* counter, float* mpart, float* lpart);
-hipError_t batch_prepare_ph(int max_cols, int max_cols_big);
-
 }  // namespace qp

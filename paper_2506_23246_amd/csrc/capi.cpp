@@ -168,7 +168,7 @@ extern "C" qp_status qp_plan_image(const qp_circuit_desc* d, void* host_buf, siz
   if (!d || !bytes) return QP_EINVAL;
   HostPlan hp;
   int status = QP_OK;
-  std::string msg = build_plan(d, &hp, &status);
+  std::string msg = build_plan(d, &hp, &status, true);
   if (!msg.empty() || status != QP_OK) return status != QP_OK ? (qp_status)status : QP_EINVAL;
   if (!hp.fused_ok) return QP_EUNSUPPORTED;
   *bytes = hp.blob.size();
@@ -244,13 +244,45 @@ int qp::fused_grid(const qp_ctx* ctx, const qp_circuit* c, int64_t P) {
   return (int)std::min<int64_t>(ntiles, cap);
 }
 
+namespace {
+struct TabLayout { size_t gtab, tcoef, ptab, gpar, lscale, xmask, total; };
+TabLayout tab_layout(const qp_circuit* c) {
+  auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const size_t F = c->hp.fused.size(), S = c->hp.sweeps.size(), T = S - (size_t)c->hp.sweep_first;
+  TabLayout L{};
+  size_t off = 0;
+  L.gtab = off; off = al(off + sizeof(float) * kGT * (F + 1) + sizeof(uint32_t) * (size_t)n_moments(c));
+  L.tcoef = off; off = al(off + sizeof(float) * kTC * S);
+  L.ptab = off; off = al(off + sizeof(float2) * ((T + 1) << c->hp.n));
+  L.gpar = off; off = al(off + sizeof(double) * kGP * F);
+  L.lscale = off; off = al(off + sizeof(double) * S);
+  L.xmask = off; off = al(off + sizeof(uint32_t) * (S + 1));
+  L.total = off;
+  return L;
+}
+}  // namespace
+
+size_t qp::sweep_tab_bytes(const qp_circuit* c) { return tab_layout(c).total; }
+
+SweepTabs qp::sweep_tabs(const qp_circuit* c, void* base) {
+  const TabLayout L = tab_layout(c);
+  char* w = static_cast<char*>(base);
+  return SweepTabs{reinterpret_cast<float*>(w + L.gtab),   reinterpret_cast<float*>(w + L.tcoef),
+                   reinterpret_cast<float2*>(w + L.ptab),  reinterpret_cast<double*>(w + L.gpar),
+                   reinterpret_cast<double*>(w + L.lscale), reinterpret_cast<uint32_t*>(w + L.xmask)};
+}
+
+SweepPlan qp::sweep_plan(const qp_circuit* c) {
+  const QPlanDev* h = reinterpret_cast<const QPlanDev*>(c->hp.blob.data());
+  return SweepPlan{c->dplan, h->n, h->n_fused, h->n_sweeps, h->sweep_first, h->off_fused, h->off_sweeps};
+}
+
 WsLayout qp::fused_layout(const qp_circuit* c, int64_t P, int grid_cap) {
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   WsLayout L{};
   const int F = (int)c->hp.fused.size();
   const int NM = n_moments(c);
   size_t off = 0;
-  L.gtab = off; off = al(off + sizeof(float) * kGT * (F + 1) + sizeof(uint32_t) * NM);   // + identity, phases
   L.counts = off; off = al(off + 2 * sizeof(int));
   if (c->hp.enc_kind == QP_ENC_RFF) {
     L.angles = off; off = al(off + sizeof(float) * (size_t)P * c->hp.n);
@@ -259,6 +291,7 @@ WsLayout qp::fused_layout(const qp_circuit* c, int64_t P, int grid_cap) {
   L.mpart = off; off = al(off + sizeof(float) * (size_t)grid_cap * (F * kGS + NM));
   L.lpart = off; off = al(off + sizeof(float) * (size_t)std::max(grid_cap, 1));
   L.m64 = off; off = al(off + sizeof(double) * ((size_t)std::max(F, 1) * kGS + NM));
+  L.tabs = off; off = al(off + sweep_tab_bytes(c));
   L.total = off;
   return L;
 }
@@ -387,10 +420,13 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   const int cap = ctx->cu_count * 4;
   const WsLayout L = fused_layout(c, P, cap);
   char* w = static_cast<char*>(ws);
-  float* gtab = reinterpret_cast<float*>(w + L.gtab);
   int* counts = reinterpret_cast<int*>(w + L.counts);
   const int NM = n_moments(c);
-  hipError_t e = launch_gate_table(c->dplan, F, NM, params, gtab, (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st);
+  const int layers = (int)c->hp.sweeps.size();
+  if (layers > kMaxSweeps) return hipcheck(ctx, hipErrorInvalidValue, "fused kernel");
+  const SweepTabs tabs = sweep_tabs(c, w + L.tabs);
+  hipError_t e = launch_sweep_tables(sweep_plan(c), NM > 0, params, tabs,
+                                     (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st);
   if (e != hipSuccess) return hipcheck(ctx, e, "gate table");
   const float* ang = angles;
   const float* jc = jac;
@@ -410,16 +446,20 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
     grid = (int)std::min<int64_t>(grid_override, (P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
   grid = std::min(grid, cap);
   const int exs = NM > 0 ? 2 : (exs_override > 0 ? exs_override : c->exs);   // phases: unpipelined kernel
-  const size_t lds = fused_lds_bytes(n, exs, F, NM);
+  const bool fwd = mode_fwd_only(mode);   // no statistics
   FusedArgs a{};
   a.plan = c->dplan;
-  a.gtab = gtab;
+  a.gtab = tabs.gtab;
+  a.tcoef = tabs.tcoef;
+  a.ptab = tabs.ptab;
+  a.xmask = tabs.xmask;
   a.points = points;
   a.angles = ang;
   a.jac = jc;
   a.P = P;
   a.ntiles = (int)((P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
-  a.n_fused = F;
+  a.n_gates = F;
+  a.n_fused = fwd ? 0 : F;
   a.out = out;
   a.tan = tan;
   a.d_out = d_out;
@@ -431,7 +471,7 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   a.counts = counts;
   a.mpart = reinterpret_cast<float*>(w + L.mpart);
   a.lpart = reinterpret_cast<float*>(w + L.lpart);
-  a.n_mom = NM;
+  a.n_mom = fwd ? 0 : NM;
   a.f_mir = f_mir;
   a.n_mir = n_mir;
   a.w_sym = w_sym;
@@ -441,7 +481,7 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   if (mode_packed(mode)) { a.tan = nullptr; a.d_tan = nullptr; }
   if (grid > 0) {
     if (ctx->timing) hipEventRecord(ctx->ev0, st);
-    if ((e = launch_fused(n, mode, a, grid, exs, c->hp.has_signs, lds, st)) != hipSuccess) return hipcheck(ctx, e, "fused kernel");
+    if ((e = launch_fused(n, mode, a, grid, exs, fused_dyn_lds(n, a.n_fused, a.n_mom), st)) != hipSuccess) return hipcheck(ctx, e, "fused kernel");
     if (ctx->timing) hipEventRecord(ctx->ev1, st);
   }
   if (mode_fwd_only(mode) || (!loss && !d_params)) return QP_OK;   // the tuner times the main kernel only
@@ -449,7 +489,7 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   if ((e = launch_reduce(a.mpart, grid, F * kGS + NM, mode == kModeMaxwell ? a.lpart : nullptr, m64,
                          mode == kModeMaxwell ? loss : nullptr, st)) != hipSuccess)
     return hipcheck(ctx, e, "reduce");
-  if (d_params && (e = launch_param_grads(c->dplan, c->hp.K, params, m64, d_params, st)) != hipSuccess)
+  if (d_params && (e = launch_param_grads(c->dplan, c->hp.K, params, m64, tabs, d_params, st)) != hipSuccess)
     return hipcheck(ctx, e, "param grads");
   return QP_OK;
 }
@@ -679,7 +719,7 @@ extern "C" qp_status qp_total_loss(qp_ctx* ctx, const qp_circuit* c, const float
   const int64_t P_rest = L.P_ext - P;
   const int m = c->hp.m;
   qp_status s = QP_OK;
-  if (P_rest > 0 && (s = run_fused(ctx, c, kModeFwdPk, params, ext + 3 * P, nullptr, nullptr, P_rest, nullptr,
+  if (P_rest > 0 && (s = run_fused(ctx, c, kModeFieldsPk, params, ext + 3 * P, nullptr, nullptr, P_rest, nullptr,
                                    fo + (size_t)m * P, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                    fws, gflags, 0, 0)) != QP_OK)
     return s;

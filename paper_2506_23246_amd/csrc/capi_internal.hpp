@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/qpinn.h"
+#include "fused.hpp"
 #include "plain.hpp"
 #include "plan.hpp"
 
@@ -36,13 +37,17 @@ struct qp_circuit {
 
 namespace qp {
 
-struct WsLayout { size_t gtab, counts, angles, jac, mpart, lpart, m64, total; };
+struct WsLayout { size_t counts, angles, jac, mpart, lpart, m64, tabs, total; };
 
 qp_status fail(qp_ctx* c, qp_status s, const char* fmt, ...);
 qp_status hipcheck(qp_ctx* c, hipError_t e, const char* what);
 void choose_launch(qp_ctx* ctx, qp_circuit* c);
 int fused_grid(const qp_ctx* ctx, const qp_circuit* c, int64_t P);
 WsLayout fused_layout(const qp_circuit* c, int64_t P, int grid_cap);
+// Tables of the sweep layers: bytes, and their pointers in a 256-byte aligned buffer.
+size_t sweep_tab_bytes(const qp_circuit* c);
+SweepTabs sweep_tabs(const qp_circuit* c, void* base);
+SweepPlan sweep_plan(const qp_circuit* c);
 int n_moments(const qp_circuit* c);   // phase-stage moments of the fused adjoint (0 without CRZ)
 qp_status run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float* params, const float* points,
                     const float* angles, const float* jac, int64_t P, const qp_maxwell_desc* ld, float* out,

@@ -5,21 +5,18 @@
 // three input tangents dpsi_t, dpsi_x, dpsi_y (and, in the adjoint, lambda and mu_t, mu_x, mu_y)
 // live in registers: a thread owns 8 amplitudes of each statevector, addressed by three
 // "register" index bits; the other n-3 index bits select the thread inside the point's thread
-// group.  A round applies up to three fused single-qubit gates whose qubits sit on the register
-// bits (no data movement); between rounds the state is re-distributed through LDS so that the
-// next round's qubits land on the register bits.  Entangler stages (CNOT/CZ runs) are folded
-// into that exchange as an index map plus a sign, so they cost no extra pass.
+// group.  The circuit runs as sweep layers (QSweep): an exchange through LDS that applies the
+// CNOT index map, one tabulated phase per amplitude, and one real rotation per qubit.
 //
 // Forward-mode tangents: a gate U acts on psi and on each dpsi_c identically because the
 // variational gates do not depend on the input point; only the encoding does, and its derivative
 // seeds dpsi at the start.  Readout: f_i = sum_j z_i(j)|psi_j|^2,
 // g_ic = 2 sum_j z_i(j) Re(conj(psi_j) dpsi_c,j) (section "QPINN architecture": Pauli-Z per qubit).
 //
-// Adjoint with uncompute: with lambda = dL/dpsi*, mu_c = dL/d(dpsi_c)* at the circuit end,
-// each gate (in reverse order) first uncomputes psi <- U^H psi, dpsi_c <- U^H dpsi_c, then adds
-//   M_ab += conj(lambda_a) psi_b + sum_c conj(mu_c,a) dpsi_c,b   (a: output row, b: input column)
-// over the gate's amplitude pairs, then pulls lambda, mu_c back through U^H.  The parameter
-// gradient is dL/dtheta = 2 Re sum_ab (dU/dtheta)_ab M_ab, evaluated after the FP64 reduction.
+// Adjoint with uncompute: with lambda = dL/dpsi*, mu_c = dL/d(dpsi_c)* at the circuit end, each layer
+// (in reverse order) takes psi, dpsi_c, lambda, mu_c back through its inverse and adds per gate
+//   S_k = Im <lambda|sigma_k|psi> + sum_c Im <mu_c|sigma_k|dpsi_c>, k = x, y, z;
+// the parameter gradient is a fixed contraction of S (grads_dev.hpp), after the FP64 reduction.
 //
 // Arithmetic is complex64 with FP32 accumulation; per-workgroup partials are reduced across
 // workgroups in a fixed order in FP64 (separate kernels), so results are deterministic.
@@ -31,99 +28,27 @@
 #include "fused.hpp"
 #include "grads_dev.hpp"
 #include "rot_dev.hpp"
+#include "sweep_tables_dev.hpp"
 
 namespace qp {
 
 
-hipError_t launch_fused_3(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_4(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_5(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_6(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_7(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_8(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_9(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_10(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_11(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-hipError_t launch_fused_12(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
+hipError_t launch_fused_3(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_4(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_5(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_6(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_7(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_8(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_9(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_10(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_11(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+hipError_t launch_fused_12(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
 
-// ---------------------------------------------------------------------------------------------
-// Gate table: U = R_{c-1} ... R_0 for every fused gate, R_P(theta) = exp(-i theta P/2).  The table
-// is formed once per call from the K parameters (work independent of the point count) in FP64
-// and rounded once to complex64; every per-point operation then runs in FP32.  The FP32-built
-// variant (k_gate_table) is kept for comparison (QP_FLAG_GATES_FP32).
-__global__ void k_gate_table64(const QPlanDev* __restrict__ plan, const float* __restrict__ params,
-                               float* __restrict__ gtab) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f > plan->n_fused) return;
-  if (f == plan->n_fused) {   // identity entry used for absent gates of a round
-    float u[8];
-    set_identity(u);
-    store_gate_entry(gtab + f * kGT, u);
-    return;
-  }
-  const QFused* fu = reinterpret_cast<const QFused*>(reinterpret_cast<const char*>(plan) + plan->off_fused) + f;
-  double u[8];
-  set_identity(u);
-  for (int c = 0; c < fu->ncomp; ++c) {
-    double s, co;
-    sincos(0.5 * (double)params[fu->param[c]], &s, &co);
-    left_mul_rot<double>(fu->kind[c], co, s, u);
-  }
-  store_gate_entry(gtab + f * kGT, u);
-}
-
-__global__ void k_gate_table(const QPlanDev* __restrict__ plan, const float* __restrict__ params,
-                             float* __restrict__ gtab) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f > plan->n_fused) return;
-  if (f == plan->n_fused) {   // identity entry used for absent gates of a round
-    float u[8];
-    set_identity(u);
-    store_gate_entry(gtab + f * kGT, u);
-    return;
-  }
-  const QFused* fu = reinterpret_cast<const QFused*>(reinterpret_cast<const char*>(plan) + plan->off_fused) + f;
-  float u[8];
-  set_identity(u);
-  for (int c = 0; c < fu->ncomp; ++c) {
-    float s, co;
-    sincosf(0.5f * params[fu->param[c]], &s, &co);
-    left_mul_rot<float>(fu->kind[c], co, s, u);
-  }
-  store_gate_entry(gtab + f * kGT, u);
-}
-
-// Phase-stage coefficients in 32-bit fractions of a turn (one thread per coefficient):
-// alpha_q = -(1/2) sum_t theta_qt, beta_qq' = theta_qq' + theta_q'q (see QPhaseStage).  Like the
-// gate table this is O(K) work per call and runs in FP64; the result is reduced modulo one turn.
-__global__ void k_phase_table(const QPlanDev* __restrict__ plan, const float* __restrict__ params,
-                              uint32_t* __restrict__ coef) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = plan->n, nt = phase_terms(n);
-  if (i >= plan->n_phase * nt) return;
-  const char* pb = reinterpret_cast<const char*>(plan);
-  const QPhaseStage& st = reinterpret_cast<const QPhaseStage*>(pb + plan->off_phase)[i / nt];
-  const QPhaseGate* gates = reinterpret_cast<const QPhaseGate*>(pb + plan->off_phase_gates) + st.gate0;
-  const int e = i % nt;
-  int qa = e, qb = -1;   // alpha_qa, or beta of the pair (qa, qb)
-  if (e >= n) {
-    int r = e - n;
-    qa = 0;
-    while (r >= n - 1 - qa) { r -= n - 1 - qa; ++qa; }
-    qb = qa + 1 + r;
-  }
-  double turns = 0.0;
-  const double inv2pi = 0.15915494309189533577;
-  for (int g = 0; g < st.ngates; ++g) {
-    const double th = (double)params[gates[g].param];
-    if (qb < 0) {
-      if (gates[g].c == qa) turns -= 0.5 * th * inv2pi;
-    } else if ((gates[g].c == qa && gates[g].t == qb) || (gates[g].c == qb && gates[g].t == qa)) {
-      turns += th * inv2pi;
-    }
-  }
-  const double frac = turns - floor(turns);                 // [0, 1)
-  coef[st.coef_off + e] = (uint32_t)(unsigned long long)(frac * 4294967296.0);
+// Tables of the sweep layers (FP64, once per call; fp32: the gate matrices formed in FP32, kept for
+// comparison, QP_FLAG_GATES_FP32).
+__global__ __launch_bounds__(kTabThreads) void k_sweep_tables(SweepPlan plan, const float* __restrict__ params,
+                                                              SweepTabs t, int fp32) {
+  sweep_tables(plan, params, t, blockIdx.x, fp32);
 }
 
 // Random-Fourier-feature angles: phi = [cos(Bp); sin(Bp)], theta = W phi, J = W dphi/dp.
@@ -196,10 +121,10 @@ __global__ void k_reduce_m(const float* __restrict__ mpart, int nblk, int ncol,
 
 // d L / d theta_k for every parameter (FP64; see grads_dev.hpp).
 __global__ void k_param_grads(const QPlanDev* __restrict__ plan, const float* __restrict__ params,
-                              const double* __restrict__ m64, float* __restrict__ grads) {
+                              const double* __restrict__ m64, SweepTabs t, float* __restrict__ grads) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= plan->n_params) return;
-  grads[k] = (float)param_grad_one(plan, params, m64, k);
+  grads[k] = (float)param_grad_one(plan, params, m64, t, k);
 }
 
 int fused_threads(int n) { return fused_wg_threads(n); }
@@ -211,30 +136,29 @@ size_t fused_lds_bytes(int n, int exs, int n_fused, int n_mom) {
          (size_t)(T / 64) * 40 * sizeof(float);
 }
 
-hipError_t launch_fused(int n, int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st) {
+size_t fused_dyn_lds(int n, int n_fused, int n_mom) {
+  return (size_t)(fused_threads(n) / 64) * (n_fused * kGS + n_mom + 40) * sizeof(float);
+}
+
+hipError_t launch_fused(int n, int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st) {
   switch (n) {
-    case 3: return launch_fused_3(mode, a, grid, exs, signs, lds, st);
-    case 4: return launch_fused_4(mode, a, grid, exs, signs, lds, st);
-    case 5: return launch_fused_5(mode, a, grid, exs, signs, lds, st);
-    case 6: return launch_fused_6(mode, a, grid, exs, signs, lds, st);
-    case 7: return launch_fused_7(mode, a, grid, exs, signs, lds, st);
-    case 8: return launch_fused_8(mode, a, grid, exs, signs, lds, st);
-    case 9: return launch_fused_9(mode, a, grid, exs, signs, lds, st);
-    case 10: return launch_fused_10(mode, a, grid, exs, signs, lds, st);
-    case 11: return launch_fused_11(mode, a, grid, exs, signs, lds, st);
-    case 12: return launch_fused_12(mode, a, grid, exs, signs, lds, st);
+    case 3: return launch_fused_3(mode, a, grid, exs, dyn, st);
+    case 4: return launch_fused_4(mode, a, grid, exs, dyn, st);
+    case 5: return launch_fused_5(mode, a, grid, exs, dyn, st);
+    case 6: return launch_fused_6(mode, a, grid, exs, dyn, st);
+    case 7: return launch_fused_7(mode, a, grid, exs, dyn, st);
+    case 8: return launch_fused_8(mode, a, grid, exs, dyn, st);
+    case 9: return launch_fused_9(mode, a, grid, exs, dyn, st);
+    case 10: return launch_fused_10(mode, a, grid, exs, dyn, st);
+    case 11: return launch_fused_11(mode, a, grid, exs, dyn, st);
+    case 12: return launch_fused_12(mode, a, grid, exs, dyn, st);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_gate_table(const QPlanDev* plan, int n_fused, int n_phase_coef, const float* params, float* gtab,
-                             int fp32, hipStream_t st) {
-  const int entries = n_fused + 1;   // + identity
-  if (fp32) hipLaunchKernelGGL(k_gate_table, dim3((entries + 127) / 128), dim3(128), 0, st, plan, params, gtab);
-  else hipLaunchKernelGGL(k_gate_table64, dim3((entries + 127) / 128), dim3(128), 0, st, plan, params, gtab);
-  if (n_phase_coef > 0)
-    hipLaunchKernelGGL(k_phase_table, dim3((n_phase_coef + 127) / 128), dim3(128), 0, st, plan, params,
-                       reinterpret_cast<uint32_t*>(gtab + (size_t)entries * kGT));
+hipError_t launch_sweep_tables(const SweepPlan& plan, bool phases, const float* params, const SweepTabs& t, int fp32,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(k_sweep_tables, dim3(sweep_table_blocks(plan.n, plan.n_sweeps - plan.sweep_first, phases)), dim3(kTabThreads), 0, st, plan, params, t, fp32);
   return hipGetLastError();
 }
 
@@ -257,9 +181,10 @@ hipError_t launch_reduce(const float* mpart, int nblk, int ncol, const float* lp
   return hipGetLastError();
 }
 
-hipError_t launch_param_grads(const QPlanDev* plan, int K, const float* params, const double* m64, float* grads, hipStream_t st) {
+hipError_t launch_param_grads(const QPlanDev* plan, int K, const float* params, const double* m64, const SweepTabs& t,
+                              float* grads, hipStream_t st) {
   if (K == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_param_grads, dim3((K + 127) / 128), dim3(128), 0, st, plan, params, m64, grads);
+  hipLaunchKernelGGL(k_param_grads, dim3((K + 127) / 128), dim3(128), 0, st, plan, params, m64, t, grads);
   return hipGetLastError();
 }
 

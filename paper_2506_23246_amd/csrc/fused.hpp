@@ -10,14 +10,35 @@
 
 namespace qp {
 
+// Per-call tables of the sweep layers (sweep_tables_dev.hpp).
+struct SweepTabs {
+  float* gtab;       // [F + 1][kGT] gate matrices U, U^H (entry F: identity), then the coefficients of the
+                     // rounds' phase stages (32-bit fractions of a turn)
+  float* tcoef;      // [n_sweeps][kTC] tan(b/2) by position
+  float2* ptab;      // [n_sweeps - sweep_first + 1][2^n] phase times cosines, [thread][register]; last: behind the last layer
+  double* gpar;      // [F][kGP] how a gate's statistics are read
+  double* lscale;    // [n_sweeps] scale of a layer's diagonal sums
+  uint32_t* xmask;   // [n_sweeps + 1] X mask of each layer; last: of the product state
+};
+
+// What the table kernel needs of the plan's header, passed by value (one dependent load less).
+struct SweepPlan {
+  const QPlanDev* plan;
+  int32_t n, n_fused, n_sweeps, sweep_first, off_fused, off_sweeps;
+};
+
 struct FusedArgs {
   const QPlanDev* plan;
-  const float* gtab;      // [F + 1][kGT] fused gate matrices U, U^H (entry F: identity)
+  const float* gtab;      // SweepTabs
+  const float* tcoef;
+  const float2* ptab;
+  const uint32_t* xmask;
   const float* points;    // [P][3]
   const float* angles;    // [P][n]   (angle-given or RFF encodings)
   const float* jac;       // [P][n][3]
   long long P;
   int ntiles;
+  int n_gates;            // fused gates (n_fused: those with statistics, 0 in the forward modes)
   int n_fused;
   float* out;             // [P][m] or null
   float* tan;             // [P][m][3] or null
@@ -43,14 +64,22 @@ int fused_threads(int n);
 // SIMD resident, so a grid above two 256-thread workgroups per CU runs in generations.
 int fused_max_wg_per_cu(int n);
 int fused_points_per_tile(int n);
+// LDS of a launch shape as the shape rules count it: exs planes, statistics, scratch.
 size_t fused_lds_bytes(int n, int exs, int n_fused, int n_mom);
-hipError_t launch_fused(int n, int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st);
-// Gate table [F + 1][kGT] and, after it, the phase-stage coefficients (n_phase_coef words).
-hipError_t launch_gate_table(const QPlanDev* plan, int n_fused, int n_phase_coef, const float* params, float* gtab,
-                             int fp32, hipStream_t st);
+// Dynamic LDS of a launch (statistics and scratch; the planes are static).
+size_t fused_dyn_lds(int n, int n_fused, int n_mom);
+hipError_t launch_fused(int n, int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st);
+// Blocks of one circuit's tables: the gate matrices, 256 entries each of the layers' phases (and of the
+// one behind the last layer), and the rounds' phase stages if it has any.
+QP_HD inline int sweep_table_blocks(int n, int layers, bool phases) {
+  return 1 + (layers + 1) * ((1 << n) > 256 ? (1 << n) / 256 : 1) + (phases ? 1 : 0);
+}
+hipError_t launch_sweep_tables(const SweepPlan& plan, bool phases, const float* params, const SweepTabs& t, int fp32,
+                               hipStream_t st);
 hipError_t launch_rff(const QPlanDev* plan, const float* points, long long P, float* angles, float* jac, hipStream_t st);
 hipError_t launch_count(const float* points, long long P, float x_if, int* counts, hipStream_t st);
 hipError_t launch_reduce(const float* mpart, int nblk, int ncol, const float* lpart, double* m64, double* loss, hipStream_t st);
-hipError_t launch_param_grads(const QPlanDev* plan, int K, const float* params, const double* m64, float* grads, hipStream_t st);
+hipError_t launch_param_grads(const QPlanDev* plan, int K, const float* params, const double* m64, const SweepTabs& t,
+                              float* grads, hipStream_t st);
 
 }  // namespace qp

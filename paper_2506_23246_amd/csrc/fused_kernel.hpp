@@ -4,26 +4,22 @@
 
 #include <cstdint>
 
+#include "const_dev.hpp"
 #include "qp_internal.hpp"
 #include "fused.hpp"
 
 namespace qp {
 
-// Uniform, read-only kernel data (plan, gate table) is read through the constant address space,
-// so the compiler emits scalar loads (SGPRs) instead of per-lane vector loads that stall a wave.
-#define QP_CONST __attribute__((address_space(4)))
-template <typename T> using CP = const QP_CONST T*;
-template <typename T> __device__ __forceinline__ CP<T> to_const(const T* p) { return (CP<T>)(p); }
-
 __device__ __forceinline__ uint32_t parity(uint32_t x) { return __popc(x) & 1u; }
 
 __device__ __forceinline__ uint32_t swz(uint32_t idx) { return lds_swizzle(idx); }
 
+// Logical index bits of a thread in mapping tpos (v: the thread's index bits, see sweep_thread).
 template <int N, typename TP>
-__device__ __forceinline__ uint32_t deposit_thread(uint32_t u, TP tpos) {
+__device__ __forceinline__ uint32_t deposit_thread(uint32_t v, TP tpos) {
   uint32_t j = 0;
 #pragma unroll
-  for (int k = 3; k < N; ++k) j |= ((u >> (k - 3)) & 1u) << tpos[k];
+  for (int k = 3; k < N; ++k) j |= ((v >> (k - 3)) & 1u) << tpos[k];
   return j;
 }
 
@@ -32,15 +28,521 @@ __device__ __forceinline__ uint32_t reg_off(int r, uint32_t p0, uint32_t p1, uin
          ((uint32_t)((r >> 2) & 1) << p2);
 }
 
-// ---- single-qubit gate on register bit B for statevectors [S0, S0+NS) ----------------------
+// Keeps the scheduler from interleaving what stands on its two sides: every side has independent work
+// enough, and interleaved the live ranges exceed the 256 registers.
+__device__ __forceinline__ void sched_cut() { __builtin_amdgcn_sched_barrier(0); }
+
+template <typename V>
+__device__ __forceinline__ void pin_sgpr(V& v) { asm volatile("" : "+s"(v)); }
+template <typename V>
+__device__ __forceinline__ void pin_vgpr(V& v) { asm volatile("" : "+v"(v)); }
+
+// DPP permutation that brings the partner lane of thread bit K (lane XOR 1, 2, 7 or 8), as an operand
+// modifier of the multiply-adds below.  They are written out because the compiler keeps the
+// permutation as a move of its own (half the rate, and a register for every moved value: the Maxwell
+// kernels spilled 700 and 1400 registers).  A VALU result may be read through DPP, or by a permlane
+// swap, two wait states after it was written; the compiler does not see into the blocks, so each one
+// starts (and, where it writes what a swap may read, ends) with that wait.
+#define QP_DPP_0 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+#define QP_DPP_1 " quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
+#define QP_DPP_2 " row_half_mirror row_mask:0xf bank_mask:0xf\n"
+#define QP_DPP_3 " row_ror:8 row_mask:0xf bank_mask:0xf\n"
+
+// ---- one sweep layer's rotations ------------------------------------------------------------------
+// RY(b) / cos(b/2): x0' = x0 - t x1, x1' = x1 + t x0 (t = tan(b/2), |t| <= 1).  One multiply-add per
+// real number, against four for a general 2x2 gate; what bounds the kernels is VALU issue (see
+// fused_tile), so the gates are kept in this form and everything diagonal goes into the tables.
+// The coefficients sit in vector registers: a multiply-add with a scalar operand or a DPP permutation
+// issues every 4 cycles, one with three vector operands every 2 to 3 (measured, 8 and 2 waves per
+// SIMD).
+template <int B, int S>
+__device__ __forceinline__ void rot_reg(float (&sr)[8][8], float (&si)[8][8], float t) {
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    if (r & (1 << B)) continue;
+    const int r1 = r | (1 << B);
+    const float a = sr[S][r], b = sr[S][r1], c = si[S][r], d = si[S][r1];
+    sr[S][r] = fmaf(-t, b, a); sr[S][r1] = fmaf(t, a, b);
+    si[S][r] = fmaf(-t, d, c); si[S][r1] = fmaf(t, c, d);
+  }
+}
+// The same on thread bit K; ts: +t in lanes whose bit is set, -t in the others.
+#define QP_ROT_LANE(D)                                                                                        \
+  asm("s_nop 1\n"                                                                                             \
+      "v_fmac_f32_dpp %0, %0, %16" D "v_fmac_f32_dpp %1, %1, %16" D "v_fmac_f32_dpp %2, %2, %16" D             \
+      "v_fmac_f32_dpp %3, %3, %16" D "v_fmac_f32_dpp %4, %4, %16" D "v_fmac_f32_dpp %5, %5, %16" D             \
+      "v_fmac_f32_dpp %6, %6, %16" D "v_fmac_f32_dpp %7, %7, %16" D "v_fmac_f32_dpp %8, %8, %16" D             \
+      "v_fmac_f32_dpp %9, %9, %16" D "v_fmac_f32_dpp %10, %10, %16" D "v_fmac_f32_dpp %11, %11, %16" D         \
+      "v_fmac_f32_dpp %12, %12, %16" D "v_fmac_f32_dpp %13, %13, %16" D "v_fmac_f32_dpp %14, %14, %16" D       \
+      "v_fmac_f32_dpp %15, %15, %16" D "s_nop 1"                                                              \
+      : "+v"(sr[S][0]), "+v"(sr[S][1]), "+v"(sr[S][2]), "+v"(sr[S][3]), "+v"(sr[S][4]), "+v"(sr[S][5]),        \
+        "+v"(sr[S][6]), "+v"(sr[S][7]), "+v"(si[S][0]), "+v"(si[S][1]), "+v"(si[S][2]), "+v"(si[S][3]),        \
+        "+v"(si[S][4]), "+v"(si[S][5]), "+v"(si[S][6]), "+v"(si[S][7])                                        \
+      : "v"(ts))
+template <int K, int S>
+__device__ __forceinline__ void rot_lane(float (&sr)[8][8], float (&si)[8][8], float ts) {
+  if constexpr (K == 0) QP_ROT_LANE(QP_DPP_0);
+  else if constexpr (K == 1) QP_ROT_LANE(QP_DPP_1);
+  else if constexpr (K == 2) QP_ROT_LANE(QP_DPP_2);
+  else QP_ROT_LANE(QP_DPP_3);
+}
+
+// Statistics of a statevector pair (x: lambda-family 4 + C, y: psi-family C):
+//   S_x = sum Im(conj(x) y'), S_y = sum +-Re(conj(x) y') (+ where the bit is set), y' the amplitude with
+// the gate's bit flipped.  Register bit B:
+template <int B, int C>
+__device__ __forceinline__ void stat_reg(const float (&sr)[8][8], const float (&si)[8][8], float& sx, float& sy) {
+  float a[2] = {0.f, 0.f}, b[2] = {0.f, 0.f};   // two partial sums: shorter dependent chains
+  int np = 0;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    if (r & (1 << B)) continue;
+    const int r1 = r | (1 << B), h = np++ & 1;
+    const float x0r = sr[4 + C][r], x0i = si[4 + C][r], x1r = sr[4 + C][r1], x1i = si[4 + C][r1];
+    const float y0r = sr[C][r], y0i = si[C][r], y1r = sr[C][r1], y1i = si[C][r1];
+    a[h] = fmaf(x0r, y1i, a[h]); a[h] = fmaf(-x0i, y1r, a[h]);
+    a[h] = fmaf(x1r, y0i, a[h]); a[h] = fmaf(-x1i, y0r, a[h]);
+    b[h] = fmaf(x1r, y0r, b[h]); b[h] = fmaf(x1i, y0i, b[h]);
+    b[h] = fmaf(-x0r, y1r, b[h]); b[h] = fmaf(-x0i, y1i, b[h]);
+  }
+  sx += a[0] + a[1];
+  sy += b[0] + b[1];
+}
+// Thread bit K (S_y without its lane sign, which the flush applies): a += Im(conj(x) y'),
+// b += Re(conj(x) y') over registers R .. R + 3.
+#define QP_STAT_LANE(D)                                                                                       \
+  asm("s_nop 1\n"                                                                                             \
+      "v_fmac_f32_dpp %0, %8, %12" D "v_fmac_f32_dpp %1, %4, %12" D                                            \
+      "v_fmac_f32_dpp %2, %9, %13" D "v_fmac_f32_dpp %3, %5, %13" D                                            \
+      "v_fmac_f32_dpp %0, -%4, %16" D "v_fmac_f32_dpp %1, %8, %16" D                                           \
+      "v_fmac_f32_dpp %2, -%5, %17" D "v_fmac_f32_dpp %3, %9, %17" D                                           \
+      "v_fmac_f32_dpp %0, %10, %14" D "v_fmac_f32_dpp %1, %6, %14" D                                           \
+      "v_fmac_f32_dpp %2, %11, %15" D "v_fmac_f32_dpp %3, %7, %15" D                                           \
+      "v_fmac_f32_dpp %0, -%6, %18" D "v_fmac_f32_dpp %1, %10, %18" D                                          \
+      "v_fmac_f32_dpp %2, -%7, %19" D "v_fmac_f32_dpp %3, %11, %19" D                                          \
+      : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1)                                                                \
+      : "v"(sr[C][R]), "v"(sr[C][R + 1]), "v"(sr[C][R + 2]), "v"(sr[C][R + 3]), "v"(si[C][R]),                 \
+        "v"(si[C][R + 1]), "v"(si[C][R + 2]), "v"(si[C][R + 3]), "v"(sr[4 + C][R]), "v"(sr[4 + C][R + 1]),     \
+        "v"(sr[4 + C][R + 2]), "v"(sr[4 + C][R + 3]), "v"(si[4 + C][R]), "v"(si[4 + C][R + 1]),                \
+        "v"(si[4 + C][R + 2]), "v"(si[4 + C][R + 3]))
+template <int K, int C, int R>
+__device__ __forceinline__ void stat_lane4(const float (&sr)[8][8], const float (&si)[8][8], float& a0, float& b0,
+                                           float& a1, float& b1) {
+  if constexpr (K == 0) QP_STAT_LANE(QP_DPP_0);
+  else if constexpr (K == 1) QP_STAT_LANE(QP_DPP_1);
+  else if constexpr (K == 2) QP_STAT_LANE(QP_DPP_2);
+  else QP_STAT_LANE(QP_DPP_3);
+}
+template <int K, int C>
+__device__ __forceinline__ void stat_lane(const float (&sr)[8][8], const float (&si)[8][8], float& sx, float& sy) {
+  float a0 = 0.f, b0 = 0.f, a1 = 0.f, b1 = 0.f;   // two partial sums: shorter dependent chains
+  stat_lane4<K, C, 0>(sr, si, a0, b0, a1, b1);
+  stat_lane4<K, C, 4>(sr, si, a0, b0, a1, b1);
+  sx += a0 + a1;
+  sy += b0 + b1;
+}
+// w_r += Im(conj(x_r) y_r): its signed sums are the S_z of every qubit and the moments of CRZ phases.
+template <int C>
+__device__ __forceinline__ void stat_diag(const float (&sr)[8][8], const float (&si)[8][8], float (&w)[8]) {
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    w[r] = fmaf(sr[4 + C][r], si[C][r], w[r]);
+    w[r] = fmaf(-si[4 + C][r], sr[C][r], w[r]);
+  }
+}
+
+// Statevector S times the layer's table entries (CONJ: their conjugates).
+template <int S, bool CONJ>
+__device__ __forceinline__ void mul_phase(float (&sr)[8][8], float (&si)[8][8], const float (&pc)[8], const float (&ps)[8]) {
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const float c = pc[r], sn = CONJ ? -ps[r] : ps[r];
+    const float a = sr[S][r], b = si[S][r];
+    sr[S][r] = a * c - b * sn;
+    si[S][r] = a * sn + b * c;
+  }
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dppf(float v) {   // DPP lane permutation (row-local)
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// Reduce-scatter of four per-lane values over the wave: permlane32_swap pairs lanes l and l+32
+// (entries split 2/2), permlane16_swap pairs rows 0/1 and 2/3 (1/1), then DPP row_ror:8,
+// quad_perm xor 1, xor 2 and row_half_mirror sum the sixteen lanes of each row.  Lanes of row e
+// end with entry e.  No LDS traffic.
+__device__ __forceinline__ float wave_reduce_scatter4(const float* v) {
+  float a[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(v[i]), __float_as_int(v[2 + i]), false, false);
+    a[i] = __int_as_float(sw[0]) + __int_as_float(sw[1]);
+  }
+  const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_int(a[0]), __float_as_int(a[1]), false, false);
+  float c = __int_as_float(sw[0]) + __int_as_float(sw[1]);
+  c += dppf<0x128>(c);   // row_ror:8  (lane l <- l ^ 8 within a row)
+  c += dppf<0xB1>(c);    // quad_perm [1,0,3,2]: xor 1
+  c += dppf<0x4E>(c);    // quad_perm [2,3,0,1]: xor 2
+  c += dppf<0x141>(c);   // row_half_mirror: lane l <- 7 - l within eight lanes
+  return c;
+}
+
+// ---- register exchange through LDS ----------------------------------------------------------
+// An exchange moves the statevectors from one layer's output mapping to the next layer's input
+// mapping through the entanglers' index map A: logical index j of a point lives at LDS entry
+// swz(pbase ^ M j), M an invertible GF(2) map chosen per exchange for conflict-free banks.  pbase is
+// a multiple of 2^N and every index is below 2^N, so pbase + x equals pbase ^ x; M and the swizzle
+// are linear over GF(2), so a register's entry is the thread's base XOR a uniform offset (woff for the
+// writer, roff for the reader, which carries A).  Up to 9 qubits a point lives in one wave, whose LDS
+// operations complete in order, so the exchange needs no barrier and one plane serves every
+// statevector in turn.
+template <int N>
+__device__ __forceinline__ void point_fence() {   // before lanes of the point read what others wrote
+  if (N >= 10) __syncthreads();
+  else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+struct Addr {
+  uint32_t w[8], r[8];   // byte offsets of the eight registers, writer and reader
+};
+__device__ __forceinline__ Addr xchg_addr(CP<uint32_t> wo, CP<uint32_t> ro, uint32_t wb, uint32_t rb) {
+  Addr A;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) { A.w[r] = wb ^ wo[r]; A.r[r] = rb ^ ro[r]; }
+  return A;
+}
+template <int T, int S, int PL>
+__device__ __forceinline__ void xwrite(const float (&sr)[8][8], const float (&si)[8][8], float2* __restrict__ buf,
+                                       const uint32_t (&a)[8]) {
+  char* b = reinterpret_cast<char*>(buf);
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+    *reinterpret_cast<float2*>(b + a[r] + PL * (T * 64)) = make_float2(sr[S][r], si[S][r]);
+}
+template <int T, int S, int PL>
+__device__ __forceinline__ void xread(float (&sr)[8][8], float (&si)[8][8], const float2* __restrict__ buf,
+                                      const uint32_t (&a)[8]) {
+  const char* b = reinterpret_cast<const char*>(buf);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const float2 v = *reinterpret_cast<const float2*>(b + a[r] + PL * (T * 64));
+    sr[S][r] = v.x; si[S][r] = v.y;
+  }
+}
+// In-wave exchange (up to 9 qubits) of statevectors [S, S + NV).
+template <int T, int S, int NV>
+__device__ __forceinline__ void exchange_wave(float (&sr)[8][8], float (&si)[8][8], float2* __restrict__ buf, const Addr& A) {
+  if constexpr (NV > 0) {
+    xwrite<T, S, 0>(sr, si, buf, A.w);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    xread<T, S, 0>(sr, si, buf, A.r);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    exchange_wave<T, S + 1, NV - 1>(sr, si, buf, A);
+  }
+}
+
+// Wave exchange (10 qubits and more): register bits 0 .. NB-1 trade places with the wave bits of the
+// point.  A plane holds [wave][register][lane]; wave w writes register r (low bits rl, high bits rh) as
+// register (rh, w) of wave rl and reads its own eight back, so the addresses are two bases and
+// constants.
+template <int N, int T, int S, int PL>
+__device__ __forceinline__ void wwrite(const float (&sr)[8][8], const float (&si)[8][8], float2* __restrict__ buf, uint32_t wbase) {
+  constexpr int NB = sweep_wave(N);
+  char* b = reinterpret_cast<char*>(buf) + wbase;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int rl = r & ((1 << NB) - 1), rh = r >> NB;
+    *reinterpret_cast<float2*>(b + PL * (T * 64) + rl * 4096 + (rh << NB) * 512) = make_float2(sr[S][r], si[S][r]);
+  }
+}
+template <int N, int T, int S, int PL>
+__device__ __forceinline__ void wread(float (&sr)[8][8], float (&si)[8][8], const float2* __restrict__ buf, uint32_t rbase) {
+  const char* b = reinterpret_cast<const char*>(buf) + rbase;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const float2 v = *reinterpret_cast<const float2*>(b + PL * (T * 64) + r * 512);
+    sr[S][r] = v.x; si[S][r] = v.y;
+  }
+}
+
+// Swap slot I of statevector S: register bit I trades places with lane bit 4 + I.  For each register
+// pair (r, r | 2^I) a cross-lane swap exchanges odd rows of the first with even rows of the second
+// (lane bit 4, permlane16_swap) or the upper half of the first with the lower half of the second
+// (lane bit 5, permlane32_swap); the value at (register bit q', lane bit h') afterwards is the one
+// that was at (q = h', h = q').  An involution.
+template <int I, int S>
+__device__ __forceinline__ void swap_slot(float (&sr)[8][8], float (&si)[8][8]) {
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    if (r & (1 << I)) continue;
+    const int r1 = r | (1 << I);
+    if (I == 0) {
+      const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(sr[S][r]), __float_as_int(sr[S][r1]), false, false);
+      const auto b = __builtin_amdgcn_permlane16_swap(__float_as_int(si[S][r]), __float_as_int(si[S][r1]), false, false);
+      sr[S][r] = __int_as_float(a[0]); sr[S][r1] = __int_as_float(a[1]);
+      si[S][r] = __int_as_float(b[0]); si[S][r1] = __int_as_float(b[1]);
+    } else {
+      const auto a = __builtin_amdgcn_permlane32_swap(__float_as_int(sr[S][r]), __float_as_int(sr[S][r1]), false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(si[S][r]), __float_as_int(si[S][r1]), false, false);
+      sr[S][r] = __int_as_float(a[0]); sr[S][r1] = __int_as_float(a[1]);
+      si[S][r] = __int_as_float(b[0]); si[S][r1] = __int_as_float(b[1]);
+    }
+  }
+}
+
+// Adds v to a per-wave statistic slot in LDS with an LDS float add that returns nothing, so the
+// wave does not wait for its outstanding LDS operations as a read-modify-write would.  Each slot
+// belongs to one wave and receives one lane's value per flush, in program order, so the sums are
+// those of the read-modify-write, bit for bit.
+__device__ __forceinline__ void slot_add(float* p, float v) {
+  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// ---- one layer's data -------------------------------------------------------------------------------
+template <int N>
+struct Coef {
+  float t[N];   // tan(b/2) by position, lane positions with the lane's sign
+};
+template <int N, int P0 = 0, int P1 = N>   // positions [P0, P1)
+__device__ __forceinline__ Coef<N> load_coef(CP<float> tc, uint32_t v, bool inverse) {
+  Coef<N> K;
+#pragma unroll
+  for (int p = P0; p < P1; ++p) {
+    float t = tc[p];
+    if (inverse) t = -t;
+    if (p >= 3 && p < 7) t = ((v >> (p - 3)) & 1u) ? t : -t;
+    pin_vgpr(t);
+    K.t[p] = t;
+  }
+  return K;
+}
+struct Phase {
+  float c[8], s[8];
+};
+__device__ __forceinline__ Phase load_phase(const float4* __restrict__ tab) {   // the thread's eight entries
+  Phase P;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float4 v = tab[i];
+    P.c[2 * i] = v.x; P.s[2 * i] = v.y; P.c[2 * i + 1] = v.z; P.s[2 * i + 1] = v.w;
+  }
+  return P;
+}
+
+// Rotations of statevector S: the positions reached in place, then the swap slots.
+template <int N, int S>
+__device__ __forceinline__ void rot_base(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
+  rot_reg<0, S>(sr, si, K.t[0]);
+  rot_reg<1, S>(sr, si, K.t[1]);
+  rot_reg<2, S>(sr, si, K.t[2]);
+  if constexpr (N > 3) rot_lane<0, S>(sr, si, K.t[3]);
+  if constexpr (N > 4) rot_lane<1, S>(sr, si, K.t[4]);
+  if constexpr (N > 5) rot_lane<2, S>(sr, si, K.t[5]);
+  if constexpr (N > 6) rot_lane<3, S>(sr, si, K.t[6]);
+}
+template <int N, int S>
+__device__ __forceinline__ void swap_all(float (&sr)[8][8], float (&si)[8][8]) {
+  if constexpr (N > 7) swap_slot<0, S>(sr, si);
+  if constexpr (N > 8) swap_slot<1, S>(sr, si);
+}
+template <int N, int S>
+__device__ __forceinline__ void rot_slots(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
+  if constexpr (N > 7) rot_reg<0, S>(sr, si, K.t[7]);
+  if constexpr (N > 8) rot_reg<1, S>(sr, si, K.t[8]);
+}
+template <int N, int S>
+__device__ __forceinline__ void rot_wave(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
+  if constexpr (N > 9) rot_reg<0, S>(sr, si, K.t[9]);
+  if constexpr (N > 10) rot_reg<1, S>(sr, si, K.t[10]);
+  if constexpr (N > 11) rot_reg<2, S>(sr, si, K.t[11]);
+}
+// Forward: phase and rotations in place, then the swap slots (the state ends in the layer's mapping
+// before the wave exchange).
+template <int N, int S>
+__device__ __forceinline__ void fwd_base(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P) {
+  mul_phase<S, false>(sr, si, P.c, P.s);
+  rot_base<N, S>(sr, si, K);
+}
+template <int N, int S>
+__device__ __forceinline__ void fwd_slots(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
+  swap_all<N, S>(sr, si);
+  rot_slots<N, S>(sr, si, K);
+}
+template <int N, int S>
+__device__ __forceinline__ void layer_fwd(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P) {
+  fwd_base<N, S>(sr, si, K, P);
+  fwd_slots<N, S>(sr, si, K);
+  sched_cut();
+}
+
+// Statistics of a layer by position: S_x, S_y, and the diagonal products.
+template <int N>
+struct Stats {
+  float x[N], y[N], w[8];
+};
+template <int N, int P0 = 0, int P1 = N>
+__device__ __forceinline__ void clear(Stats<N>& Q) {
+#pragma unroll
+  for (int p = P0; p < P1; ++p) Q.x[p] = Q.y[p] = 0.f;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) Q.w[r] = 0.f;
+}
+// Marks the statistics as computed here: else the compiler sinks their multiply-adds into the flush,
+// past the gates that overwrite the statevectors, and spills what they need.
+template <int N, int P0, int P1>
+__device__ __forceinline__ void pin_stats(Stats<N>& Q, bool w) {
+#pragma unroll
+  for (int p = P0; p < P1; ++p) { pin_vgpr(Q.x[p]); pin_vgpr(Q.y[p]); }
+  if (w)
+#pragma unroll
+    for (int r = 0; r < 8; ++r) pin_vgpr(Q.w[r]);
+}
+// Adjoint of the wave positions on the pair (C, 4 + C): pull back, then the statistics.
+template <int N, int C>
+__device__ __forceinline__ void wave_rot(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
+  rot_wave<N, C>(sr, si, K); rot_wave<N, 4 + C>(sr, si, K);
+}
+template <int N, int C>
+__device__ __forceinline__ void wave_stat(const float (&sr)[8][8], const float (&si)[8][8], Stats<N>& Q) {
+  if constexpr (N > 9) stat_reg<0, C>(sr, si, Q.x[9], Q.y[9]);
+  if constexpr (N > 10) stat_reg<1, C>(sr, si, Q.x[10], Q.y[10]);
+  if constexpr (N > 11) stat_reg<2, C>(sr, si, Q.x[11], Q.y[11]);
+  pin_stats<N, 9, N>(Q, false);
+  sched_cut();
+}
+// Adjoint of the rest of a layer on the pair (unless PULL, of a layer folded into the encoding, whose
+// statistics alone are taken): swap slots with their statistics, rotations in place; then the
+// statistics of these, and the conjugate phase.  Gates of one layer act on different qubits and
+// commute, so each statistic may be taken with any of the others pulled back or not; only the cosines
+// left out so far scale it, which the gradient kernel puts back (gpar).
+template <int N, int C, bool PULL>
+__device__ __forceinline__ void adj_rot(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, Stats<N>& Q) {
+  if constexpr (N > 7) {
+    if (PULL) { rot_slots<N, C>(sr, si, K); rot_slots<N, 4 + C>(sr, si, K); }
+    stat_reg<0, C>(sr, si, Q.x[7], Q.y[7]);
+    if constexpr (N > 8) stat_reg<1, C>(sr, si, Q.x[8], Q.y[8]);
+    pin_stats<N, 7, N < 9 ? N : 9>(Q, false);
+    swap_all<N, C>(sr, si); swap_all<N, 4 + C>(sr, si);
+  }
+  sched_cut();
+  if (PULL) { rot_base<N, C>(sr, si, K); rot_base<N, 4 + C>(sr, si, K); }
+  sched_cut();
+}
+template <int N, int C, bool PULL>
+__device__ __forceinline__ void adj_stat(float (&sr)[8][8], float (&si)[8][8], const Phase& P, Stats<N>& Q) {
+  stat_reg<0, C>(sr, si, Q.x[0], Q.y[0]);
+  stat_reg<1, C>(sr, si, Q.x[1], Q.y[1]);
+  stat_reg<2, C>(sr, si, Q.x[2], Q.y[2]);
+  sched_cut();
+  if constexpr (N > 3) stat_lane<0, C>(sr, si, Q.x[3], Q.y[3]);
+  if constexpr (N > 4) stat_lane<1, C>(sr, si, Q.x[4], Q.y[4]);
+  if constexpr (N > 5) stat_lane<2, C>(sr, si, Q.x[5], Q.y[5]);
+  if constexpr (N > 6) stat_lane<3, C>(sr, si, Q.x[6], Q.y[6]);
+  stat_diag<C>(sr, si, Q.w);
+  pin_stats<N, 0, N < 7 ? N : 7>(Q, true);
+  sched_cut();
+  if (PULL) { mul_phase<C, true>(sr, si, P.c, P.s); mul_phase<4 + C, true>(sr, si, P.c, P.s); }
+  sched_cut();
+}
+template <int N, int C, bool PULL>
+__device__ __forceinline__ void layer_adj(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P, Stats<N>& Q) {
+  adj_rot<N, C, PULL>(sr, si, K, Q);
+  adj_stat<N, C, PULL>(sr, si, P, Q);
+}
+
+// Adds the S_x and S_y of positions [P0, P1) to the wave's slots (two gates per reduction).
+template <int N, int P0, int P1>
+__device__ __forceinline__ void flush_xy(CP<QSweep> L, const Stats<N>& Q, uint32_t v, float* __restrict__ slots, int F,
+                                         int wave, int lane) {
+#pragma unroll
+  for (int p = P0; p < P1; p += 2) {
+    const int q = p + 1 < P1 ? p + 1 : p;
+    auto ys = [&](int k) { return k >= 3 && k < 7 && !((v >> (k - 3)) & 1u) ? -Q.y[k] : Q.y[k]; };
+    const float v4[4] = {Q.x[p], ys(p), Q.x[q], ys(q)};
+    const float s = wave_reduce_scatter4(v4);
+    const int g = lane < 32 ? L->gate[p] : (q > p ? L->gate[q] : -1);
+    if (g >= 0 && (lane & 15) == 0) slot_add(slots + (wave * F + g) * kGS + ((lane >> 4) & 1), s);
+  }
+}
+// Signed sums of w over the wave: S_z of every position, and with a CRZ phase in front of the layer
+// (mslots) the first- and second-order parity sums W_q, W_qq' its gradient needs.
+template <int N>
+__device__ __forceinline__ void flush_z(CP<QSweep> L, const float (&w)[8], uint32_t v, float* __restrict__ slots,
+                                        float* __restrict__ mom, int F, int wave, int lane) {
+  float W[8];   // Walsh transform over the register bits: W[s] = sum_r (-1)^(s.r) w_r
+#pragma unroll
+  for (int r = 0; r < 8; ++r) W[r] = w[r];
+#pragma unroll
+  for (int b = 1; b < 8; b <<= 1)
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (!(r & b)) { const float x = W[r], y = W[r | b]; W[r] = x + y; W[r | b] = x - y; }
+  auto flip = [&](float x, int p) { return ((v >> (p - 3)) & 1u) ? -x : x; };   // times (-1)^bit of thread position p
+  float z[N];
+#pragma unroll
+  for (int p = 0; p < N; ++p) z[p] = p < 3 ? W[1 << p] : flip(W[0], p);
+#pragma unroll
+  for (int p = 0; p < N; p += 4) {
+    float v4[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v4[i] = p + i < N ? z[p + i < N ? p + i : 0] : 0.f;
+    const float s = wave_reduce_scatter4(v4);
+    const int row = lane >> 4;
+    int g = -1, t = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (p + i < N && row == i) { g = L->gate[p + i < N ? p + i : 0]; t = L->tin[p + i < N ? p + i : 0]; }
+    if ((lane & 15) == 0 && p + row < N) {
+      if (g >= 0) slot_add(slots + (wave * F + g) * kGS + 2, s);
+      if (mom) slot_add(mom + (N - 1 - t), s);
+    }
+  }
+  if (mom) {
+#pragma unroll
+    for (int p = 0; p < N; ++p) {
+#pragma unroll
+      for (int q0 = p + 1; q0 < N; q0 += 4) {
+        float v4[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int q = q0 + i;
+          float x = 0.f;
+          if (q < N) {
+            if (q < 3) x = W[(1 << p) | (1 << (q < 3 ? q : 0))];
+            else x = flip(p < 3 ? W[1 << (p < 3 ? p : 0)] : flip(W[0], p), q);
+          }
+          v4[i] = x;
+        }
+        const float s = wave_reduce_scatter4(v4);
+        const int row = lane >> 4;
+        int t = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (q0 + i < N && row == i) t = L->tin[q0 + i < N ? q0 + i : 0];
+        const int a = N - 1 - L->tin[p], b = N - 1 - t;
+        if ((lane & 15) == 0 && q0 + row < N)
+          slot_add(mom + N + phase_pair_index(N, a < b ? a : b, a < b ? b : a), s);
+      }
+    }
+  }
+}
+
+// ---- forward by rounds ------------------------------------------------------------------------------
+// The kernels that return a loss (and the fields the total loss is formed from) run the forward on the
+// fused 2x2 gates as they are, in rounds of three register-bit gates and up to two swap slots (QRound),
+// with the roundings and the summation order in which their FP64 losses have always been formed; only
+// the adjoint, and calls that return no loss, run the sweep layers.
+//
+// Single-qubit gate on register bit B for statevectors [S0, S0 + NS).
 // u: u00r,u00i,u01r,u01i,u10r,u10i,u11r,u11i.  Each lane applies the gate to its own amplitude
 // pairs on the matrix cores: v_mfma_f32_4x4x1f32 treats the wave as 16 blocks of 4 lanes,
 // C[m][n] += A[m] B[n] with A[m] from lane 4b + m, B[n] from lane 4b + n and C[m][n] in register m
 // of lane 4b + n.  With lane 4b + m holding row m of the gate's real 4x4 form M (acting on
 // (re x, im x, re y, im y)) as A, and every lane its own pair component k as B, four such steps
 // (k = 0..3) leave M (x, y) of each lane's pair in its four C registers.  The 2x2 products thus
-// leave the vector ALU, which keeps the gate statistics, exchanges and readout.  Called in
-// wave-uniform control flow only: a lane's result depends on the A operands of the other three
+// leave the vector ALU (no gain in rate: the two share the FP32 pipe; one instruction does the work of
+// four).  Called in wave-uniform control flow only: a lane's result depends on the A operands of the other three
 // lanes of its block, so all 64 lanes must be active.
 template <int B, int S0, int NS>
 __device__ __forceinline__ void apply_gate(float (&sr)[8][8], float (&si)[8][8], const float* u) {
@@ -86,117 +588,6 @@ __device__ __forceinline__ void apply_gate(float (&sr)[8][8], float (&si)[8][8],
   }
 }
 
-// Gate statistic of one statevector pair (lambda-family 4 + C, psi-family C), both taken
-// before the gate, for the register pairs on bit B:
-//   S_x += Im(conj(x0) y1) + Im(conj(x1) y0)
-//   S_y += Re(conj(x1) y0) - Re(conj(x0) y1)
-//   S_z += Im(conj(x0) y0) - Im(conj(x1) y1)
-template <int B, int C>
-__device__ __forceinline__ void accum_s1(const float (&sr)[8][8], const float (&si)[8][8], float* m) {
-  // two partial sums per component (alternate register pairs): shorter dependent FMA chains
-  float a[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
-  int np = 0;
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    if (r & (1 << B)) continue;
-    const int r1 = r | (1 << B);
-    float* mm = a[np & 1];
-    ++np;
-    const float x0r = sr[4 + C][r], x0i = si[4 + C][r], x1r = sr[4 + C][r1], x1i = si[4 + C][r1];
-    const float y0r = sr[C][r], y0i = si[C][r], y1r = sr[C][r1], y1i = si[C][r1];
-    mm[0] = fmaf(x0r, y1i, mm[0]); mm[0] = fmaf(-x0i, y1r, mm[0]);
-    mm[0] = fmaf(x1r, y0i, mm[0]); mm[0] = fmaf(-x1i, y0r, mm[0]);
-    mm[1] = fmaf(x1r, y0r, mm[1]); mm[1] = fmaf(x1i, y0i, mm[1]);
-    mm[1] = fmaf(-x0r, y1r, mm[1]); mm[1] = fmaf(-x0i, y1i, mm[1]);
-    mm[2] = fmaf(x0r, y0i, mm[2]); mm[2] = fmaf(-x0i, y0r, mm[2]);
-    mm[2] = fmaf(-x1r, y1i, mm[2]); mm[2] = fmaf(x1i, y1r, mm[2]);
-  }
-  m[0] += a[0][0] + a[1][0];
-  m[1] += a[0][1] + a[1][1];
-  m[2] += a[0][2] + a[1][2];
-}
-
-template <int B>
-__device__ __forceinline__ void accum_s(const float (&sr)[8][8], const float (&si)[8][8], float* q) {
-  // Pauli components of the gate's adjoint product for the pairs on register bit B, with
-  // x = lambda-family (statevectors 4..7) and y = psi-family (0..3), both before the gate:
-  //   S_x += Im(conj(x0) y1) + Im(conj(x1) y0)
-  //   S_y += Re(conj(x1) y0) - Re(conj(x0) y1)
-  //   S_z += Im(conj(x0) y0) - Im(conj(x1) y1)
-  // Two accumulators per component (even/odd statevector pair) shorten the FMA chains.
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    float* m = q + 3 * (s & 1);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      if (r & (1 << B)) continue;
-      const int r1 = r | (1 << B);
-      const float x0r = sr[4 + s][r], x0i = si[4 + s][r], x1r = sr[4 + s][r1], x1i = si[4 + s][r1];
-      const float y0r = sr[s][r], y0i = si[s][r], y1r = sr[s][r1], y1i = si[s][r1];
-      m[0] = fmaf(x0r, y1i, m[0]); m[0] = fmaf(-x0i, y1r, m[0]);
-      m[0] = fmaf(x1r, y0i, m[0]); m[0] = fmaf(-x1i, y0r, m[0]);
-      m[1] = fmaf(x1r, y0r, m[1]); m[1] = fmaf(x1i, y0i, m[1]);
-      m[1] = fmaf(-x0r, y1r, m[1]); m[1] = fmaf(-x0i, y1i, m[1]);
-      m[2] = fmaf(x0r, y0i, m[2]); m[2] = fmaf(-x0i, y0r, m[2]);
-      m[2] = fmaf(-x1r, y1i, m[2]); m[2] = fmaf(x1i, y1r, m[2]);
-    }
-  }
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dppf(float v) {   // DPP lane permutation (row-local)
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-// Reduce 8 floats over the 64 lanes of a wave; afterwards lane 8*e holds the sum of entry e.
-// Reduce-scatter of four per-lane values over the wave: permlane32_swap pairs lanes l and l+32
-// (entries split 2/2), permlane16_swap pairs rows 0/1 and 2/3 (1/1), then DPP row_ror:8,
-// quad_perm xor 1, xor 2 and row_half_mirror sum the sixteen lanes of each row.  Lanes of row e
-// end with entry e.  No LDS traffic.
-__device__ __forceinline__ float wave_reduce_scatter4(const float* v) {
-  float a[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(v[i]), __float_as_int(v[2 + i]), false, false);
-    a[i] = __int_as_float(sw[0]) + __int_as_float(sw[1]);
-  }
-  const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_int(a[0]), __float_as_int(a[1]), false, false);
-  float c = __int_as_float(sw[0]) + __int_as_float(sw[1]);
-  c += dppf<0x128>(c);   // row_ror:8  (lane l <- l ^ 8 within a row)
-  c += dppf<0xB1>(c);    // quad_perm [1,0,3,2]: xor 1
-  c += dppf<0x4E>(c);    // quad_perm [2,3,0,1]: xor 2
-  c += dppf<0x141>(c);   // row_half_mirror: lane l <- 7 - l within eight lanes
-  return c;
-}
-
-// ---- register exchange through LDS ----------------------------------------------------------
-// An exchange moves the statevectors from the writer round's mapping to the reader round's
-// mapping: each thread writes its registers at their logical indices and reads back the
-// amplitudes its registers hold in the new mapping, through the descriptor X (index map A and
-// sign (-1)^Q).  Logical index j of a point lives at LDS entry swz(pbase ^ M j), M an invertible
-// GF(2) map chosen per exchange for conflict-free banks.  Address arithmetic: pbase is a multiple
-// of 2^N and every index is below 2^N, so pbase + x equals pbase ^ x; M and the swizzle are linear
-// over GF(2), so the entry of j ^ o is the entry of j XOR swz(M o), and the planner stores
-// 8 swz(M o) (byte offsets of complex64 entries) for the eight register offsets (woff for the
-// writer, roff for the reader).
-// Per exchange a lane needs three words: its writer and reader byte bases and the sign bits of
-// its eight reads (the planner tabulates them per thread of a point: QLane); each access then
-// costs one XOR.
-struct XLane {
-  uint32_t wb, rb, sgn;
-};
-
-// Per-round uniform data, loaded once before the round's first barrier and pinned in SGPRs:
-// scalar loads share the lgkm counter with LDS operations, so a scalar load inside a slot would
-// make the next use wait for every outstanding LDS write as well.
-template <typename V>
-__device__ __forceinline__ void pin_sgpr(V& v) { asm volatile("" : "+s"(v)); }
-
-template <bool B>
-struct BoolC {
-  static constexpr bool value = B;
-};
-
 // Marks statevector S as computed at this point of the instruction stream: keeps the compiler
 // from sinking a group's gate arithmetic past the following barrier, which would undo the
 // overlap of that group's arithmetic with another group's LDS traffic.
@@ -207,25 +598,21 @@ __device__ __forceinline__ void pin_sv(float (&sr)[8][8], float (&si)[8][8]) {
 }
 
 struct RoundCoef {
-  float c[40];   // gate b's 2x2 matrix (U, or U^H in the adjoint) at c[8b .. 8b+7]; b = 3, 4: swap slots
-  int gid[5];    // fused-gate ids (-1: none): register bits 0..2, then swap slots 0, 1
+  float c[40];   // gate b's 2x2 matrix at c[8b .. 8b+7]; b = 3, 4: swap slots
 };
 
-template <bool ADJ, int NS>
+template <int NS>
 __device__ __forceinline__ RoundCoef load_round(CP<QRound> rk, CP<float> gtab, int F) {
   RoundCoef R;
 #pragma unroll
   for (int b = 0; b < 3 + NS; ++b) {
     const int g = b < 3 ? rk->gate[b] : rk->sgate[b - 3];
-    R.gid[b] = g;
     const int gi = g >= 0 ? g : F;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) R.c[8 * b + e] = gtab[gi * kGT + (ADJ ? 8 : 0) + e];
+    for (int e = 0; e < 8; ++e) R.c[8 * b + e] = gtab[gi * kGT + e];
   }
 #pragma unroll
   for (int i = 0; i < 8 * (3 + NS); ++i) pin_sgpr(R.c[i]);
-#pragma unroll
-  for (int b = 0; b < 3 + NS; ++b) pin_sgpr(R.gid[b]);
   return R;
 }
 
@@ -240,12 +627,18 @@ __device__ __forceinline__ Offs load_offs(CP<uint32_t> p) {
   return O;
 }
 
-// The lane words of exchange k in direction dir (0 forward, 1 reverse) for thread u of the point
-// whose swizzled base is pb8 = 8 swz(pbase): one 16-byte vector load from the plan's lane table
+// Per exchange a lane needs three words: its writer and reader byte bases and the sign bits of
+// its eight reads (the planner tabulates them per thread of a point: QLane); each access then
+// costs one XOR.
+struct XLane {
+  uint32_t wb, rb, sgn;
+};
+
+// The lane words of exchange k for thread u of the point whose swizzled base is pb8 = 8 swz(pbase): one 16-byte vector load from the plan's lane table
 // (vector loads use their own wait counter, so a load issued early does not hold up LDS waits).
-__device__ __forceinline__ XLane lane_words(const QLane* __restrict__ lanes, int dir, int R, int k, int TPn,
-                                            uint32_t u, uint32_t pb8) {
-  const QLane L = lanes[((size_t)dir * R + k) * TPn + u];
+__device__ __forceinline__ XLane lane_words(const QLane* __restrict__ lanes, int k, int TPn, uint32_t u,
+                                            uint32_t pb8) {
+  const QLane L = lanes[(size_t)k * TPn + u];
   XLane x;
   x.wb = L.wb ^ pb8;
   x.rb = L.rb ^ pb8;
@@ -255,7 +648,7 @@ __device__ __forceinline__ XLane lane_words(const QLane* __restrict__ lanes, int
 
 // Writes statevectors SV0 and SV1 to LDS planes PL and PL + 1 in the writer mapping wr.
 template <int T, int SV0, int SV1, int PL>
-__device__ __forceinline__ void xwrite(const float (&sr)[8][8], const float (&si)[8][8], float2* __restrict__ buf,
+__device__ __forceinline__ void rwrite(const float (&sr)[8][8], const float (&si)[8][8], float2* __restrict__ buf,
                                        const Offs& wo, uint32_t wb) {
   constexpr uint32_t PLANE = T * 8 * 8;   // bytes; a power of two above every in-plane offset
   char* b = reinterpret_cast<char*>(buf);
@@ -268,10 +661,9 @@ __device__ __forceinline__ void xwrite(const float (&sr)[8][8], const float (&si
   }
 }
 
-// Reads statevectors SV0 and SV1 back from planes PL, PL + 1 through the descriptor X.  SG = false:
-// the circuit has no CZ stage, so no exchange carries signs and the sign code is left out.
-template <int T, int SV0, int SV1, int PL, bool SG = true>
-__device__ __forceinline__ void xread(float (&sr)[8][8], float (&si)[8][8], const float2* __restrict__ buf,
+// Reads statevectors SV0 and SV1 back from planes PL, PL + 1 through the descriptor X.
+template <int T, int SV0, int SV1, int PL>
+__device__ __forceinline__ void rread(float (&sr)[8][8], float (&si)[8][8], const float2* __restrict__ buf,
                                       const Offs& ro, bool signs, uint32_t rb, uint32_t sgn) {
   // SV0 is read completely before SV1, so the gates on SV0 can start while SV1 is in flight.
   constexpr uint32_t PLANE = T * 8 * 8;   // bytes; a power of two above every in-plane offset
@@ -290,7 +682,7 @@ __device__ __forceinline__ void xread(float (&sr)[8][8], float (&si)[8][8], cons
       if (h == 0) { sr[SV0][r] = v.x; si[SV0][r] = v.y; } else { sr[SV1][r] = v.x; si[SV1][r] = v.y; }
     }
   __builtin_amdgcn_s_setprio(0);
-  if (SG && signs) {   // a CZ stage: negate the amplitudes whose sign bit is set (uniform branch)
+  if (signs) {   // a CZ stage: negate the amplitudes whose sign bit is set (uniform branch)
     // The empty volatile asm keeps this a branch: merged into the unconditional path, the flips
     // would cost two XORs per amplitude on every exchange and consume the loaded values at once,
     // which forces the LDS reads to complete before any independent work can cover them.
@@ -306,54 +698,21 @@ __device__ __forceinline__ void xread(float (&sr)[8][8], float (&si)[8][8], cons
   }
 }
 
-// Unpipelined exchange of statevectors [0, NSV) in groups of EXS planes (used when the LDS
-// holds only two planes per workgroup).
-template <int N, int T, int NSV, int EXS>
-__device__ __forceinline__ void exchange(float (&sr)[8][8], float (&si)[8][8], float2* __restrict__ buf,
-                                         CP<QXchg> X, const XLane& x) {
-  static_assert(EXS == 2, "pairs of planes");
+// The exchange of the four statevectors, pair by pair through planes 0 and 1 (up to 9 qubits inside a
+// wave; from 10 where the LDS holds only two planes per workgroup).
+template <int N, int T>
+__device__ __forceinline__ void rexchange(float (&sr)[8][8], float (&si)[8][8], float2* __restrict__ buf,
+                                          CP<QXchg> X, const XLane& x) {
   const Offs wo = load_offs(X->woff), ro = load_offs(X->roff);
   const bool sg = X->nterms != 0;
-#pragma unroll
-  for (int g = 0; g < NSV; g += 2) {
-    if (g == 0) xwrite<T, 0, 1, 0>(sr, si, buf, wo, x.wb);
-    if (g == 2) xwrite<T, 2, 3, 0>(sr, si, buf, wo, x.wb);
-    if (g == 4) xwrite<T, 4, 5, 0>(sr, si, buf, wo, x.wb);
-    if (g == 6) xwrite<T, 6, 7, 0>(sr, si, buf, wo, x.wb);
-    __syncthreads();
-    if (g == 0) xread<T, 0, 1, 0>(sr, si, buf, ro, sg, x.rb, x.sgn);
-    if (g == 2) xread<T, 2, 3, 0>(sr, si, buf, ro, sg, x.rb, x.sgn);
-    if (g == 4) xread<T, 4, 5, 0>(sr, si, buf, ro, sg, x.rb, x.sgn);
-    if (g == 6) xread<T, 6, 7, 0>(sr, si, buf, ro, sg, x.rb, x.sgn);
-    __syncthreads();
-  }
-}
-
-// Swap slot I of statevectors [S0, S0 + NSV): register bit I trades places with lane bit 4 + I
-// (thread bit 4 + I).  For each register pair (r, r | 2^I) a cross-lane swap exchanges odd rows of
-// the first with even rows of the second (lane bit 4, permlane16_swap) or the upper half of the
-// first with the lower half of the second (lane bit 5, permlane32_swap); the value at (register
-// bit q', lane bit h') afterwards is the one that was at (q = h', h = q').  An involution.
-template <int I, int S0, int NSV>
-__device__ __forceinline__ void swap_slot(float (&sr)[8][8], float (&si)[8][8]) {
-#pragma unroll
-  for (int s = S0; s < S0 + NSV; ++s)
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      if (r & (1 << I)) continue;
-      const int r1 = r | (1 << I);
-      if (I == 0) {
-        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(sr[s][r]), __float_as_int(sr[s][r1]), false, false);
-        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_int(si[s][r]), __float_as_int(si[s][r1]), false, false);
-        sr[s][r] = __int_as_float(a[0]); sr[s][r1] = __int_as_float(a[1]);
-        si[s][r] = __int_as_float(b[0]); si[s][r1] = __int_as_float(b[1]);
-      } else {
-        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_int(sr[s][r]), __float_as_int(sr[s][r1]), false, false);
-        const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(si[s][r]), __float_as_int(si[s][r1]), false, false);
-        sr[s][r] = __int_as_float(a[0]); sr[s][r1] = __int_as_float(a[1]);
-        si[s][r] = __int_as_float(b[0]); si[s][r1] = __int_as_float(b[1]);
-      }
-    }
+  rwrite<T, 0, 1, 0>(sr, si, buf, wo, x.wb);
+  point_fence<N>();
+  rread<T, 0, 1, 0>(sr, si, buf, ro, sg, x.rb, x.sgn);
+  point_fence<N>();
+  rwrite<T, 2, 3, 0>(sr, si, buf, wo, x.wb);
+  point_fence<N>();
+  rread<T, 2, 3, 0>(sr, si, buf, ro, sg, x.rb, x.sgn);
+  point_fence<N>();
 }
 
 // Forward gates of a round on statevectors S0, S0 + 1 (an absent gate is the identity entry):
@@ -374,11 +733,11 @@ template <int S0, int NS>
 __device__ __forceinline__ void finish(float (&sr)[8][8], float (&si)[8][8], const RoundCoef& R) {
   gate2<S0>(sr, si, R);
   if (NS > 0) {
-    swap_slot<0, S0, 2>(sr, si);
+    swap_slot<0, S0>(sr, si); swap_slot<0, S0 + 1>(sr, si);
     apply_gate<0, S0, 1>(sr, si, R.c + 24); apply_gate<0, S0 + 1, 1>(sr, si, R.c + 24);
   }
   if (NS > 1) {
-    swap_slot<1, S0, 2>(sr, si);
+    swap_slot<1, S0>(sr, si); swap_slot<1, S0 + 1>(sr, si);
     apply_gate<1, S0, 1>(sr, si, R.c + 32); apply_gate<1, S0 + 1, 1>(sr, si, R.c + 32);
   }
 }
@@ -388,120 +747,7 @@ __device__ __forceinline__ void round_fwd(float (&sr)[8][8], float (&si)[8][8], 
   finish<S0, NS>(sr, si, R);
 }
 
-// Adds v to a per-wave statistic slot in LDS with an LDS float add that returns nothing, so the
-// wave does not wait for its outstanding LDS operations as a read-modify-write would.  Each slot
-// belongs to one wave and receives one lane's value per flush, in program order, so the sums are
-// those of the read-modify-write, bit for bit.
-__device__ __forceinline__ void slot_add(float* p, float v) {
-  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Wave-reduces the round's gate statistics (register bits 0..2, then the NS swap slots) and adds
-// them to the per-wave LDS slots.
-template <int NS>
-__device__ __forceinline__ void round_stat_flush(const RoundCoef& R, float* __restrict__ slots, const float* q, int F,
-                                                 int wave, int lane) {
-#pragma unroll
-  for (int bb = 0; bb < 3 + NS; ++bb) {
-    const int gsrc = R.gid[bb];
-    const float v4[4] = {q[3 * bb], q[3 * bb + 1], q[3 * bb + 2], 0.f};
-    const float v = wave_reduce_scatter4(v4);
-    if (gsrc >= 0 && (lane & 15) == 0 && lane < 48) slot_add(slots + (wave * F + gsrc) * kGS + (lane >> 4), v);
-  }
-}
-
-// Adjoint of a round on the pair (C, 4 + C), starting in the round's output mapping: the swap-slot
-// gates are pulled back first, each gate's statistic taken right after its pull-back (q[9 + 3i]),
-// the swaps undone, then the three register-bit gates pulled back (their statistics follow in
-// stat_accum, at the round input).  PULL = false (a round of the leading stage): nothing is pulled
-// back; every statistic is taken at the stage output, where the stage's gates all commute.
-template <int C, int NS, bool PULL = true>
-__device__ __forceinline__ void round_adj(float (&sr)[8][8], float (&si)[8][8], const RoundCoef& R, float* q) {
-  if (NS > 1) {
-    if (PULL) { apply_gate<1, C, 1>(sr, si, R.c + 32); apply_gate<1, 4 + C, 1>(sr, si, R.c + 32); }
-    accum_s1<1, C>(sr, si, q + 12);
-    swap_slot<1, C, 1>(sr, si); swap_slot<1, 4 + C, 1>(sr, si);
-  }
-  if (NS > 0) {
-    if (PULL) { apply_gate<0, C, 1>(sr, si, R.c + 24); apply_gate<0, 4 + C, 1>(sr, si, R.c + 24); }
-    accum_s1<0, C>(sr, si, q + 9);
-    swap_slot<0, C, 1>(sr, si); swap_slot<0, 4 + C, 1>(sr, si);
-  }
-  if (PULL) {
-    apply_gate<2, C, 1>(sr, si, R.c + 16); apply_gate<2, 4 + C, 1>(sr, si, R.c + 16);
-    apply_gate<1, C, 1>(sr, si, R.c + 8);  apply_gate<1, 4 + C, 1>(sr, si, R.c + 8);
-    apply_gate<0, C, 1>(sr, si, R.c);      apply_gate<0, 4 + C, 1>(sr, si, R.c);
-  }
-}
-
-// The pair's share of the round's three register-bit gate statistics, q[3 b + k] += S_k(bit b).
-// These gates act on different qubits and commute, so every gate's statistic may be taken with
-// both statevectors at the round input (all three gates pulled back): then the pull-backs of the
-// other two gates cancel inside <lambda|sigma_b|psi>.
-template <int C>
-__device__ __forceinline__ void stat_accum(const float (&sr)[8][8], const float (&si)[8][8], float* q) {
-  accum_s1<0, C>(sr, si, q);
-  accum_s1<1, C>(sr, si, q + 3);
-  accum_s1<2, C>(sr, si, q + 6);
-}
-
-// One gate's eight coefficients, loaded and pinned in SGPRs like a round's (returned by value:
-// a local array read through apply_gate's selects would be kept in scratch memory instead).
-struct GateCoef {
-  float c[8];
-};
-__device__ __forceinline__ GateCoef load_gate(CP<float> g) {
-  GateCoef G;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) { G.c[e] = g[e]; pin_sgpr(G.c[e]); }
-  return G;
-}
-
-template <int NQ>
-__device__ __forceinline__ void pin_q(float* q) {
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) asm volatile("" : "+v"(q[i]));
-}
-
-// One gate of round_adj_all: all eight statevectors <- U^H on register bit B (unless PULL is
-// false: a gate of the leading stage), its statistic flushed at once.
-template <int B, bool PULL>
-__device__ __forceinline__ void adj_gate_all(float (&sr)[8][8], float (&si)[8][8], int gsrc, CP<float> gtab, int F,
-                                             float* __restrict__ slots, int wave, int lane) {
-  float q6[6];
-#pragma unroll
-  for (int e = 0; e < 6; ++e) q6[e] = 0.f;
-  if (PULL) {
-    const int gid = gsrc >= 0 ? gsrc : F;
-    const GateCoef d = load_gate(gtab + gid * kGT + 8);   // U^H
-    apply_gate<B, 0, 8>(sr, si, d.c);
-  }
-  accum_s<B>(sr, si, q6);
-  const float v4[4] = {q6[0] + q6[3], q6[1] + q6[4], q6[2] + q6[5], 0.f};
-  const float v = wave_reduce_scatter4(v4);
-  if (gsrc >= 0 && (lane & 15) == 0 && lane < 48) slot_add(slots + (wave * F + gsrc) * kGS + (lane >> 4), v);
-}
-
-// Adjoint of round rk on all four pairs, gate by gate (where no pipelining separates the pairs;
-// keeps one gate's values live at a time): swap-slot gates and swaps in reverse, then the
-// register-bit gates.
-template <int NS, bool PULL>
-__device__ __forceinline__ void round_adj_all(float (&sr)[8][8], float (&si)[8][8], CP<QRound> rk, CP<float> gtab,
-                                              int F, float* __restrict__ slots, int wave, int lane) {
-  if (NS > 1) {
-    adj_gate_all<1, PULL>(sr, si, rk->sgate[1], gtab, F, slots, wave, lane);
-    swap_slot<1, 0, 8>(sr, si);
-  }
-  if (NS > 0) {
-    adj_gate_all<0, PULL>(sr, si, rk->sgate[0], gtab, F, slots, wave, lane);
-    swap_slot<0, 0, 8>(sr, si);
-  }
-  adj_gate_all<2, PULL>(sr, si, rk->gate[2], gtab, F, slots, wave, lane);
-  adj_gate_all<1, PULL>(sr, si, rk->gate[1], gtab, F, slots, wave, lane);
-  adj_gate_all<0, PULL>(sr, si, rk->gate[0], gtab, F, slots, wave, lane);
-}
-
-// ---- phase stages (CRZ runs) ------------------------------------------------------------------
+// Phase stages (CRZ runs).
 // In a round's input mapping, slot k (register bit k < 3, thread bit k - 3 otherwise) holds the
 // index bit of qubit N - 1 - tpos[k].  phi(j) = sum_q alpha_q b_q + sum_(q<q') beta_qq' b_q b_q' is
 // split into the thread's part and per-register terms; all sums are unsigned 32-bit fractions of a
@@ -546,83 +792,24 @@ __device__ __forceinline__ void phase_factors(CP<QRound> rk, CP<uint32_t> coef, 
   }
 }
 
-// Multiply statevectors [S0, S0 + NS) by e^{+i phi} (CONJ: e^{-i phi}).
-template <int S0, int NS, bool CONJ>
-__device__ __forceinline__ void apply_phase(float (&sr)[8][8], float (&si)[8][8], const float (&pc)[8],
-                                            const float (&ps)[8]) {
-#pragma unroll
-  for (int s = S0; s < S0 + NS; ++s)
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float c = pc[r], sn = CONJ ? -ps[r] : ps[r];
-      const float a = sr[s][r], b = si[s][r];
-      sr[s][r] = a * c - b * sn;
-      si[s][r] = a * sn + b * c;
-    }
-}
-
-// Phase-stage moments of w_j = Im(conj(lambda_j) psi_j) + sum_c Im(conj(mu_c,j) dpsi_c,j): M_q and
-// M_qq' (q < q') summed over the wave, added to the wave's slots mslots[mom_off ...].
-template <int N>
-__device__ __forceinline__ void phase_moments(const float (&sr)[8][8], const float (&si)[8][8], CP<QRound> rk, uint32_t u,
-                                              float* __restrict__ mslots, int lane) {
-  float w[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    float v = 0.f;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) v += sr[4 + p][r] * si[p][r] - si[4 + p][r] * sr[p][r];
-    w[r] = v;
-  }
-  float Wi[3] = {0.f, 0.f, 0.f}, Wii[3] = {0.f, 0.f, 0.f}, Wt = 0.f;
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    Wt += w[r];
-    if (r & 1) Wi[0] += w[r];
-    if (r & 2) Wi[1] += w[r];
-    if (r & 4) Wi[2] += w[r];
-    if ((r & 3) == 3) Wii[0] += w[r];
-    if ((r & 5) == 5) Wii[1] += w[r];
-    if ((r & 6) == 6) Wii[2] += w[r];
-  }
-  int qk[N];
-#pragma unroll
-  for (int k = 0; k < N; ++k) qk[k] = N - 1 - rk->tpos[k];
-  auto flush = [&](float v, int idx) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    if (lane == 0) slot_add(mslots + idx, v);
-  };
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const float v = k < 3 ? Wi[k] : (((u >> (k - 3)) & 1u) ? Wt : 0.f);
-    flush(v, qk[k]);
-  }
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-#pragma unroll
-    for (int k2 = k + 1; k2 < N; ++k2) {
-      float v;
-      if (k2 < 3) v = Wii[k + k2 - 1];                                  // (0,1) (0,2) (1,2)
-      else if (k < 3) v = ((u >> (k2 - 3)) & 1u) ? Wi[k] : 0.f;
-      else v = (((u >> (k - 3)) & (u >> (k2 - 3))) & 1u) ? Wt : 0.f;
-      const int a = qk[k] < qk[k2] ? qk[k] : qk[k2], b = qk[k] < qk[k2] ? qk[k2] : qk[k];
-      flush(v, N + phase_pair_index(N, a, b));
-    }
-}
+template <int I>
+struct IntC {
+  static constexpr int value = I;
+};
 
 // ---- angle encoding of one qubit ------------------------------------------------------------
 // Embedded single-qubit state e(b) (b = 0, 1) and its angle derivative d(b) for qubit q, with the
 // Jacobian d theta_q / d(t, x, y).  RY: e = (cos, sin), RX: e = (cos, -i sin), of theta/2.  When the
 // circuit opens with a rotation stage, the qubit's gate U of that stage is applied here (e <- U e,
-// d <- U d): the stage acts on the product state, so the state after it is still a product.
+// d <- U d): the stage acts on the product state, so the state after it is still a product.  (The
+// rounds fold the stage's rounds but the circuit's last, the sweeps always the whole stage.)
 struct QEnc {
   float e0r, e0i, e1r, e1i, d0r, d0i, d1r, d1i, j[3];
 };
 
 template <int N>
 __device__ __forceinline__ QEnc encode_qubit(CP<QPlanDev> plan, CP<float> gtab, const FusedArgs& a, long long pt,
-                                             bool valid, const float* p3, int q) {
+                                             bool valid, const float* p3, int q, uint32_t x, bool rounds) {
   float c, s, j0 = 0.f, j1 = 0.f, j2 = 0.f;
   if (plan->enc_kind == QP_ENC_CYCLE) {
     const int cc = plan->coord_of_qubit[q];
@@ -666,7 +853,7 @@ __device__ __forceinline__ QEnc encode_qubit(CP<QPlanDev> plan, CP<float> gtab, 
   } else {   // RX|0> = (cos, -i sin)
     E.e1r = 0.f; E.e1i = -s; E.d1r = 0.f; E.d1i = -0.5f * c;
   }
-  const int hg = plan->head_gate[q];
+  const int hg = rounds ? plan->head_gate[q] : plan->hgate[q];
   if (hg >= 0) {
     CP<float> g = gtab + hg * kGT;   // U: u00r, u00i, u01r, u01i, u10r, u10i, u11r, u11i
     const float xr = E.e0r, xi = E.e0i, yr = E.e1r, yi = E.e1i;
@@ -681,6 +868,11 @@ __device__ __forceinline__ QEnc encode_qubit(CP<QPlanDev> plan, CP<float> gtab, 
     E.d1i = g[4] * ai + g[5] * ar + g[6] * bi + g[7] * br;
   }
   E.j[0] = j0; E.j[1] = j1; E.j[2] = j2;
+  if (!rounds && ((x >> (N - 1 - q)) & 1u)) {   // the sweeps' X mask in front of the first layer
+    const QEnc D = E;
+    E.e0r = D.e1r; E.e0i = D.e1i; E.e1r = D.e0r; E.e1i = D.e0i;
+    E.d0r = D.d1r; E.d0i = D.d1i; E.d1r = D.d0r; E.d1i = D.d0i;
+  }
   return E;
 }
 
@@ -693,8 +885,8 @@ __device__ __forceinline__ QEnc encode_qubit(CP<QPlanDev> plan, CP<float> gtab, 
 // the same Pauli statistics the adjoint takes for every gate, but per point.  When the circuit's
 // opening rotation stage is folded into the encoding, the sweep ends at that stage's output, and
 // G_q is replaced by U_q G_q U_q^H (U_q the stage's gate on qubit q), which the statistics
-// contract with as an axis (n_x, n_y, n_z).  At the end of the sweep the statevectors sit in round
-// 0's input mapping.  The partner amplitude of a pair (index bit of qubit q flipped) lies in the
+// contract with as an axis (n_x, n_y, n_z).  At the end of the sweep the statevectors sit in mapping
+// gtpos.  The partner amplitude of a pair (index bit of qubit q flipped) lies in the
 // same thread (register bit) or in another thread of the point (thread bit); it is read back from
 // the LDS planes, where the psi-family is staged two statevectors at a time.
 template <int N, int T>
@@ -713,21 +905,22 @@ __device__ __forceinline__ float enc_pair(float nx, float ny, float nz, float sb
 template <int N, int T, int PASS>
 __device__ __forceinline__ void enc_grad_pass(const float (&sr)[8][8], const float (&si)[8][8],
                                               float2* __restrict__ buf, float* __restrict__ red, CP<QPlanDev> plan,
-                                              CP<QRound> r0, CP<float> gtab, uint32_t jl, const FusedArgs& a,
+                                              CP<float> gtab, uint32_t jl, const FusedArgs& a,
                                               long long pt, bool valid, uint32_t u) {
   constexpr int PLANE = T * 8;
   constexpr int TP = 1 << (N - 3);
   const uint32_t tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const uint32_t l0 = r0->tpos[0], l1 = r0->tpos[1], l2 = r0->tpos[2];
-  __syncthreads();   // the planes are free (every wave is past its last read of the sweep)
+  CP<int32_t> gt = plan->gtpos;
+  const uint32_t l0 = gt[0], l1 = gt[1], l2 = gt[2];
+  point_fence<N>();   // the planes are free (every wave of the point is past its last read of the sweep)
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const uint32_t e = tid * 8 + (r ^ (tid & 7));
     buf[e] = make_float2(sr[2 * PASS][r], si[2 * PASS][r]);
     buf[PLANE + e] = make_float2(sr[2 * PASS + 1][r], si[2 * PASS + 1][r]);
   }
-  __syncthreads();
+  point_fence<N>();
   const bool rx = plan->enc_gate == QP_ENC_RX;
 #pragma unroll 1
   for (int q = 0; q < N; ++q) {
@@ -735,14 +928,14 @@ __device__ __forceinline__ void enc_grad_pass(const float (&sr)[8][8], const flo
     uint32_t rmask = 0, tmask = 0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      if (r0->tpos[k] == pos) {
+      if (gt[k] == pos) {
         if (k < 3) rmask = 1u << k;
-        else tmask = 1u << (k - 3);
+        else tmask = sweep_xor(k - 3);
       }
     }
     // axis of U G U^H (U: the opening-stage gate on q, identity if none; G = X or Y)
     float u8[8] = {1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 1.f, 0.f};
-    const int hg = plan->head_gate[q];
+    const int hg = plan->hgate[q];
     if (hg >= 0) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) u8[i] = gtab[hg * kGT + i];
@@ -827,19 +1020,20 @@ __device__ __forceinline__ void enc_grad_pass(const float (&sr)[8][8], const flo
 template <int N, int T>
 __device__ __forceinline__ void encoding_grads(const float (&sr)[8][8], const float (&si)[8][8],
                                                float2* __restrict__ buf, float* __restrict__ red, CP<QPlanDev> plan,
-                                               CP<QRound> r0, CP<float> gtab, const FusedArgs& a, long long pt,
+                                               CP<float> gtab, const FusedArgs& a, long long pt,
                                                bool valid, uint32_t u) {
-  const uint32_t jl = deposit_thread<N>(u, r0->tpos);
-  enc_grad_pass<N, T, 0>(sr, si, buf, red, plan, r0, gtab, jl, a, pt, valid, u);
-  enc_grad_pass<N, T, 1>(sr, si, buf, red, plan, r0, gtab, jl, a, pt, valid, u);
-  __syncthreads();   // the next tile's first exchange writes the planes
+  const uint32_t jl = deposit_thread<N>(sweep_thread(u, N), plan->gtpos) ^ to_const(a.xmask)[plan->n_sweeps];
+  enc_grad_pass<N, T, 0>(sr, si, buf, red, plan, gtab, jl, a, pt, valid, u);
+  enc_grad_pass<N, T, 1>(sr, si, buf, red, plan, gtab, jl, a, pt, valid, u);
+  point_fence<N>();   // the next tile's first exchange writes the planes
 }
 
 // Packed modes: the product state of point pt0 + SL in statevector slot SL, formed in the mapping
 // emap (no input tangents; an out-of-range point gives the zero state).
 template <int N, int SL>
 __device__ __forceinline__ void packed_state(float (&sr)[8][8], float (&si)[8][8], CP<QPlanDev> plan, CP<float> gtab,
-                                             const FusedArgs& a, long long pt0, uint32_t u, CP<int32_t> emap) {
+                                             const FusedArgs& a, long long pt0, uint32_t v, CP<int32_t> emap, uint32_t x,
+                                             bool rounds) {
   const long long pts = pt0 + SL;
   const bool vs = pts < a.P;
   float q3[3] = {0.f, 0.f, 0.f};
@@ -851,15 +1045,15 @@ __device__ __forceinline__ void packed_state(float (&sr)[8][8], float (&si)[8][8
   float Pr = vs ? 1.f : 0.f, Pi = 0.f;
 #pragma unroll 1
   for (int k = 3; k < N; ++k) {
-    const QEnc E = encode_qubit<N>(plan, gtab, a, pts, vs, q3, N - 1 - emap[k]);
-    const bool bit = (u >> (k - 3)) & 1u;
+    const QEnc E = encode_qubit<N>(plan, gtab, a, pts, vs, q3, N - 1 - emap[k], x, rounds);
+    const bool bit = (v >> (k - 3)) & 1u;
     const float er = bit ? E.e1r : E.e0r, ei = bit ? E.e1i : E.e0i;
     const float npr = Pr * er - Pi * ei, npi = Pr * ei + Pi * er;
     Pr = npr; Pi = npi;
   }
   QEnc Q[3];
 #pragma unroll
-  for (int i = 0; i < 3; ++i) Q[i] = encode_qubit<N>(plan, gtab, a, pts, vs, q3, N - 1 - emap[i]);
+  for (int i = 0; i < 3; ++i) Q[i] = encode_qubit<N>(plan, gtab, a, pts, vs, q3, N - 1 - emap[i], x, rounds);
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     float pr = Pr, pi = Pi;
@@ -875,10 +1069,15 @@ __device__ __forceinline__ void packed_state(float (&sr)[8][8], float (&si)[8][8
 }
 
 // ---- one tile of PPW points: forward, readout, seeds, adjoint --------------------------------
-// buf: EXS exchange planes; slots: per-wave gate statistics [WAVES][F][kGS]; red: [WAVES][40].
-// PH: the plan may carry CRZ phase stages (false where the caller knows it has none, as the
-// uneven-batch kernels do for such circuits: the phase code is then compiled out).
-template <int N, int T, int EXS, int MODE, bool SG = true, bool EG = false, bool PH = true>
+// buf: exchange planes (one up to 9 qubits, two with input gradients; else EXS); slots: per-wave gate
+// statistics [WAVES][F][kGS]; mslots: per-wave parity sums of CRZ layers; red: [WAVES][40].
+//
+// What bounds it: VALU issue.  Per amplitude and layer a statevector costs N multiply-adds per real
+// number and one complex product, the statistics of a gate 4 multiply-adds per amplitude and
+// statevector pair for each of S_x and S_y, and S_z of all gates together 2; LDS moves every
+// statevector once per layer (twice from 10 qubits, where the wave bits are brought into registers
+// through it).
+template <int N, int T, int EXS, int MODE, bool EG = false>
 __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2* __restrict__ buf,
                                            float* __restrict__ slots, float* __restrict__ mslots,
                                            float* __restrict__ red, float& lacc) {
@@ -886,18 +1085,18 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
   constexpr int PPW = T / TP;              // points per workgroup tile (x4 in the packed modes)
   constexpr int DIM = 1 << N;
   constexpr bool PK = mode_packed(MODE);
+  constexpr bool RND = mode_rounds(MODE);  // forward by rounds (see there), else by sweep layers
   static_assert(PPW >= 1, "tile too small");
   static_assert(!(PK && EG), "the packed modes carry no input gradients");
   CP<QPlanDev> plan = to_const(a.plan);
   CP<char> pb = reinterpret_cast<CP<char>>(plan);
-  CP<QRound> rounds = reinterpret_cast<CP<QRound>>(pb + plan->off_rounds);
-  CP<QXchg> xf = reinterpret_cast<CP<QXchg>>(pb + plan->off_xf);
-  CP<QXchg> xb = reinterpret_cast<CP<QXchg>>(pb + plan->off_xb);
+  CP<QSweep> sweeps = reinterpret_cast<CP<QSweep>>(pb + plan->off_sweeps);
+  const uint4* __restrict__ slanes =
+      reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.plan) + plan->off_slanes);
   CP<float> gtab = to_const(a.gtab);
-  // phase stages: descriptors in the plan, coefficients after the gate table
-  const QPhaseStage* pstages = reinterpret_cast<const QPhaseStage*>(reinterpret_cast<const char*>(a.plan) + plan->off_phase);
-  CP<uint32_t> pcoef = reinterpret_cast<CP<uint32_t>>(gtab + (a.n_fused + 1) * kGT);
-  const int R = plan->n_rounds;
+  CP<QRound> rounds = reinterpret_cast<CP<QRound>>(pb + plan->off_rounds);
+  CP<float> tcoef = to_const(a.tcoef);
+  const int L0 = plan->sweep_first, L1 = plan->n_sweeps;
   const int m = plan->n_out;
   const int F = a.n_fused;
   const int tid = threadIdx.x;
@@ -905,7 +1104,16 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
   const int wave = tid >> 6;
   const int ps = tid / TP;
   const uint32_t u = (uint32_t)(tid % TP);
+  const uint32_t v = sweep_thread(u, N);   // the thread's index bits
   const uint32_t pbase = (uint32_t)ps * DIM;
+  const uint32_t pb8 = swz(pbase) * 8u;
+  // wave exchange: bases of the thread's writes and reads (see wwrite)
+  constexpr int WPP = TP > 64 ? TP / 64 : 1;
+  const uint32_t wvb = (uint32_t)((wave / WPP) * WPP * 4096 + (wave % WPP) * 512 + lane * 8);
+  const uint32_t rvb = (uint32_t)(wave * 4096 + lane * 8);
+  const float4* __restrict__ ptab = reinterpret_cast<const float4*>(a.ptab) + u * 4;   // this thread's entries, per layer
+  auto phase_of = [&](int l) { return load_phase(ptab + (size_t)(l - L0) * (DIM / 2)); };
+  auto lane_of = [&](int l) { return slanes[(size_t)l * TP + u]; };
   // loss weights: 1/P for the mean over all points, 1/N_vac and 1/N_diel for the split loss
   float w_all = 1.f, w_vac = 1.f, w_diel = 1.f;
   if ((MODE == kModeMaxwell || MODE == kModeTotal) && !a.loss_sum) {
@@ -924,11 +1132,12 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
     const bool valid = pt < a.P;
 
     // ---------------- encoding and product state -------------------------------------------
-    // The leading rotation stage (rounds 0 .. H-1) is folded into the product state, which is
-    // then formed in round H-1's output mapping (round 0's input mapping if H = 0).  Each qubit's
-    // embedded amplitudes are formed where they are used (qubit index uniform across the
-    // workgroup), so no per-qubit arrays are indexed at run time.
+    // An opening rotation stage is folded into the product state, which is formed in that layer's
+    // output mapping.  Each qubit's embedded amplitudes are formed where they are used (qubit index
+    // uniform across the workgroup), so no per-qubit arrays are indexed at run time.
     const int H = plan->n_head;
+    CP<int32_t> emap = !RND ? plan->etpos : (H > 0 ? rounds[H - 1].tpost : rounds[0].tpos);
+    const uint32_t ve = RND ? u : v, xe = to_const(a.xmask)[L1];   // thread bits of the mapping; X mask of the product state
     float p3[3] = {0.f, 0.f, 0.f};
     if (valid && a.points && plan->enc_kind != QP_ENC_ANGLES) {
       p3[0] = a.points[pt * 3 + 0];
@@ -938,20 +1147,18 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
     if constexpr (PK) {
       // four product states, one per slot (no tangents); one call per slot keeps the slot index
       // a compile-time constant (the statevector arrays stay in registers)
-      CP<int32_t> emap = H > 0 ? rounds[H - 1].tpost : rounds[0].tpos;
-      packed_state<N, 0>(sr, si, plan, gtab, a, pt0, u, emap);
-      packed_state<N, 1>(sr, si, plan, gtab, a, pt0, u, emap);
-      packed_state<N, 2>(sr, si, plan, gtab, a, pt0, u, emap);
-      packed_state<N, 3>(sr, si, plan, gtab, a, pt0, u, emap);
+      packed_state<N, 0>(sr, si, plan, gtab, a, pt0, ve, emap, xe, RND);
+      packed_state<N, 1>(sr, si, plan, gtab, a, pt0, ve, emap, xe, RND);
+      packed_state<N, 2>(sr, si, plan, gtab, a, pt0, ve, emap, xe, RND);
+      packed_state<N, 3>(sr, si, plan, gtab, a, pt0, ve, emap, xe, RND);
     } else {
-      CP<int32_t> emap = H > 0 ? rounds[H - 1].tpost : rounds[0].tpos;
       // thread part: (P, D_c) by the product rule over the thread qubits
       float Pr = valid ? 1.f : 0.f, Pi = 0.f;
       float Dr[3] = {0.f, 0.f, 0.f}, Di[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int k = 3; k < N; ++k) {
-        const QEnc E = encode_qubit<N>(plan, gtab, a, pt, valid, p3, N - 1 - emap[k]);
-        const bool bit = (u >> (k - 3)) & 1u;
+        const QEnc E = encode_qubit<N>(plan, gtab, a, pt, valid, p3, N - 1 - emap[k], xe, RND);
+        const bool bit = (ve >> (k - 3)) & 1u;
         const float er = bit ? E.e1r : E.e0r, ei = bit ? E.e1i : E.e0i;
         const float dr = bit ? E.d1r : E.d0r, di = bit ? E.d1i : E.d0i;
 #pragma unroll
@@ -965,7 +1172,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
       }
       QEnc Q[3];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) Q[i] = encode_qubit<N>(plan, gtab, a, pt, valid, p3, N - 1 - emap[i]);
+      for (int i = 0; i < 3; ++i) Q[i] = encode_qubit<N>(plan, gtab, a, pt, valid, p3, N - 1 - emap[i], xe, RND);
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
         float pr = Pr, pi = Pi, dr[3] = {Dr[0], Dr[1], Dr[2]}, di[3] = {Di[0], Di[1], Di[2]};
@@ -988,88 +1195,182 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
         for (int c = 0; c < 3; ++c) { sr[1 + c][r] = dr[c]; si[1 + c][r] = di[c]; }
       }
     }
-    // ---------------- forward rounds -------------------------------------------------------
-    constexpr int NS = swap_slots(N);
-    const QLane* __restrict__ lanes = reinterpret_cast<const QLane*>(reinterpret_cast<const char*>(a.plan) + plan->off_lanes);
-    const uint32_t pb8 = swz(pbase) * 8u;
-    if constexpr (EXS == 4) {
-      // Software-pipelined: group A = statevectors {0, 1} (planes 0, 1), group B = {2, 3}
-      // (planes 2, 3).  Each slot reads one group, finishes the other group's round (its bit-2
-      // gate and swap slots) and writes it, then runs the bit-0/1 gates of the group just read:
-      // the finishing work covers the read latency and the writes drain under the following
-      // gates.  Every barrier separates a plane pair's reads from its next writes.
-      // All four statevectors complete in round k0 - 1's output mapping: the encoding leaves them
-      // there when the opening stage is folded (k0 = H); otherwise round 0 runs here (k0 = 1).
-      int k0 = H;
-      RoundCoef Rc = load_round<false, NS>(rounds + (H > 0 ? H - 1 : 0), gtab, F);
-      if (k0 == 0) {
-        round_fwd<0, NS>(sr, si, Rc);
-        round_fwd<2, NS>(sr, si, Rc);
-        k0 = 1;
-      }
-      if (k0 < R) {
-        Offs wo = load_offs(xf[k0].woff);
-        // lane words of the current exchange as scalars (updated inside the lambda below)
-        uint32_t xwb, xrb, xsg;
-        {
-          const XLane x0 = lane_words(lanes, 0, R, k0, TP, u, pb8);
-          xwb = x0.wb; xrb = x0.rb; xsg = x0.sgn;
+    // ---------------- forward ----------------------------------------------------------------
+    if constexpr (RND) {
+      constexpr int NS = swap_slots(N);
+      CP<QXchg> xf = reinterpret_cast<CP<QXchg>>(pb + plan->off_xf);
+      const QLane* __restrict__ lanes =
+          reinterpret_cast<const QLane*>(reinterpret_cast<const char*>(a.plan) + plan->off_lanes);
+      const int R = plan->n_rounds;
+      if constexpr (N >= 10 && EXS == 4) {
+        // Software-pipelined: group A = statevectors {0, 1} (planes 0, 1), group B = {2, 3} (planes 2, 3).
+        // Each slot reads one group, finishes the other group's round (its bit-2 gate and swap slots)
+        // and writes it, then runs the bit-0/1 gates of the group just read: the finishing work covers
+        // the read latency and the writes drain under the following gates.  Every barrier separates a
+        // plane pair's reads from its next writes.
+        // All four statevectors complete in round k0 - 1's output mapping: the encoding leaves them
+        // there when the opening stage is folded (k0 = H); otherwise round 0 runs here (k0 = 1).
+        int k0 = H;
+        RoundCoef Rc = load_round<NS>(rounds + (H > 0 ? H - 1 : 0), gtab, a.n_gates);
+        if (k0 == 0) {
+          round_fwd<0, NS>(sr, si, Rc);
+          round_fwd<2, NS>(sr, si, Rc);
+          k0 = 1;
         }
-        xwrite<T, 0, 1, 0>(sr, si, buf, wo, xwb);
-        // Iteration k: group A is read and runs round k; group B lags by half a round (it finishes
-        // round k - 1 while A's read is in flight, except in the first iteration, where it is
-        // complete).  The first iteration is peeled so that neither copy has a branch around
-        // group B's work.
-        auto iter = [&](int k, auto lag) {
-          constexpr bool LAG = decltype(lag)::value;
+        if (k0 < R) {
+          Offs wo = load_offs(xf[k0].woff);
+          // lane words of the current exchange as scalars (updated inside the lambda below)
+          uint32_t xwb, xrb, xsg;
+          {
+            const XLane x0 = lane_words(lanes, k0, TP, u, pb8);
+            xwb = x0.wb; xrb = x0.rb; xsg = x0.sgn;
+          }
+          rwrite<T, 0, 1, 0>(sr, si, buf, wo, xwb);
+          // Iteration k: group A is read and runs round k; group B lags by half a round (it finishes
+          // round k - 1 while A's read is in flight, except in the first iteration, where it is
+          // complete).  The first iteration is peeled so that neither copy has a branch around
+          // group B's work.
+          auto iter = [&](int k, auto lag) {
+            constexpr bool LAG = decltype(lag)::value != 0;
+            CP<QRound> rk = rounds + k;
+            const RoundCoef Rk = load_round<NS>(rk, gtab, a.n_gates);
+            const Offs ro = load_offs(xf[k].roff);
+            const bool sg = xf[k].nterms != 0;
+            // the next exchange's lane words: a vector load issued a whole round ahead of its use
+            XLane xn{xwb, xrb, xsg};
+            if (k + 1 < R) xn = lane_words(lanes, k + 1, TP, u, pb8);
+            __syncthreads();
+            rread<T, 0, 1, 0>(sr, si, buf, ro, sg, xrb, xsg);
+            if (LAG) finish<2, NS>(sr, si, Rc);          // group B finishes round k - 1
+            rwrite<T, 2, 3, 2>(sr, si, buf, wo, xwb);
+            gates01<0>(sr, si, Rk);
+            pin_sv<0>(sr, si); pin_sv<1>(sr, si);
+            // The next exchange's write offsets, loaded before the barrier: scalar loads share the
+            // wait counter with LDS operations, and waiting here costs nothing.
+            if (k + 1 < R) wo = load_offs(xf[k + 1].woff);
+            __syncthreads();
+            rread<T, 2, 3, 2>(sr, si, buf, ro, sg, xrb, xsg);
+            finish<0, NS>(sr, si, Rk);                   // group A finishes round k
+            if (k + 1 < R) rwrite<T, 0, 1, 0>(sr, si, buf, wo, xn.wb);
+            gates01<2>(sr, si, Rk);
+            pin_sv<2>(sr, si); pin_sv<3>(sr, si);
+            xwb = xn.wb; xrb = xn.rb; xsg = xn.sgn;
+            Rc = Rk;
+          };
+          iter(k0, IntC<0>{});
+          for (int k = k0 + 1; k < R; ++k) iter(k, IntC<1>{});
+          __syncthreads();
+          finish<2, NS>(sr, si, Rc);                     // group B finishes the last round
+        }
+      } else {
+        CP<uint32_t> pcoef = reinterpret_cast<CP<uint32_t>>(gtab + (a.n_gates + 1) * kGT);
+        const QPhaseStage* pstages =
+            reinterpret_cast<const QPhaseStage*>(reinterpret_cast<const char*>(a.plan) + plan->off_phase);
+        for (int k = H; k < R; ++k) {
           CP<QRound> rk = rounds + k;
-          const RoundCoef Rk = load_round<false, NS>(rk, gtab, F);
-          const Offs ro = load_offs(xf[k].roff);
-          const bool sg = xf[k].nterms != 0;
-          // the next exchange's lane words: a vector load issued a whole round ahead of its use
-          XLane xn{xwb, xrb, xsg};
-          if (k + 1 < R) xn = lane_words(lanes, 0, R, k + 1, TP, u, pb8);
+          if (k > 0) rexchange<N, T>(sr, si, buf, xf + k, lane_words(lanes, k, TP, u, pb8));
+          if (rk->phase >= 0) {   // CRZ phase stage after the exchange
+            float pc[8], ps[8];
+            phase_factors<N>(rk, pcoef + to_const(pstages)[rk->phase].coef_off, u, pc, ps);
+            mul_phase<0, false>(sr, si, pc, ps); mul_phase<1, false>(sr, si, pc, ps);
+            mul_phase<2, false>(sr, si, pc, ps); mul_phase<3, false>(sr, si, pc, ps);
+          }
+          const RoundCoef Rk = load_round<NS>(rk, gtab, a.n_gates);
+          round_fwd<0, NS>(sr, si, Rk);
+          round_fwd<2, NS>(sr, si, Rk);
+        }
+      }
+    } else if constexpr (N < 10) {
+      for (int l = L0; l < L1; ++l) {
+        CP<QSweep> L = sweeps + l;
+        const Phase P = phase_of(l);
+        const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, false);
+        if (L->flags & kSweepXchg) {
+          const uint4 w = lane_of(l);
+          const Addr A = xchg_addr(L->woff, L->roff, w.x ^ pb8, w.y ^ pb8);
+          exchange_wave<T, 0, 4>(sr, si, buf, A);
+        }
+        layer_fwd<N, 0>(sr, si, K, P);
+        layer_fwd<N, 1>(sr, si, K, P);
+        layer_fwd<N, 2>(sr, si, K, P);
+        layer_fwd<N, 3>(sr, si, K, P);
+      }
+    } else if constexpr (EXS == 4) {
+      // Statevectors {0, 1} go through planes 0 and 1, {2, 3} through planes 2 and 3: between two
+      // barriers one group is read and rotated while the other is written, so every barrier
+      // separates a plane's reads from its next writes.
+      Addr A;
+      auto addr = [&](int l) {
+        const uint4 w = lane_of(l);
+        A = xchg_addr(sweeps[l].woff, sweeps[l].roff, w.x ^ pb8, w.y ^ pb8);
+      };
+      if (L0 < L1 && (sweeps[L0].flags & kSweepXchg)) {
+        addr(L0);
+        xwrite<T, 0, 0>(sr, si, buf, A.w); xwrite<T, 1, 1>(sr, si, buf, A.w);
+      }
+      for (int l = L0; l < L1; ++l) {
+        CP<QSweep> L = sweeps + l;
+        const bool moves = L->flags & kSweepXchg;
+        const Phase P = phase_of(l);
+        const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, false);
+        if (moves) {
           __syncthreads();
-          xread<T, 0, 1, 0, SG>(sr, si, buf, ro, sg, xrb, xsg);
-          if (LAG) finish<2, NS>(sr, si, Rc);          // group B finishes round k - 1
-          xwrite<T, 2, 3, 2>(sr, si, buf, wo, xwb);
-          gates01<0>(sr, si, Rk);
-          pin_sv<0>(sr, si); pin_sv<1>(sr, si);
-          // The next exchange's write offsets, loaded before the barrier: scalar loads share the
-          // wait counter with LDS operations, and waiting here costs nothing.
-          if (k + 1 < R) wo = load_offs(xf[k + 1].woff);
+          xread<T, 0, 0>(sr, si, buf, A.r); xread<T, 1, 1>(sr, si, buf, A.r);
+          xwrite<T, 2, 2>(sr, si, buf, A.w); xwrite<T, 3, 3>(sr, si, buf, A.w);
+        }
+        layer_fwd<N, 0>(sr, si, K, P);
+        layer_fwd<N, 1>(sr, si, K, P);
+        if (moves) {
           __syncthreads();
-          xread<T, 2, 3, 2, SG>(sr, si, buf, ro, sg, xrb, xsg);
-          finish<0, NS>(sr, si, Rk);                   // group A finishes round k
-          if (k + 1 < R) xwrite<T, 0, 1, 0>(sr, si, buf, wo, xn.wb);
-          gates01<2>(sr, si, Rk);
-          pin_sv<2>(sr, si); pin_sv<3>(sr, si);
-          xwb = xn.wb; xrb = xn.rb; xsg = xn.sgn;
-          Rc = Rk;
-        };
-        iter(k0, BoolC<false>{});
-        for (int k = k0 + 1; k < R; ++k) iter(k, BoolC<true>{});
+          xread<T, 2, 2>(sr, si, buf, A.r); xread<T, 3, 3>(sr, si, buf, A.r);
+        }
+        wwrite<N, T, 0, 0>(sr, si, buf, wvb); wwrite<N, T, 1, 1>(sr, si, buf, wvb);
+        layer_fwd<N, 2>(sr, si, K, P);
+        layer_fwd<N, 3>(sr, si, K, P);
         __syncthreads();
-        finish<2, NS>(sr, si, Rc);                     // group B finishes the last round
+        wread<N, T, 0, 0>(sr, si, buf, rvb); wread<N, T, 1, 1>(sr, si, buf, rvb);
+        wwrite<N, T, 2, 2>(sr, si, buf, wvb); wwrite<N, T, 3, 3>(sr, si, buf, wvb);
+        rot_wave<N, 0>(sr, si, K); rot_wave<N, 1>(sr, si, K);
+        __syncthreads();
+        wread<N, T, 2, 2>(sr, si, buf, rvb); wread<N, T, 3, 3>(sr, si, buf, rvb);
+        if (l + 1 < L1 && (sweeps[l + 1].flags & kSweepXchg)) {
+          addr(l + 1);
+          xwrite<T, 0, 0>(sr, si, buf, A.w); xwrite<T, 1, 1>(sr, si, buf, A.w);
+        }
+        rot_wave<N, 2>(sr, si, K); rot_wave<N, 3>(sr, si, K);
       }
     } else {
-      for (int k = H; k < R; ++k) {
-        CP<QRound> rk = rounds + k;
-        if (k > 0) exchange<N, T, 4, 2>(sr, si, buf, xf + k, lane_words(lanes, 0, R, k, TP, u, pb8));
-        if (PH && rk->phase >= 0) {   // CRZ phase stage after the exchange (unpipelined kernel only)
-          float pc[8], ps[8];
-          phase_factors<N>(rk, pcoef + to_const(pstages)[rk->phase].coef_off, u, pc, ps);
-          apply_phase<0, 4, false>(sr, si, pc, ps);
-        }
-        const RoundCoef Rk = load_round<false, NS>(rk, gtab, F);
-        round_fwd<0, NS>(sr, si, Rk);
-        round_fwd<2, NS>(sr, si, Rk);
+      for (int l = L0; l < L1; ++l) {
+        CP<QSweep> L = sweeps + l;
+        const Phase P = phase_of(l);
+        const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, false);
+        const bool moves = L->flags & kSweepXchg;
+        const uint4 w = lane_of(l);
+        const Addr A = xchg_addr(L->woff, L->roff, w.x ^ pb8, w.y ^ pb8);
+        auto pair = [&](auto c) {
+          constexpr int S = decltype(c)::value;
+          if (moves) {
+            xwrite<T, S, 0>(sr, si, buf, A.w); xwrite<T, S + 1, 1>(sr, si, buf, A.w);
+            __syncthreads();
+            xread<T, S, 0>(sr, si, buf, A.r); xread<T, S + 1, 1>(sr, si, buf, A.r);
+            __syncthreads();
+          }
+          layer_fwd<N, S>(sr, si, K, P);
+          layer_fwd<N, S + 1>(sr, si, K, P);
+          wwrite<N, T, S, 0>(sr, si, buf, wvb); wwrite<N, T, S + 1, 1>(sr, si, buf, wvb);
+          __syncthreads();
+          wread<N, T, S, 0>(sr, si, buf, rvb); wread<N, T, S + 1, 1>(sr, si, buf, rvb);
+          __syncthreads();
+          rot_wave<N, S>(sr, si, K); rot_wave<N, S + 1>(sr, si, K);
+        };
+        pair(IntC<0>{});
+        pair(IntC<2>{});
       }
     }
     // ---------------- readout ----------------------------------------------------------------
-    CP<QRound> rl = rounds + (R - 1);   // the statevectors are in the last round's output mapping
-    const uint32_t jl = deposit_thread<N>(u, rl->tpost);
-    const uint32_t l0 = rl->tpost[0], l1 = rl->tpost[1], l2 = rl->tpost[2];
+    CP<int32_t> ft = RND ? rounds[plan->n_rounds - 1].tpost : plan->ftpos;
+    uint32_t jl = deposit_thread<N>(RND ? u : v, ft);
+    uint32_t l0 = ft[0], l1 = ft[1], l2 = ft[2];
     float acc[kMaxOut * 4];
 #pragma unroll
     for (int i = 0; i < kMaxOut * 4; ++i) acc[i] = 0.f;
@@ -1222,6 +1523,32 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
         }
       }
     }
+    if constexpr (RND) {
+      // From the rounds' mapping to the sweeps', and behind the last layer's diagonal part (which the
+      // readout does not see): an exchange and a phase.
+      CP<QTurn> turn = reinterpret_cast<CP<QTurn>>(pb + plan->off_turn);
+      const uint2 w = reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(a.plan) + plan->off_tlanes)[u];
+      const Addr A = xchg_addr(turn->woff, turn->roff, w.x ^ pb8, w.y ^ pb8);
+      const Phase P = phase_of(L1);
+      if constexpr (N < 10) {
+        exchange_wave<T, 0, 4>(sr, si, buf, A);
+      } else {
+        __syncthreads();
+        xwrite<T, 0, 0>(sr, si, buf, A.w); xwrite<T, 1, 1>(sr, si, buf, A.w);
+        __syncthreads();
+        xread<T, 0, 0>(sr, si, buf, A.r); xread<T, 1, 1>(sr, si, buf, A.r);
+        __syncthreads();
+        xwrite<T, 2, 0>(sr, si, buf, A.w); xwrite<T, 3, 1>(sr, si, buf, A.w);
+        __syncthreads();
+        xread<T, 2, 0>(sr, si, buf, A.r); xread<T, 3, 1>(sr, si, buf, A.r);
+        __syncthreads();
+      }
+      mul_phase<0, true>(sr, si, P.c, P.s); mul_phase<1, true>(sr, si, P.c, P.s);
+      mul_phase<2, true>(sr, si, P.c, P.s); mul_phase<3, true>(sr, si, P.c, P.s);
+      CP<int32_t> f2 = plan->ftpos;
+      jl = deposit_thread<N>(v, f2);
+      l0 = f2[0]; l1 = f2[1]; l2 = f2[2];
+    }
     // lambda = Df psi + sum_c D_c dpsi_c, mu_c = D_c psi (D real diagonal in the final basis)
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -1251,105 +1578,141 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
       }
     }
     // ---------------- adjoint sweep with uncompute -----------------------------------------
-    // Per round in reverse: psi-family <- U^H (uncompute), lambda-family <- U^H, gate statistics,
-    // then the inverse exchange.  The pair (psi_c, lambda_c) for c = 0..3 is a self-contained
-    // group (its gates and its share of the statistics need no other statevector).
-    if constexpr (EXS == 4) {
-      // Software-pipelined over the four pair groups with plane pairs {0, 1} and {2, 3} in turn.
-      // Each slot: read one pair group, add the previous group's gate statistics (covering the
-      // read latency), write the next group, then pull the group just read back through the
-      // round.  Writing after the statistics lets every wave's reads drain from the LDS queue
-      // before the writes of the workgroup's waves compete with them.  A round's statistics are
-      // flushed in the next round's first slot.
-      // The last round is pulled back first, gate by gate (H < R: it is never a leading-stage round).
-      CP<QRound> rl = rounds + (R - 1);
-      round_adj_all<NS, true>(sr, si, rl, gtab, F, slots, wave, lane);
-      if (R > 1) {
-        Offs wo = load_offs(xb[R - 1].woff);
-        // the current exchange's lane words as plain scalars (the loop body below is a lambda that
-        // updates them; an aggregate captured by reference would not stay in registers)
-        uint32_t xwb, xrb, xsg;
-        {
-          const XLane x0 = lane_words(lanes, 1, R, R - 1, TP, u, pb8);
-          xwb = x0.wb; xrb = x0.rb; xsg = x0.sgn;
+    // Per layer in reverse: psi-family (uncompute) and lambda-family through the inverse rotations, gate
+    // statistics, conjugate phase, inverse exchange.  The pair (psi_c, lambda_c) for c = 0..3 is a
+    // self-contained group (its gates and its share of the statistics need no other statevector).
+    // Layers below L0 (the opening layer, folded into the encoding) only take their statistics.
+    Stats<N> Q;
+    auto mom_of = [&](CP<QSweep> L) -> float* {
+      return L->phase >= 0 ? mslots + wave * a.n_mom + L->phase * phase_terms(N) : nullptr;
+    };
+    if constexpr (N < 10) {
+      auto layer = [&](int l, auto pull) {
+        constexpr bool PULL = decltype(pull)::value != 0;
+        CP<QSweep> L = sweeps + l;
+        Phase P{};
+        if (PULL) P = phase_of(l);
+        const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, true);
+        clear(Q);
+        layer_adj<N, 0, PULL>(sr, si, K, P, Q);
+        layer_adj<N, 1, PULL>(sr, si, K, P, Q);
+        layer_adj<N, 2, PULL>(sr, si, K, P, Q);
+        layer_adj<N, 3, PULL>(sr, si, K, P, Q);
+        flush_xy<N, 0, N>(L, Q, v, slots, F, wave, lane);
+        flush_z<N>(L, Q.w, v, slots, mom_of(L), F, wave, lane);
+        if (PULL && (L->flags & kSweepXchg) && (l > 0 || EG)) {   // (nothing follows the first layer else)
+          const uint4 w = lane_of(l);
+          const Addr A = xchg_addr(L->bwoff, L->broff, w.z ^ pb8, w.w ^ pb8);
+          exchange_wave<T, 0, 8>(sr, si, buf, A);
         }
-        xwrite<T, 0, 4, 0>(sr, si, buf, wo, xwb);
-        constexpr int NQ = 3 * (3 + NS);
-        float q[NQ];
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) q[i] = 0.f;
-        RoundCoef Rq = load_round<true, NS>(rl, gtab, F);   // gate ids of the round whose q is pending
-        // Iteration k moves the state from round k's input mapping to round k - 1's output mapping
-        // and pulls round k - 1 back (PULL), or, for a round of the leading stage, only takes its
-        // statistics.  Two loops instead of a branch inside one keep the register allocation of
-        // the pulling loop unchanged.
-        auto iter = [&](int k, auto pull) {
-          constexpr bool PULL = decltype(pull)::value;
-          CP<QRound> rp = rounds + (k - 1);
-          const RoundCoef Rp = load_round<true, NS>(rp, gtab, F);
-          const Offs ro = load_offs(xb[k].roff);
-          const bool sg = xb[k].nterms != 0;
-          __syncthreads();
-          xread<T, 0, 4, 0, SG>(sr, si, buf, ro, sg, xrb, xsg);
-          if (k < R - 1) {                             // finish the previous round's statistics
-            stat_accum<3>(sr, si, q);
-            round_stat_flush<NS>(Rq, slots, q, F, wave, lane);
-#pragma unroll
-            for (int i = 0; i < NQ; ++i) q[i] = 0.f;
-          }
-          xwrite<T, 1, 5, 2>(sr, si, buf, wo, xwb);
-          round_adj<0, NS, PULL>(sr, si, Rp, q);
-          pin_sv<0>(sr, si); pin_sv<4>(sr, si); pin_q<NQ>(q);
-          __syncthreads();
-          xread<T, 1, 5, 2, SG>(sr, si, buf, ro, sg, xrb, xsg);
-          stat_accum<0>(sr, si, q);
-          xwrite<T, 2, 6, 0>(sr, si, buf, wo, xwb);
-          round_adj<1, NS, PULL>(sr, si, Rp, q);
-          pin_sv<1>(sr, si); pin_sv<5>(sr, si); pin_q<NQ>(q);
-          __syncthreads();
-          xread<T, 2, 6, 0, SG>(sr, si, buf, ro, sg, xrb, xsg);
-          stat_accum<1>(sr, si, q);
-          xwrite<T, 3, 7, 2>(sr, si, buf, wo, xwb);
-          round_adj<2, NS, PULL>(sr, si, Rp, q);
-          pin_sv<2>(sr, si); pin_sv<6>(sr, si); pin_q<NQ>(q);
-          // the next exchange's write offsets (scalar, before the barrier as in the forward sweep)
-          if (k > 1) wo = load_offs(xb[k - 1].woff);
-          __syncthreads();
-          xread<T, 3, 7, 2, SG>(sr, si, buf, ro, sg, xrb, xsg);
-          // and its lane words: a vector load (its own wait counter), covered by the statistics
-          XLane xn{xwb, xrb, xsg};
-          if (k > 1) xn = lane_words(lanes, 1, R, k - 1, TP, u, pb8);
-          stat_accum<2>(sr, si, q);
-          if (k > 1) xwrite<T, 0, 4, 0>(sr, si, buf, wo, xn.wb);
-          round_adj<3, NS, PULL>(sr, si, Rp, q);
-          pin_sv<3>(sr, si); pin_sv<7>(sr, si); pin_q<NQ>(q);
-          xwb = xn.wb; xrb = xn.rb; xsg = xn.sgn;
-          Rq = Rp;
-        };
-        for (int k = R - 1; k > H; --k) iter(k, BoolC<true>{});
-        for (int k = H; k >= 1; --k) iter(k, BoolC<false>{});
-        stat_accum<3>(sr, si, q);                      // round 0's last group
-        round_stat_flush<NS>(Rq, slots, q, F, wave, lane);
+      };
+      for (int l = L1 - 1; l >= L0; --l) layer(l, IntC<1>{});
+      if (L0 > 0) layer(0, IntC<0>{});
+    } else if constexpr (EXS == 4) {
+      // Pair c goes through planes 2 (c & 1) and 2 (c & 1) + 1.  Between two barriers one pair is read,
+      // the next one written, and the pair just read rotated and its statistics taken.  A layer takes
+      // two such passes: the wave positions (behind the index-map exchange of the layer above, if it
+      // has one), then, behind the wave exchange, the rest.  The statistics of a pass are flushed at
+      // its end, and the first pair of an index-map exchange is written after that: with both live the
+      // kernel spilled.
+      auto wpair = [&](auto c) {   // wave exchange, writes
+        constexpr int C = decltype(c)::value, PL = 2 * (C & 1);
+        wwrite<N, T, C, PL>(sr, si, buf, wvb); wwrite<N, T, 4 + C, PL + 1>(sr, si, buf, wvb);
+      };
+      Addr A;
+      auto xpair = [&](auto c) {   // index-map exchange, writes
+        constexpr int C = decltype(c)::value, PL = 2 * (C & 1);
+        xwrite<T, C, PL>(sr, si, buf, A.w); xwrite<T, 4 + C, PL + 1>(sr, si, buf, A.w);
+      };
+      auto xstep = [&](auto c) {
+        constexpr int C = decltype(c)::value, PL = 2 * (C & 1);
         __syncthreads();
-      }
-    } else {
-      for (int k = R - 1; k >= H; --k) {
-        CP<QRound> rk = rounds + k;
-        round_adj_all<NS, true>(sr, si, rk, gtab, F, slots, wave, lane);
-        if (PH && rk->phase >= 0) {   // CRZ phase stage: moments at its output, then uncompute and pull back
-          CP<QPhaseStage> pst = to_const(pstages) + rk->phase;
-          phase_moments<N>(sr, si, rk, u, mslots + wave * a.n_mom + pst->mom_off, lane);
-          float pc[8], ps[8];
-          phase_factors<N>(rk, pcoef + pst->coef_off, u, pc, ps);
-          apply_phase<0, 8, true>(sr, si, pc, ps);
+        xread<T, C, PL>(sr, si, buf, A.r); xread<T, 4 + C, PL + 1>(sr, si, buf, A.r);
+        if constexpr (C < 3) xpair(IntC<C + 1>{});
+      };
+      bool moves = false;          // the layer above ended with its index-map exchange's first write
+      auto enter = [&](int l, auto pull) {
+        constexpr bool PULL = decltype(pull)::value != 0;
+        const Coef<N> K = load_coef<N, 9, N>(tcoef + l * kTC, v, true);
+        clear<N, 9, N>(Q);
+        auto step = [&](auto c) {
+          constexpr int C = decltype(c)::value;
+          if (moves) xstep(c);
+          if (PULL) wave_rot<N, C>(sr, si, K);
+          wave_stat<N, C>(sr, si, Q);
+          if constexpr (C == 3) wpair(IntC<0>{});
+        };
+        step(IntC<0>{}); step(IntC<1>{}); step(IntC<2>{}); step(IntC<3>{});
+        flush_xy<N, 9, N>(sweeps + l, Q, v, slots, F, wave, lane);
+      };
+      auto rest = [&](int l, auto pull) {
+        constexpr bool PULL = decltype(pull)::value != 0;
+        CP<QSweep> L = sweeps + l;
+        Phase P{};
+        if (PULL) P = phase_of(l);
+        const Coef<N> K = load_coef<N, 0, 9>(tcoef + l * kTC, v, true);
+        clear<N, 0, 9>(Q);
+        auto step = [&](auto c) {
+          constexpr int C = decltype(c)::value, PL = 2 * (C & 1);
+          __syncthreads();
+          wread<N, T, C, PL>(sr, si, buf, rvb); wread<N, T, 4 + C, PL + 1>(sr, si, buf, rvb);
+          if constexpr (C < 3) wpair(IntC<C + 1>{});
+          layer_adj<N, C, PULL>(sr, si, K, P, Q);
+        };
+        step(IntC<0>{}); step(IntC<1>{}); step(IntC<2>{}); step(IntC<3>{});
+        flush_xy<N, 0, 9>(L, Q, v, slots, F, wave, lane);
+        flush_z<N>(L, Q.w, v, slots, mom_of(L), F, wave, lane);
+        moves = PULL && (L->flags & kSweepXchg) && (l > 0 || EG);
+        if (moves) {
+          const uint4 w = lane_of(l);
+          A = xchg_addr(L->bwoff, L->broff, w.z ^ pb8, w.w ^ pb8);
+          xpair(IntC<0>{});
         }
-        if (k > 0) exchange<N, T, 8, 2>(sr, si, buf, xb + k, lane_words(lanes, 1, R, k, TP, u, pb8));
+      };
+      for (int l = L1 - 1; l >= L0; --l) {
+        enter(l, IntC<1>{});
+        rest(l, IntC<1>{});
       }
-      for (int k = H - 1; k >= 0; --k) {   // the leading stage: statistics only
-        CP<QRound> rk = rounds + k;
-        round_adj_all<NS, false>(sr, si, rk, gtab, F, slots, wave, lane);
-        if (k > 0) exchange<N, T, 8, 2>(sr, si, buf, xb + k, lane_words(lanes, 1, R, k, TP, u, pb8));
+      if (L0 > 0) {
+        enter(0, IntC<0>{});
+        rest(0, IntC<0>{});
+      } else if (EG && moves) {
+        xstep(IntC<0>{}); xstep(IntC<1>{}); xstep(IntC<2>{}); xstep(IntC<3>{});
       }
+      __syncthreads();
+    } else {
+      auto layer = [&](int l, auto pull) {
+        constexpr bool PULL = decltype(pull)::value != 0;
+        CP<QSweep> L = sweeps + l;
+        Phase P{};
+        if (PULL) P = phase_of(l);
+        const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, true);
+        const bool moves = PULL && (L->flags & kSweepXchg) && (l > 0 || EG);
+        const uint4 w = lane_of(l);
+        const Addr A = xchg_addr(L->bwoff, L->broff, w.z ^ pb8, w.w ^ pb8);
+        clear(Q);
+        auto pair = [&](auto c) {
+          constexpr int C = decltype(c)::value;
+          if (PULL) wave_rot<N, C>(sr, si, K);
+          wave_stat<N, C>(sr, si, Q);
+          wwrite<N, T, C, 0>(sr, si, buf, wvb); wwrite<N, T, 4 + C, 1>(sr, si, buf, wvb);
+          __syncthreads();
+          wread<N, T, C, 0>(sr, si, buf, rvb); wread<N, T, 4 + C, 1>(sr, si, buf, rvb);
+          __syncthreads();
+          layer_adj<N, C, PULL>(sr, si, K, P, Q);
+          if (moves) {
+            xwrite<T, C, 0>(sr, si, buf, A.w); xwrite<T, 4 + C, 1>(sr, si, buf, A.w);
+            __syncthreads();
+            xread<T, C, 0>(sr, si, buf, A.r); xread<T, 4 + C, 1>(sr, si, buf, A.r);
+            __syncthreads();
+          }
+        };
+        pair(IntC<0>{}); pair(IntC<1>{}); pair(IntC<2>{}); pair(IntC<3>{});
+        flush_xy<N, 0, N>(L, Q, v, slots, F, wave, lane);
+        flush_z<N>(L, Q.w, v, slots, mom_of(L), F, wave, lane);
+      };
+      for (int l = L1 - 1; l >= L0; --l) layer(l, IntC<1>{});
+      if (L0 > 0) layer(0, IntC<0>{});
     }
     if constexpr (EG) {
       // the point index again, from an opaque copy of the thread index: keeping pt and valid live
@@ -1357,19 +1720,19 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
       uint32_t t2 = threadIdx.x;
       asm volatile("" : "+v"(t2));
       const long long pt2 = PK ? 0 : (long long)tile * PPW + (long long)(t2 / TP);
-      encoding_grads<N, T>(sr, si, buf, red, plan, rounds, gtab, a, pt2, pt2 < a.P, u);
+      encoding_grads<N, T>(sr, si, buf, red, plan, gtab, a, pt2, pt2 < a.P, u);
     }
   }
 }
 
 // ---- the fused kernel: a persistent grid walks the tiles ------------------------------------
-template <int N, int T, int EXS, int MODE, bool SG, bool EG = false>
+template <int N, int T, int EXS, int MODE, bool EG = false>
 __global__ __launch_bounds__(T, 2) void k_fused(FusedArgs a) {
   constexpr int WAVES = T / 64;
   constexpr int PLANE = T * 8;
   // Exchange planes in static LDS (their address is a link-time constant, so every access is
   // one XOR of a byte offset); gate statistics and readout scratch in the dynamic part.
-  __shared__ float4 planes[EXS * PLANE / 2];
+  __shared__ float4 planes[sweep_planes(N, EXS, EG || mode_rounds(MODE)) * PLANE / 2];
   extern __shared__ float4 smem4[];
   float2* buf = reinterpret_cast<float2*>(planes);
   float* slots = reinterpret_cast<float*>(smem4);                   // [WAVES][F][kGS]
@@ -1396,7 +1759,7 @@ __global__ __launch_bounds__(T, 2) void k_fused(FusedArgs a) {
     t_step = gridDim.x / kXcd;
   }
   for (int tile = t_begin; tile < t_end; tile += t_step)
-    fused_tile<N, T, EXS, MODE, SG, EG>(a, tile, buf, slots, mslots, red, lacc);
+    fused_tile<N, T, EXS, MODE, EG>(a, tile, buf, slots, mslots, red, lacc);
   if (mode_fwd_only(MODE)) return;
   // ---------------- per-workgroup partials (fixed order) -----------------------------------
   __syncthreads();
@@ -1426,13 +1789,10 @@ __global__ __launch_bounds__(T, 2) void k_fused(FusedArgs a) {
 }
 
 
-template <int N, int EXS, int MODE, bool SG, bool EG = false>
-hipError_t launch_one(const FusedArgs& a, int grid, size_t lds, hipStream_t st) {
+template <int N, int EXS, int MODE, bool EG = false>
+hipError_t launch_one(const FusedArgs& a, int grid, size_t dyn, hipStream_t st) {
   constexpr int T = fused_wg_threads(N);
-  auto kern = k_fused<N, T, EXS, MODE, SG, EG>;
-  // lds counts the static exchange planes and the dynamic part; only the latter is passed.
-  const size_t planes = (size_t)EXS * T * 8 * sizeof(float2);
-  const size_t dyn = lds > planes ? lds - planes : 0;
+  auto kern = k_fused<N, T, EXS, MODE, EG>;
   // the attribute is set once per device (and raised when a larger size comes)
   static size_t attr_bytes[kMaxDevices] = {};
   int dev = 0;
@@ -1448,43 +1808,29 @@ hipError_t launch_one(const FusedArgs& a, int grid, size_t lds, hipStream_t st) 
   return hipGetLastError();
 }
 
-// Entry point of one per-N unit.  signs: some exchange of the circuit carries CZ signs (the
-// pipelined kernel has a variant without the sign code for circuits that have none).
+// Entry point of one per-N unit.  exs: exchange planes (2 or 4) from 10 qubits on; below, an exchange
+// stays inside a wave and one kernel serves both.
+template <int N, int MODE, bool EG = false>
+hipError_t launch_mode(const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st) {
+  if constexpr (N >= 10) {
+    if (exs == 4) return launch_one<N, 4, MODE, EG>(a, grid, dyn, st);
+  }
+  return launch_one<N, 2, MODE, EG>(a, grid, dyn, st);
+}
 template <int N>
-hipError_t launch_fused_n(int mode, const FusedArgs& a, int grid, int exs, bool signs, size_t lds, hipStream_t st) {
-  if ((mode == kModeMaxwell || mode == kModeVjp) && (a.d_angles || a.d_jac)) {   // per-point input gradients
-    if (mode == kModeMaxwell)
-      return exs == 2 ? launch_one<N, 2, kModeMaxwell, true, true>(a, grid, lds, st)
-                      : launch_one<N, 4, kModeMaxwell, true, true>(a, grid, lds, st);
-    return exs == 2 ? launch_one<N, 2, kModeVjp, true, true>(a, grid, lds, st)
-                    : launch_one<N, 4, kModeVjp, true, true>(a, grid, lds, st);
+hipError_t launch_fused_n(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st) {
+  const bool eg = a.d_angles || a.d_jac;   // per-point input gradients
+  switch (mode) {
+    case kModeFwd: return launch_mode<N, kModeFwd>(a, grid, exs, dyn, st);
+    case kModeFwdPk: return launch_mode<N, kModeFwdPk>(a, grid, exs, dyn, st);
+    case kModeFieldsPk: return launch_mode<N, kModeFieldsPk>(a, grid, exs, dyn, st);
+    case kModeTotal: return launch_mode<N, kModeTotal>(a, grid, exs, dyn, st);
+    case kModeVjpPk: return launch_mode<N, kModeVjpPk>(a, grid, exs, dyn, st);
+    case kModeMaxwell:
+      return eg ? launch_mode<N, kModeMaxwell, true>(a, grid, exs, dyn, st) : launch_mode<N, kModeMaxwell>(a, grid, exs, dyn, st);
+    default:
+      return eg ? launch_mode<N, kModeVjp, true>(a, grid, exs, dyn, st) : launch_mode<N, kModeVjp>(a, grid, exs, dyn, st);
   }
-  if (mode == kModeFwd) {
-    if (exs == 2) return launch_one<N, 2, kModeFwd, true>(a, grid, lds, st);
-    return signs ? launch_one<N, 4, kModeFwd, true>(a, grid, lds, st) : launch_one<N, 4, kModeFwd, false>(a, grid, lds, st);
-  }
-  if (mode == kModeTotal) {
-    if (exs == 2) return launch_one<N, 2, kModeTotal, true>(a, grid, lds, st);
-    return signs ? launch_one<N, 4, kModeTotal, true>(a, grid, lds, st)
-                 : launch_one<N, 4, kModeTotal, false>(a, grid, lds, st);
-  }
-  if (mode == kModeMaxwell) {
-    if (exs == 2) return launch_one<N, 2, kModeMaxwell, true>(a, grid, lds, st);
-    return signs ? launch_one<N, 4, kModeMaxwell, true>(a, grid, lds, st)
-                 : launch_one<N, 4, kModeMaxwell, false>(a, grid, lds, st);
-  }
-  if (mode == kModeFwdPk) {
-    if (exs == 2) return launch_one<N, 2, kModeFwdPk, true>(a, grid, lds, st);
-    return signs ? launch_one<N, 4, kModeFwdPk, true>(a, grid, lds, st)
-                 : launch_one<N, 4, kModeFwdPk, false>(a, grid, lds, st);
-  }
-  if (mode == kModeVjpPk) {
-    if (exs == 2) return launch_one<N, 2, kModeVjpPk, true>(a, grid, lds, st);
-    return signs ? launch_one<N, 4, kModeVjpPk, true>(a, grid, lds, st)
-                 : launch_one<N, 4, kModeVjpPk, false>(a, grid, lds, st);
-  }
-  if (exs == 2) return launch_one<N, 2, kModeVjp, true>(a, grid, lds, st);
-  return signs ? launch_one<N, 4, kModeVjp, true>(a, grid, lds, st) : launch_one<N, 4, kModeVjp, false>(a, grid, lds, st);
 }
 
 }  // namespace qp

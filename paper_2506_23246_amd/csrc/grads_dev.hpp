@@ -4,7 +4,8 @@
 // With lambda and psi both taken before the gate,
 //   d L / d theta_c = 2 Re <lambda_after| dU |psi> = Im <lambda|G_c|psi> = sum_k n_k S_k,
 // where G_c = n_x X + n_y Y + n_z Z and S_k = Im <lambda|sigma_k|psi> is what the adjoint sweep
-// accumulates per gate.  A gate of the leading stage has its statistic taken after the gate
+// accumulates per gate, there behind the RZ(c) of the gate's ZYZ split (QSweep), so G_c's axis is
+// turned about z by c.  A gate of the opening layer has its statistic taken after the gate
 // (lambda_after, psi_after = U psi); the same derivative is then Im <lambda_after|G'_c|psi_after>
 // with G'_c = U G_c U^H = V P_c V^H, V = R_{n-1} ... R_{c+1} the components after c (R_c
 // commutes with P_c).
@@ -13,13 +14,14 @@
 
 #include "../../include/qpinn.h"
 #include "qp_internal.hpp"
+#include "fused.hpp"
 #include "rot_dev.hpp"
 
 namespace qp {
 
 // Axis (n_x, n_y, n_z) of G_c for component ci of fused gate fu.
 __host__ __device__ inline void generator_axis(const QFused& fu, const float* __restrict__ params, int ci, double* nvec) {
-  if (fu.stat_out) {
+  if (fu.head) {
     double v[8];
     set_identity(v);
     for (int c = ci + 1; c < fu.ncomp; ++c) {
@@ -63,7 +65,7 @@ __host__ __device__ inline void generator_axis(const QFused& fu, const float* __
 }
 
 __device__ inline double param_grad_one(const QPlanDev* __restrict__ plan, const float* __restrict__ params,
-                                        const double* __restrict__ s64, int k) {
+                                        const double* __restrict__ s64, const SweepTabs& T, int k) {
   const char* pb = reinterpret_cast<const char*>(plan);
   const QFused* fused = reinterpret_cast<const QFused*>(pb + plan->off_fused);
   const int* ptr = reinterpret_cast<const int*>(pb + plan->off_csr_ptr);
@@ -73,25 +75,28 @@ __device__ inline double param_grad_one(const QPlanDev* __restrict__ plan, const
     const int fi = idx[e] >> 2, ci = idx[e] & 3;
     double nv[3];
     generator_axis(fused[fi], params, ci, nv);
+    // the cosines left out when the statistics were taken, and the sign of Y and Z behind an X mask
     const double* S = s64 + fi * kGS;
-    gsum += nv[0] * S[0] + nv[1] * S[1] + nv[2] * S[2];
+    const double* g = T.gpar + (long long)fi * kGP;
+    const double nx = g[0] * nv[0] - g[1] * nv[1], ny = g[1] * nv[0] + g[0] * nv[1];
+    gsum += nx * S[0] * g[2] + (g[3] < 0.0 ? -ny : ny) * S[1] * g[2] + nv[2] * S[2] * g[3];
   }
-  // CRZ(c, t) occurrences: dL/dtheta = M_c - 2 M_ct from the phase-stage moments, which follow the
+  // CRZ(c, t) occurrences: dL/dtheta = (W_t - W_ct) / 2 from the layer's parity sums, which follow the
   // fused-gate statistics (see QPhaseStage)
   if (plan->n_phase > 0) {
     const int* pptr = reinterpret_cast<const int*>(pb + plan->off_pcsr_ptr);
     const int* pidx = reinterpret_cast<const int*>(pb + plan->off_pcsr_idx);
     const QPhaseStage* stages = reinterpret_cast<const QPhaseStage*>(pb + plan->off_phase);
     const QPhaseGate* pg = reinterpret_cast<const QPhaseGate*>(pb + plan->off_phase_gates);
+    const QSweep* sweeps = reinterpret_cast<const QSweep*>(pb + plan->off_sweeps);
     const int n = plan->n;
     for (int e = pptr[k]; e < pptr[k + 1]; ++e) {
-      const int gi = pidx[e];
-      int s = 0;
-      while (s + 1 < plan->n_phase && stages[s + 1].gate0 <= gi) ++s;
-      const double* M = s64 + plan->n_fused * kGS + stages[s].mom_off;
-      const int c = pg[gi].c, t = pg[gi].t;
-      const int a = c < t ? c : t, b = c < t ? t : c;
-      gsum += M[c] - 2.0 * M[n + phase_pair_index(n, a, b)];
+      const QPhaseGate G = pg[pidx[e]];
+      const double* W = s64 + plan->n_fused * kGS + stages[sweeps[G.layer].phase].mom_off;
+      const uint32_t x = T.xmask[G.layer];
+      const double zc = ((x >> (n - 1 - G.c)) & 1u) ? -1.0 : 1.0, zt = ((x >> (n - 1 - G.t)) & 1u) ? -1.0 : 1.0;
+      const int a = G.c < G.t ? G.c : G.t, b = G.c < G.t ? G.t : G.c;
+      gsum += 0.5 * T.lscale[G.layer] * zt * (W[G.t] - zc * W[n + phase_pair_index(n, a, b)]);
     }
   }
   return gsum;

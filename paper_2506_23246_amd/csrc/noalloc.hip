@@ -17,7 +17,11 @@ namespace {
 
 static_assert(QP_NOALLOC_SCRATCH_BYTES % 256 == 0, "scratch size must keep 256-byte alignment");
 
-__device__ __align__(256) unsigned char scratch[QP_NOALLOC_SCRATCH_BYTES];
+// The tables of the sweep layers lie behind the rest of a call's scratch and are counted apart:
+// 2^n entries of 8 bytes per layer, 24 MiB for the most layers whose statistics fit the LDS and the
+// fixed scratch (744 at 12 qubits).
+constexpr size_t kTableBytes = 32u << 20;
+__device__ __align__(256) unsigned char scratch[QP_NOALLOC_SCRATCH_BYTES + kTableBytes];
 
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[qp::kMaxDevices] = {};
@@ -52,8 +56,8 @@ extern "C" qp_status qp_maxwell_fused_noalloc(qp_ctx* ctx, const qp_circuit* c, 
   if (P < 0) return qp::fail(ctx, QP_EINVAL, "%s: P < 0", who);
   if (ctx->device < 0 || ctx->device >= qp::kMaxDevices)
     return qp::fail(ctx, QP_EUNSUPPORTED, "%s: device index %d out of range", who, ctx->device);
-  const size_t need = qp::ws_required(c, P, 0);
-  if (need > QP_NOALLOC_SCRATCH_BYTES)
+  const size_t tables = qp::sweep_tab_bytes(c), need = qp::ws_required(c, P, 0) - tables;
+  if (need > QP_NOALLOC_SCRATCH_BYTES || tables > kTableBytes)
     return qp::fail(ctx, QP_EWORKSPACE, "%s: this call needs %zu scratch bytes, above the fixed %zu; use qp_maxwell_fused "
                     "with a workspace or split the points", who, need, (size_t)QP_NOALLOC_SCRATCH_BYTES);
   hipError_t e = hipSetDevice(ctx->device);
@@ -61,5 +65,5 @@ extern "C" qp_status qp_maxwell_fused_noalloc(qp_ctx* ctx, const qp_circuit* c, 
   if (e == hipSuccess) e = scratch_address(ctx->device, &ws);
   if (e != hipSuccess) return qp::hipcheck(ctx, e, "qp_maxwell_fused_noalloc: scratch address");
   return qp::maxwell_entry(ctx, c, params, points, angles, jac, P, loss_desc, out, tan, loss, d_params, d_angles,
-                           d_jac, ws, QP_NOALLOC_SCRATCH_BYTES, flags, who);
+                           d_jac, ws, QP_NOALLOC_SCRATCH_BYTES + kTableBytes, flags, who);
 }

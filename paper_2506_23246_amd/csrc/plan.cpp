@@ -214,12 +214,13 @@ void bank_score(int n, int T, const uint32_t* M, const std::vector<uint32_t>& wj
 }
 
 void choose_index_map(int n, int T, const int32_t* wmap, const int32_t* rmap, const uint32_t* Acols, int salt,
-                      uint32_t* M) {
+                      uint32_t* M, bool sweep = false) {
   const int TP = 1 << (n - 3);
   std::vector<uint32_t> wj(TP), rj(TP);
   for (int u = 0; u < TP; ++u) {
-    wj[u] = deposit_host((uint32_t)u, wmap, n);
-    rj[u] = apply_cols(Acols, n, deposit_host((uint32_t)u, rmap, n));
+    const uint32_t v = sweep ? sweep_thread((uint32_t)u, n) : (uint32_t)u;
+    wj[u] = deposit_host(v, wmap, n);
+    rj[u] = apply_cols(Acols, n, deposit_host(v, rmap, n));
   }
   const int target = std::min(16, T);
   uint32_t best[16];
@@ -364,7 +365,7 @@ static void build_dense(HostPlan* hp) {
   }
 }
 
-std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status) {
+std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool rounds_image) {
   *status = QP_EINVAL;
   if (!d) return "null circuit descriptor";
   const int n = d->n_qubits;
@@ -489,6 +490,11 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status) {
   if (!hp->fused_ok) {   // no register rounds; the image still carries the dense plan
     hp->rounds.clear();
     hp->lanes.clear();
+    hp->sweeps.clear();
+    hp->slanes.clear();
+    hp->terms.clear();
+    hp->tlanes.clear();
+    hp->sweep_first = 0;
     for (int i = 0; i < hp->m; ++i) hp->zmask[i] = 1u << (n - 1 - hp->out_qubits[i]);
     goto image;
   }
@@ -682,32 +688,162 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status) {
   const int TP = 1 << (n - 3);
   hp->xf.assign(R, QXchg{});
   hp->xb.assign(R, QXchg{});
-  hp->lanes.assign((size_t)2 * R * TP, QLane{});
-  hp->n_exchanges = 0;
-  hp->has_signs = false;
+  hp->lanes.assign((size_t)(rounds_image ? 2 : 1) * R * TP, QLane{});
+  hp->n_exchanges = R > 1 ? R - 1 : 0;
   for (int k = 1; k < R; ++k) {
     const Affine& a = round_ent[k];
     fill_xchg(&hp->xf[k], n, a.acol, a, false, hp->rounds[k].tpos);
     uint32_t inv[16];
     if (!gf2_inverse(a.acol, n, inv)) { *status = QP_EINVAL; return "singular entangler map"; }
     fill_xchg(&hp->xb[k], n, inv, a, true, hp->rounds[k - 1].tpost);
-    hp->n_exchanges++;
-    if (hp->xf[k].nterms != 0 || hp->xb[k].nterms != 0) hp->has_signs = true;
     // forward: round k-1's output mapping -> round k's input mapping; reverse: the other way
     const int T = fused_wg_threads(n);
     uint32_t Mf[16], Mb[16];
     choose_index_map(n, T, hp->rounds[k - 1].tpost, hp->rounds[k].tpos, a.acol, 2 * k, Mf);
-    choose_index_map(n, T, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, inv, 2 * k + 1, Mb);
     set_lds_layout(&hp->xf[k], n, Mf, hp->rounds[k - 1].tpost, hp->rounds[k].tpos, a.acol);
-    set_lds_layout(&hp->xb[k], n, Mb, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, inv);
-    for (int u = 0; u < TP; ++u) {
+    for (int u = 0; u < TP; ++u)
       hp->lanes[((size_t)0 * R + k) * TP + u] =
           lane_words(n, a.acol, a, false, hp->rounds[k - 1].tpost, hp->rounds[k].tpos, Mf, (uint32_t)u);
+    if (!rounds_image) continue;   // the kernels' adjoint runs the sweep layers
+    choose_index_map(n, T, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, inv, 2 * k + 1, Mb);
+    set_lds_layout(&hp->xb[k], n, Mb, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, inv);
+    for (int u = 0; u < TP; ++u)
       hp->lanes[((size_t)1 * R + k) * TP + u] =
           lane_words(n, inv, a, true, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, Mb, (uint32_t)u);
-    }
   }
 
+  // ---------------- sweep layers ----------------
+  {
+  const int TP = 1 << (n - 3);
+  const int nsl = sweep_slots(n), nw = sweep_wave(n);
+  const int T = n <= 9 ? 64 : fused_wg_threads(n);   // up to 9 qubits an exchange stays inside a wave
+  hp->sweeps.clear();
+  hp->slanes.clear();
+  hp->terms.clear();
+  hp->sweep_first = 0;
+  for (int q = 0; q < 16; ++q) hp->hgate[q] = -1;
+  int32_t cur[16];                 // mapping of the state as it stands
+  for (int k = 0; k < 16; ++k) cur[k] = k < n ? k : 0;
+  for (int k = 0; k < 16; ++k) hp->etpos[k] = hp->gtpos[k] = cur[k];
+  const Stage* ent = nullptr;      // entanglers since the last rotation stage
+  int nph = 0;                     // CRZ runs so far (numbered as hp->phases)
+  for (size_t si = 0; si < stages.size(); ++si) {
+    const Stage& s = stages[si];
+    if (!s.rot) { ent = &s; continue; }
+    QSweep L{};
+    const bool head = si == 0;
+    Affine a;
+    a.init(n);
+    if (ent) a = ent->aff;
+    uint32_t inv[16];
+    if (!gf2_inverse(a.acol, n, inv)) { *status = QP_EINVAL; return "singular entangler map"; }
+    bool moves = false;
+    for (int k = 0; k < n; ++k) moves = moves || a.acol[k] != (1u << k);
+    for (int k = 0; k < 16; ++k) {
+      L.arow[k] = 0;
+      for (int b = 0; b < n; ++b) L.arow[k] |= ((a.acol[b] >> k) & 1u) << b;
+    }
+    L.term0 = (int)hp->terms.size() / 2;
+    L.nterms = (int)a.terms.size();
+    for (const auto& t : a.terms) { hp->terms.push_back(t.first); hp->terms.push_back(t.second); }
+    L.phase = -1;
+    if (ent && !ent->phase.empty()) {
+      L.phase = nph++;
+      const QPhaseStage& ps = hp->phases[L.phase];
+      for (int g = 0; g < ps.ngates; ++g) hp->phase_gates[ps.gate0 + g].layer = (int)hp->sweeps.size();
+    }
+    // input mapping: after an exchange a free choice (the qubits with gates first), else the state's
+    // mapping as it stands
+    int32_t tin[16];
+    for (int k = 0; k < 16; ++k) tin[k] = cur[k];
+    if (moves || head) {
+      int c = 0;
+      for (int pass = 0; pass < 2; ++pass)
+        for (int p = 0; p < n; ++p)
+          if ((s.fused_of_qubit.count(n - 1 - p) != 0) == (pass == 0)) tin[c++] = p;
+    }
+    for (int k = 0; k < kPos; ++k) L.gate[k] = -1;
+    for (int k = 0; k < n; ++k) {
+      auto it = s.fused_of_qubit.find(n - 1 - tin[k]);
+      if (it == s.fused_of_qubit.end()) continue;
+      L.gate[k] = it->second;
+      hp->fused[it->second].layer = (int)hp->sweeps.size();
+      hp->fused[it->second].head = head ? 1 : 0;
+      if (head) hp->hgate[it->first] = it->second;
+    }
+    int32_t tout[16];
+    for (int k = 0; k < 16; ++k) tout[k] = tin[k];
+    for (int i = 0; i < nsl; ++i) std::swap(tout[i], tout[7 + i]);
+    for (int i = 0; i < nw; ++i) std::swap(tout[i], tout[9 + i]);
+    L.flags = moves && !head ? kSweepXchg : 0;
+    const size_t l0 = hp->slanes.size();
+    hp->slanes.resize(l0 + TP, QSweepLane{});
+    if (L.flags & kSweepXchg) {
+      uint32_t Mf[16], Mb[16];
+      const int salt = 2 * (int)hp->sweeps.size();
+      choose_index_map(n, T, cur, tin, a.acol, salt, Mf, true);
+      choose_index_map(n, T, tin, cur, inv, salt + 1, Mb, true);
+      for (int r = 0; r < 8; ++r) {
+        L.woff[r] = 8u * lds_swizzle(apply_cols(Mf, n, jr_of(cur, r)));
+        L.roff[r] = 8u * lds_swizzle(apply_cols(Mf, n, apply_cols(a.acol, n, jr_of(tin, r))));
+        L.bwoff[r] = 8u * lds_swizzle(apply_cols(Mb, n, jr_of(tin, r)));
+        L.broff[r] = 8u * lds_swizzle(apply_cols(Mb, n, apply_cols(inv, n, jr_of(cur, r))));
+      }
+      for (int u = 0; u < TP; ++u) {
+        const uint32_t v = sweep_thread((uint32_t)u, n);
+        const uint32_t jc = deposit_host(v, cur, n), jt = deposit_host(v, tin, n);
+        QSweepLane& W = hp->slanes[l0 + u];
+        W.fwb = 8u * lds_swizzle(apply_cols(Mf, n, jc));
+        W.frb = 8u * lds_swizzle(apply_cols(Mf, n, apply_cols(a.acol, n, jt)));
+        W.bwb = 8u * lds_swizzle(apply_cols(Mb, n, jt));
+        W.brb = 8u * lds_swizzle(apply_cols(Mb, n, apply_cols(inv, n, jc)));
+      }
+    }
+    for (int k = 0; k < 16; ++k) { L.tin[k] = tin[k]; L.tout[k] = tout[k]; cur[k] = tout[k]; }
+    if (head) {
+      hp->sweep_first = 1;
+      for (int k = 0; k < 16; ++k) { hp->etpos[k] = tout[k]; hp->gtpos[k] = tin[k]; }
+    }
+    hp->sweeps.push_back(L);
+    ent = nullptr;
+  }
+  for (int k = 0; k < 16; ++k) hp->ftpos[k] = cur[k];
+  // the turn from the rounds' last mapping (thread bits as they are) to ftpos
+  const int32_t* rpos = hp->rounds.back().tpost;
+  uint32_t best[16] = {0};
+  int bmin = -1, bsum = -1;
+  for (int it = 0; it < 64 && bmin < 16; ++it) {   // an LDS layout as for the other exchanges
+    uint32_t M[16];
+    MapSearch rng;
+    rng.state ^= (uint32_t)it * 0x9E3779B1u;
+    int perm[16];
+    for (int k = 0; k < n; ++k) perm[k] = k;
+    if (it > 0)
+      for (int k = n - 1; k > 0; --k) std::swap(perm[k], perm[rng.next() % (uint32_t)(k + 1)]);
+    for (int k = 0; k < 16; ++k) M[k] = k < n ? 1u << perm[k] : 0u;
+    std::vector<uint32_t> wj(TP), rj(TP);
+    for (int u = 0; u < TP; ++u) {
+      wj[u] = deposit_host((uint32_t)u, rpos, n);
+      rj[u] = deposit_host(sweep_thread((uint32_t)u, n), hp->ftpos, n);
+    }
+    int mv, sm;
+    bank_score(n, T, M, wj, rj, &mv, &sm);
+    if (mv > bmin || (mv == bmin && sm > bsum)) {
+      bmin = mv;
+      bsum = sm;
+      std::copy(M, M + 16, best);
+    }
+  }
+  hp->tlanes.assign((size_t)2 * TP, 0u);
+  for (int r = 0; r < 8; ++r) {
+    hp->turn.woff[r] = 8u * lds_swizzle(apply_cols(best, n, jr_of(rpos, r)));
+    hp->turn.roff[r] = 8u * lds_swizzle(apply_cols(best, n, jr_of(hp->ftpos, r)));
+  }
+  for (int u = 0; u < TP; ++u) {
+    hp->tlanes[2 * u] = 8u * lds_swizzle(apply_cols(best, n, deposit_host((uint32_t)u, rpos, n)));
+    hp->tlanes[2 * u + 1] = 8u * lds_swizzle(apply_cols(best, n, deposit_host(sweep_thread((uint32_t)u, n), hp->ftpos, n)));
+  }
+  }
   }
 image:
   // device image
@@ -752,6 +888,19 @@ image:
   h.off_phase_gates = (int)off; off = align16(off + sizeof(QPhaseGate) * hp->phase_gates.size());
   h.off_pcsr_ptr = (int)off; off = align16(off + sizeof(int32_t) * std::max<size_t>(1, hp->pcsr_ptr.size()));
   h.off_pcsr_idx = (int)off; off = align16(off + sizeof(int32_t) * std::max<size_t>(1, hp->pcsr_idx.size()));
+  h.n_sweeps = hp->fused_ok ? (int)hp->sweeps.size() : 0;
+  h.sweep_first = hp->sweep_first;
+  h.off_sweeps = (int)off; off = align16(off + sizeof(QSweep) * hp->sweeps.size());
+  h.off_slanes = (int)off; off = align16(off + sizeof(QSweepLane) * hp->slanes.size());
+  h.off_terms = (int)off; off = align16(off + sizeof(uint32_t) * std::max<size_t>(2, hp->terms.size()));
+  h.off_turn = (int)off; off = align16(off + sizeof(QTurn));
+  h.off_tlanes = (int)off; off = align16(off + sizeof(uint32_t) * hp->tlanes.size());
+  for (int k = 0; k < 16; ++k) {
+    h.hgate[k] = hp->fused_ok ? hp->hgate[k] : -1;
+    h.etpos[k] = hp->fused_ok ? hp->etpos[k] : 0;
+    h.ftpos[k] = hp->fused_ok ? hp->ftpos[k] : 0;
+    h.gtpos[k] = hp->fused_ok ? hp->gtpos[k] : 0;
+  }
   h.bytes = (int)off;
   hp->blob.assign(off, 0);
   std::memcpy(hp->blob.data(), &h, sizeof(h));
@@ -775,6 +924,11 @@ image:
   if (!hp->phase_gates.empty())
     std::memcpy(hp->blob.data() + h.off_phase_gates, hp->phase_gates.data(), sizeof(QPhaseGate) * hp->phase_gates.size());
   if (!hp->pcsr_ptr.empty()) std::memcpy(hp->blob.data() + h.off_pcsr_ptr, hp->pcsr_ptr.data(), sizeof(int32_t) * hp->pcsr_ptr.size());
+  if (!hp->sweeps.empty()) std::memcpy(hp->blob.data() + h.off_sweeps, hp->sweeps.data(), sizeof(QSweep) * hp->sweeps.size());
+  if (!hp->slanes.empty()) std::memcpy(hp->blob.data() + h.off_slanes, hp->slanes.data(), sizeof(QSweepLane) * hp->slanes.size());
+  std::memcpy(hp->blob.data() + h.off_turn, &hp->turn, sizeof(QTurn));
+  if (!hp->tlanes.empty()) std::memcpy(hp->blob.data() + h.off_tlanes, hp->tlanes.data(), sizeof(uint32_t) * hp->tlanes.size());
+  if (!hp->terms.empty()) std::memcpy(hp->blob.data() + h.off_terms, hp->terms.data(), sizeof(uint32_t) * hp->terms.size());
   if (!hp->pcsr_idx.empty()) std::memcpy(hp->blob.data() + h.off_pcsr_idx, hp->pcsr_idx.data(), sizeof(int32_t) * hp->pcsr_idx.size());
   return "";
 }

@@ -28,12 +28,19 @@ struct HostPlan {
   uint32_t zmask[kMaxOut] = {0};
   std::vector<int32_t> csr_ptr, csr_idx;
   int n_exchanges = 0;                 // exchanges that move data
-  bool has_signs = false;              // some exchange carries CZ signs
   std::vector<QPhaseStage> phases;     // CRZ phase stages, by exchange
   std::vector<QPhaseGate> phase_gates;
   std::vector<int32_t> pcsr_ptr, pcsr_idx;
   int n_head = 0;                      // leading rounds folded into the encoding
   int32_t head_gate[16];               // per qubit: its leading-stage fused gate, or -1
+  // sweep layers (what the kernels run)
+  std::vector<QSweep> sweeps;
+  std::vector<QSweepLane> slanes;      // [layer][2^(n-3)]
+  std::vector<uint32_t> terms;         // CZ terms (pairs of masks)
+  QTurn turn = {};
+  std::vector<uint32_t> tlanes;
+  int sweep_first = 0;
+  int32_t hgate[16], etpos[16], ftpos[16], gtpos[16];
   // dense-block plan (MFMA path)
   bool dense_ok = false;
   std::vector<QDenseGroup> dgroups;
@@ -43,7 +50,9 @@ struct HostPlan {
 };
 
 // Returns "" on success, else a message; *status receives the qp_status to return.
-std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status);
+// rounds_image: also lay out the reverse exchanges of the round schedule (qp_plan_image hands them out;
+// the kernels run only its forward, the adjoint by sweep layers).
+std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool rounds_image = false);
 
 // GF(2) helpers (exposed for the self-check in the test suite through the C API only).
 uint32_t gf2_apply(const uint32_t* cols, int n, uint32_t x);

@@ -101,27 +101,83 @@ struct alignas(16) QFused {
   int32_t kind[3];
   int32_t param[3];
   int32_t stat_out;
+  int32_t layer;   // sweep layer that applies the gate (index into the QSweep array)
+  int32_t head;    // 1: the gate belongs to the opening layer folded into the encoding
+  int32_t pad;
 };
 static_assert(sizeof(QFused) == 48, "QFused layout");
+
+// ---- sweep layers: what the fused kernels execute ------------------------------------------------
+// Every fused gate is split as U = e^{i g} RZ(a) RY(b) RZ(c).  The RZ factors of a rotation stage and
+// the CZ and CRZ gates between two stages are all diagonal, so everything diagonal between one
+// stage's RYs and the next one's is a single phase per basis index, tabulated once per call
+// (k_sweep_tables); what is left of a stage is one real rotation per qubit, applied as
+// x0' = x0 - t x1, x1' = x1 + t x0 with t = tan(b/2) and its cosine folded into the table.  Where
+// |tan| would exceed one, RY(b) = RY(pi) RY(b - pi) and RY(pi) is an X and a sign: the X is not
+// applied but carried along as a mask x (statevector index i stands for basis index i ^ x; the mask is
+// zero at the readout), the sign goes into the next table.
+//
+// A layer is one rotation stage with the entanglers before it: an index-map exchange (xchg), the
+// table's phase, then the RYs.  Physical bit k of an index: 0..2 register bits, 3..6 lane bits whose
+// partner lane a DPP permutation reaches, 7..8 the lane bits 4 and 5 (swapped with register bits 0
+// and 1 by permlane swaps), 9..11 the wave bits (swapped with register bits through LDS).  A gate at
+// a position 7.. runs on the register bit it was swapped into, so the layer starts in mapping tin
+// and ends in mapping tout.  Lane bits are counted in the basis 1, 2, 7, 8, 16, 32 of lane XORs (a
+// half-row mirror flips lane bits 0..2 together): see sweep_thread.
+constexpr int kPos = 12;
+struct alignas(16) QSweep {
+  int32_t gate[kPos];       // fused gate at each position (-1: none)
+  int32_t flags;            // kSweepXchg: an index-map exchange comes first
+  int32_t phase;            // CRZ phase stage in front of the layer, or -1
+  int32_t term0, nterms;    // CZ terms in front of the layer: masks [term0, term0 + nterms) of the term list
+  int32_t tin[16], tout[16];
+  uint32_t woff[8], roff[8];     // forward exchange: LDS byte offsets of the registers, writer and reader
+  uint32_t bwoff[8], broff[8];   // reverse exchange
+  uint32_t arow[16];        // index map: new index j takes the amplitude of old index A j (rows of A)
+};
+static_assert(sizeof(QSweep) == 384, "QSweep layout");
+constexpr int kSweepXchg = 1;
+// Per thread of a point and layer: LDS byte bases of the forward and reverse exchange.
+struct alignas(16) QSweepLane {
+  uint32_t fwb, frb, bwb, brb;
+};
+// The exchange from the rounds' mapping at the readout to the sweeps' (ftpos): register offsets, and per
+// thread of a point the writer's and the reader's base.
+struct alignas(16) QTurn {
+  uint32_t woff[8], roff[8];
+};
+// Lane bits reached by DPP, permlane swap slots and wave bits at n qubits.
+QP_HD inline constexpr int sweep_dpp(int n) { return n < 7 ? n - 3 : 4; }
+QP_HD inline constexpr int sweep_slots(int n) { return n < 8 ? 0 : (n < 9 ? 1 : 2); }
+QP_HD inline constexpr int sweep_wave(int n) { return n < 10 ? 0 : n - 9; }
+// Index bits of thread u of a point in the lane basis above (1 and 2 as they are, 7 for bit 2).
+QP_HD inline constexpr uint32_t sweep_thread(uint32_t u, int n) { return n >= 6 ? u ^ (((u >> 2) & 1u) * 3u) : u; }
+// Lane XOR that flips thread bit k.
+QP_HD inline constexpr uint32_t sweep_xor(int k) { return k == 2 ? 7u : 1u << k; }
+// Exchange planes a fused kernel allocates: up to 9 qubits an exchange stays inside a wave and one
+// plane serves all statevectors (two: the rounds' exchange and the input gradients); else exs.
+QP_HD inline constexpr int sweep_planes(int n, int exs, bool two) { return n >= 10 ? exs : (two ? 2 : 1); }
+constexpr int kTC = 16;            // floats per layer of the coefficient table (kPos used)
+constexpr int kGP = 4;             // doubles per gate: cos c, sin c, scale of S_x and S_y, scale of S_z (sign: X mask)
+constexpr int kMaxSweeps = 4096;   // layers the table kernel can scan
 
 // Phase stage: a run of CRZ gates (with any CZ of the same stage), all diagonal, applied as one
 // phase e^{i phi(j)} per basis index after the exchange that precedes a round.  With
 // CRZ(c, t)(theta) = |0><0|_c (x) I + |1><1|_c (x) RZ_t(theta),
 //   phi(j) = sum_(c,t) theta_ct (-1/2) b_c(j) (1 - 2 b_t(j)) = sum_q alpha_q b_q + sum_(q<q') beta_qq' b_q b_q',
 //   alpha_q = -(1/2) sum_t theta_qt,  beta_qq' = theta_qq' + theta_q'q.
-// The coefficients are kept as unsigned 32-bit fractions of a turn (2 pi = 2^32), so phases add
-// exactly modulo 2 pi.  Per stage: n alpha's then the n(n-1)/2 beta's (pairs q < q' in row order),
-// at coef_off (in 32-bit words) of the phase table that follows the gate table.  The adjoint
-// accumulates the moments M_q = sum_j w_j b_q and M_qq' = sum_j w_j b_q b_q' of
-// w_j = Im(conj(lambda_j) psi_j) + sum_c Im(conj(mu_c,j) dpsi_c,j) at the stage output (same
-// order, at mom_off among the phase moments), and dL/dtheta_ct = M_c - 2 M_ct.
+// The kernels take phi from the layer's table (QSweep).  The adjoint accumulates the parity sums
+// W_q = sum_j w_j z_q and W_qq' = sum_j w_j z_q z_q', z_q = (-1)^{b_q}, of
+// w_j = Im(conj(lambda_j) psi_j) + sum_c Im(conj(mu_c,j) dpsi_c,j) (n of the first, then the n(n-1)/2
+// of the second, pairs q < q' in row order, at mom_off among the moments), and
+// dL/dtheta_ct = sum_j w_j b_c z_t = (W_t - W_ct) / 2.
 struct alignas(16) QPhaseStage {
   int32_t gate0, ngates;  // range in the QPhaseGate array
-  int32_t coef_off;       // first coefficient (32-bit words) in the phase table
+  int32_t coef_off;       // first coefficient alpha, beta of the stage (n + n(n-1)/2 per stage)
   int32_t mom_off;        // first moment among the phase moments
 };
 struct alignas(16) QPhaseGate {
-  int32_t c, t, param, pad;   // control and target qubits, parameter index
+  int32_t c, t, param, layer;   // control and target qubits, parameter index, sweep layer behind the stage
 };
 QP_HD inline constexpr int phase_pair_index(int n, int a, int b) {   // a < b
   return a * n - a * (a + 1) / 2 + (b - a - 1);
@@ -133,9 +189,12 @@ QP_HD inline constexpr int phase_terms(int n) { return n + n * (n - 1) / 2; }
 // adjoint slots holding each point's lambda), so a point costs a quarter of a tangent-carrying one.
 // kModeTotal: the Maxwell step of the paper's total loss over the collocation points (residual,
 // energy and symmetry seeds formed in the kernel; the mirror images' outputs come from memory).
-enum Mode : int { kModeFwd = 0, kModeMaxwell = 1, kModeVjp = 2, kModeFwdPk = 3, kModeVjpPk = 4, kModeTotal = 5 };
-QP_HD inline constexpr bool mode_packed(int mode) { return mode == kModeFwdPk || mode == kModeVjpPk; }
-QP_HD inline constexpr bool mode_fwd_only(int mode) { return mode == kModeFwd || mode == kModeFwdPk; }
+// kModeFieldsPk: the packed forward of the total loss's mirror and initial-condition points.
+enum Mode : int { kModeFwd = 0, kModeMaxwell = 1, kModeVjp = 2, kModeFwdPk = 3, kModeVjpPk = 4, kModeTotal = 5, kModeFieldsPk = 6 };
+QP_HD inline constexpr bool mode_packed(int mode) { return mode == kModeFwdPk || mode == kModeVjpPk || mode == kModeFieldsPk; }
+QP_HD inline constexpr bool mode_fwd_only(int mode) { return mode == kModeFwd || mode == kModeFwdPk || mode == kModeFieldsPk; }
+// Modes whose results enter an FP64 loss: their forward runs the rounds.
+QP_HD inline constexpr bool mode_rounds(int mode) { return mode == kModeMaxwell || mode == kModeTotal || mode == kModeFieldsPk; }
 
 // Dense 2^5 blocks (MFMA path): a contiguous run of gates acting on at most five qubits.
 constexpr int kDenseK = 5;
@@ -173,15 +232,25 @@ struct alignas(16) QPlanDev {
   uint32_t zplain[kMaxOut];         // readout parity mask of output i without folding
   int32_t n_head;                   // leading rounds folded into the encoding (rounds 0 .. n_head-1; < n_rounds)
   int32_t head_gate[16];            // per qubit: fused gate of the leading stage, -1 if none
-  int32_t off_lanes;                // QLane[2][n_rounds][2^(n-3)]: forward (0) and reverse (1) exchanges
+  int32_t off_lanes;                // QLane[2][n_rounds][2^(n-3)]: forward (0) and reverse (1) exchanges (the kernels' image: forward only)
   int32_t n_phase;                  // phase stages (CRZ runs)
   int32_t off_phase;                // QPhaseStage[n_phase]
   int32_t off_phase_gates;          // QPhaseGate[...]
-  int32_t n_phase_coef;             // 32-bit words of the phase table (n_phase * phase_terms(n))
+  int32_t n_phase_coef;             // coefficients of the phase stages (n_phase * phase_terms(n))
   int32_t n_moments;                // phase moments accumulated by the adjoint (same count)
   int32_t off_pcsr_ptr;             // int32[n_params+1]: parameter -> CRZ occurrences
   int32_t off_pcsr_idx;             // int32[...]: phase-gate index
-  int32_t pad_end;
+  int32_t n_sweeps;                 // sweep layers, the folded opening layer included
+  int32_t sweep_first;              // 1: layer 0 is the opening layer folded into the encoding
+  int32_t off_sweeps;               // QSweep[n_sweeps]
+  int32_t off_slanes;               // QSweepLane[n_sweeps][2^(n-3)]
+  int32_t off_terms;                // uint32[][2]: CZ terms of the sweep layers
+  int32_t hgate[16];                // per qubit: gate of the folded opening layer, -1 if none
+  int32_t etpos[16];                // mapping in which the product state is formed
+  int32_t ftpos[16];                // mapping at the readout
+  int32_t gtpos[16];                // mapping at the end of the adjoint
+  int32_t off_turn;                 // QTurn
+  int32_t off_tlanes;               // uint32[2^(n-3)][2]
 };
 
 }  // namespace qp

@@ -1,0 +1,312 @@
+// Per-call tables of the sweep layers, formed in FP64 from the parameters and rounded once
+// (O(layers 2^n) work, independent of the point count): the tangents of the layers' rotations, the
+// phase (times the rotations' cosines) of every basis index in front of each layer, the X masks, and
+// what the gradient kernel needs to read the statistics.  See QSweep.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+
+#include "const_dev.hpp"
+#include "fused.hpp"
+#include "qp_internal.hpp"
+#include "rot_dev.hpp"
+
+namespace qp {
+
+// U of a fused gate from its parameters.
+template <typename R>
+__device__ inline void fused_product(const QFused& fu, const float* __restrict__ params, R* u) {
+  set_identity(u);
+#pragma unroll 1
+  for (int c = 0; c < fu.ncomp; ++c) {
+    R s, co;
+    if constexpr (sizeof(R) == 4) sincosf(0.5f * params[fu.param[c]], &s, &co);
+    else sincos(0.5 * (double)params[fu.param[c]], &s, &co);
+    left_mul_rot<R>(fu.kind[c], co, s, u);
+  }
+}
+
+// The matrix of gate f for the rounds and the encoding, formed in FP64 and rounded once (fp32: in FP32,
+// kept for comparison); f = n_fused: the identity (absent gates of a round).
+__device__ inline void gate_entry(const QPlanDev* __restrict__ plan, const float* __restrict__ params, int f, int fp32,
+                                  float* __restrict__ gtab) {
+  float* o = gtab + (size_t)f * kGT;
+  if (f == plan->n_fused) {
+    float u[8];
+    set_identity(u);
+    store_gate_entry(o, u);
+    return;
+  }
+  const QFused& fu = (reinterpret_cast<const QFused*>(reinterpret_cast<const char*>(plan) + plan->off_fused))[f];
+  if (fp32) {
+    float u[8];
+    fused_product<float>(fu, params, u);
+    store_gate_entry(o, u);
+  } else {
+    double u[8];
+    fused_product<double>(fu, params, u);
+    store_gate_entry(o, u);
+  }
+}
+
+// Phase-stage coefficient i of the rounds in 32-bit fractions of a turn: alpha_q = -(1/2) sum_t
+// theta_qt, beta_qq' = theta_qq' + theta_q'q (see QPhaseStage), formed in FP64.
+__device__ inline void phase_entry(const QPlanDev* __restrict__ plan, const float* __restrict__ params, int i,
+                                   uint32_t* __restrict__ coef) {
+  const int n = plan->n, nt = phase_terms(n);
+  const char* pb = reinterpret_cast<const char*>(plan);
+  const QPhaseStage& st = reinterpret_cast<const QPhaseStage*>(pb + plan->off_phase)[i / nt];
+  const QPhaseGate* gates = reinterpret_cast<const QPhaseGate*>(pb + plan->off_phase_gates) + st.gate0;
+  const int e = i % nt;
+  int qa = e, qb = -1;   // alpha_qa, or beta of the pair (qa, qb)
+  if (e >= n) {
+    int r = e - n;
+    qa = 0;
+    while (r >= n - 1 - qa) { r -= n - 1 - qa; ++qa; }
+    qb = qa + 1 + r;
+  }
+  double turns = 0.0;
+  const double inv2pi = 0.15915494309189533577;
+  for (int g = 0; g < st.ngates; ++g) {
+    const double th = (double)params[gates[g].param];
+    if (qb < 0) {
+      if (gates[g].c == qa) turns -= 0.5 * th * inv2pi;
+    } else if ((gates[g].c == qa && gates[g].t == qb) || (gates[g].c == qb && gates[g].t == qa)) {
+      turns += th * inv2pi;
+    }
+  }
+  const double frac = turns - floor(turns);                 // [0, 1)
+  coef[st.coef_off + e] = (uint32_t)(unsigned long long)(frac * 4294967296.0);
+}
+
+// U = e^{i g} RZ(a) RY(b) RZ(c): u00 = e^{-i(a+c)/2} cos(b/2), u10 = e^{i(a-c)/2} sin(b/2).  The phases of
+// u00 and u10 give e^{ia} and e^{ic}; RZ(a) is diag(1, e^{ia}) up to a global phase, which no result
+// depends on.  flip: RY(b) = RY(pi) RY(b - pi) where |tan(b/2)| > 1; t is the tangent that is left.
+struct Zyz {
+  double2 a, c;   // e^{ia}, e^{ic}
+  double t, cosb;
+  int flip;
+};
+__device__ inline int zyz_flip(const double* u) { return u[4] * u[4] + u[5] * u[5] > u[0] * u[0] + u[1] * u[1]; }
+__device__ inline double2 cmul(double2 x, double2 y) { return make_double2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x); }
+__device__ inline Zyz zyz_split(const double* u) {
+  Zyz z;
+  const double n0 = u[0] * u[0] + u[1] * u[1], n1 = u[4] * u[4] + u[5] * u[5];
+  const double i0 = rsqrt(n0), i1 = rsqrt(n1), r0 = n0 > 0.0 ? n0 * i0 : 0.0, r1 = n1 > 0.0 ? n1 * i1 : 0.0;
+  const double2 p0 = r0 > 0.0 ? make_double2(u[0] * i0, u[1] * i0) : make_double2(1.0, 0.0);
+  const double2 p1 = r1 > 0.0 ? make_double2(u[4] * i1, u[5] * i1) : make_double2(1.0, 0.0);
+  const double2 q = cmul(p0, p1);
+  z.a = cmul(p1, make_double2(p0.x, -p0.y));
+  z.c = make_double2(q.x, -q.y);
+  z.flip = zyz_flip(u);
+  z.t = z.flip ? -r0 * i1 : r1 * i0;
+  z.cosb = z.flip ? r1 : r0;   // (U has unit determinant)
+  return z;
+}
+
+constexpr int kTabThreads = 256;
+
+// Block blk of a circuit's tables (kTabThreads threads; all of them call this).  What bounds it is
+// latency: dependent loads, barriers, and code run once from a cold instruction cache.  So everything
+// that comes from the plan is fetched before anything is formed, uniform data by scalar loads, and the
+// layer's rotations are written by another wave than the first entries.
+__device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict__ params, const SweepTabs& T, int blk,
+                                    int fp32) {
+  __shared__ uint32_t flips[kMaxSweeps];
+  __shared__ double2 s_c[kMaxQubits], s_a[kMaxQubits];   // by the qubit's index bit, as the three below
+  __shared__ double s_cos[kMaxQubits], s_t[kMaxQubits];
+  __shared__ int s_flip[kMaxQubits];
+  __shared__ double2 s_trig[kTabThreads];
+  __shared__ uint32_t s_x, s_xo;
+  const int tid = threadIdx.x;
+  const QPlanDev* gplan = A.plan;
+  CP<QPlanDev> plan = to_const(gplan);
+  CP<char> pb = reinterpret_cast<CP<char>>(plan);
+  const QFused* fused = reinterpret_cast<const QFused*>(reinterpret_cast<const char*>(gplan) + A.off_fused);
+  CP<QSweep> sweeps = reinterpret_cast<CP<QSweep>>(pb + A.off_sweeps);
+  const int n = A.n, F = A.n_fused, S = A.n_sweeps, L0 = A.sweep_first;
+  const int cpl = (1 << n) > kTabThreads ? (1 << n) / kTabThreads : 1;
+  if (blk == 0) {
+    for (int f = tid; f <= F; f += kTabThreads) gate_entry(gplan, params, f, fp32, T.gtab);
+    return;
+  }
+  const int l = L0 + (blk - 1) / cpl, chunk = (blk - 1) % cpl;   // l = S: behind the last layer
+  if (l > S) {
+    for (int i = tid; i < plan->n_phase_coef; i += kTabThreads)
+      phase_entry(gplan, params, i, reinterpret_cast<uint32_t*>(T.gtab + (size_t)(F + 1) * kGT));
+    return;
+  }
+  // a thread per rotation takes its sine, then one per gate multiplies them up
+  constexpr int kGates = kTabThreads / 3;
+  const int rc = tid % 3, ti = tid - (kTabThreads - 64);
+  QFused fu{};
+  int nc = 0, pi = 0;
+  if (F > 0) {   // a circuit without parameters has no gate to read and may have no parameter array
+    fu = fused[tid < F ? tid : 0];
+    nc = fused[tid / 3 < F ? tid / 3 : 0].ncomp;
+    pi = fused[tid / 3 < F ? tid / 3 : 0].param[rc];
+  }
+  constexpr int kAhead = 4;
+  const uint32_t* grows = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(gplan) + A.off_sweeps +
+                                                            offsetof(QSweep, arow));
+  auto row_of = [&](int k) { return k >= 0 && k < S && tid < 16 ? grows[(size_t)k * (sizeof(QSweep) / 4) + tid] : 0u; };
+  uint32_t ahead[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) ahead[i] = row_of(S - 1 - i);
+  const uint32_t row_l = row_of(l);
+  CP<QSweep> L = sweeps + (l < S ? l : 0);
+  const bool rot = ti >= 0 && ti < kPos && l < S;
+  const int my_gate = rot ? reinterpret_cast<const QSweep*>(reinterpret_cast<const char*>(gplan) + A.off_sweeps)[l].gate[ti] : -1;
+  CP<int32_t> tin = reinterpret_cast<CP<int32_t>>(pb + (l < S ? A.off_sweeps + l * (int)sizeof(QSweep) + (int)offsetof(QSweep, tin)
+                                                              : (int)offsetof(QPlanDev, ftpos)));
+  int tb[kMaxQubits];   // index bit of each position of the mapping
+#pragma unroll
+  for (int k = 0; k < kMaxQubits; ++k) tb[k] = k < n ? tin[k] : 0;
+  float th = F > 0 ? params[rc < nc ? pi : 0] : 0.f;
+  // this thread's index in the layer's mapping, without the X mask, and where it was before the index map
+  // (linear, so the mask's share is added later)
+  const int i = chunk * kTabThreads + tid;
+  const uint32_t v = sweep_thread((uint32_t)i >> 3, n), r = (uint32_t)i & 7u;
+  uint32_t ji = 0, joi = 0;
+#pragma unroll
+  for (int k = 0; k < kMaxQubits; ++k)
+    if (k < n) ji ^= ((k < 3 ? r >> k : v >> (k - 3)) & 1u) << tb[k];
+  if (l < S)
+#pragma unroll
+    for (int b = 0; b < kMaxQubits; ++b)
+      if (b < n) joi |= ((uint32_t)__popc(L->arow[b] & ji) & 1u) << b;
+  for (int k = l + tid; k < S; k += kTabThreads) flips[k] = 0;
+  if (tid < kMaxQubits) {
+    s_c[tid] = s_a[tid] = make_double2(1.0, 0.0);
+    s_t[tid] = 0.0; s_cos[tid] = 1.0; s_flip[tid] = 0;
+  }
+  // flips from layer l on; layer l's gates, and those before it (sincospi: no long argument reduction, and
+  // good to FP64 rounding all the same)
+  for (int f0 = 0; f0 < F; f0 += kGates) {
+    const int f = f0 + tid, fr = f0 + tid / 3;
+    if (f0) {
+      fu = fused[f < F ? f : 0];
+      nc = fused[fr < F ? fr : 0].ncomp, pi = fused[fr < F ? fr : 0].param[rc];
+      th = params[rc < nc ? pi : 0];
+    }
+    if (tid < 3 * kGates && fr < F) {
+      double sn, cn;
+      if (fp32) {
+        float sf, cf;
+        sincosf(0.5f * th, &sf, &cf);
+        sn = sf; cn = cf;
+      } else {
+        sincospi(0.5 * 0.31830988618379067154 * (double)th, &sn, &cn);
+      }
+      s_trig[tid] = make_double2(cn, sn);
+    }
+    __syncthreads();
+    if (tid < kGates && f < F && !fu.head && fu.layer >= l - 1) {
+      double u[8];
+      set_identity(u);
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < fu.ncomp) left_mul_rot<double>(fu.kind[k], s_trig[3 * tid + k].x, s_trig[3 * tid + k].y, u);
+      const int b = n - 1 - fu.qubit, flip = zyz_flip(u);
+      if (fu.layer >= l && flip) atomicOr(&flips[fu.layer], 1u << b);
+      if (fu.layer <= l) {
+        const Zyz z = zyz_split(u);
+        if (fu.layer == l) { s_c[b] = z.c; s_cos[b] = z.cosb; s_t[b] = z.t; }
+        else { s_a[b] = z.a; s_flip[b] = flip; }
+      }
+    }
+    __syncthreads();
+  }
+  if (F == 0) __syncthreads();
+  if (tid < 64) {   // layer l's X mask, carried back from the readout through the index maps (ballots of row parities)
+    uint32_t x = 0;
+    auto step = [&](int k, uint32_t row) {
+      x ^= __builtin_amdgcn_readfirstlane(flips[k]);
+      if (k > l) x = (uint32_t)__ballot((int)(__popc(x & row) & 1u));
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (S - 1 - i >= l) step(S - 1 - i, ahead[i]);
+#pragma unroll 1
+    for (int k = S - 1 - kAhead; k >= l; --k) step(k, row_of(k));
+    const uint32_t xo = l < S ? (uint32_t)__ballot((int)(__popc(x & row_l) & 1u)) : x;   // before the index map
+    if (tid == 0) {
+      s_x = x;
+      s_xo = xo;
+      if (l == L0) T.xmask[S] = xo;   // the product state's (behind the opening layer, or in front of the first)
+    }
+  }
+  double mag = 1.0;
+#pragma unroll
+  for (int b = 0; b < kMaxQubits; ++b) mag *= s_cos[b];
+  __syncthreads();
+  const uint32_t x = s_x;
+  if (l == L0 && chunk == 0 && L0 > 0) {   // the opening layer: nothing is pulled back
+    if (tid < kTC) T.tcoef[tid] = 0.f;
+    if (tid == 0) { T.xmask[0] = s_xo; T.lscale[0] = 1.0; }
+    for (int f = tid; f < F; f += kTabThreads) {
+      if (!fused[f].head) continue;
+      double* g = T.gpar + (size_t)f * kGP;
+      g[0] = 1.0; g[1] = 0.0; g[2] = 1.0;
+      g[3] = ((s_xo >> (n - 1 - fused[f].qubit)) & 1u) ? -1.0 : 1.0;
+    }
+  }
+  if (chunk == 0 && l < S && ti >= 0 && ti < kTC) {
+    if (ti == 0) { T.xmask[l] = x; T.lscale[l] = mag * mag; }
+    float t = 0.f;
+    if (my_gate >= 0) {
+      // S_x, S_y: the cosines of the gates pulled back when they are taken (wave positions first,
+      // then the swap slots, then the rest); S_z: of all
+      const int from = ti >= 9 ? 9 : (ti >= 7 ? 7 : 0);
+      double sc = 1.0;
+      int b = 0;
+#pragma unroll
+      for (int p = 0; p < kMaxQubits; ++p) {
+        b = p == ti ? tb[p] : b;
+        if (p < n && p >= from) sc *= s_cos[tb[p]] * s_cos[tb[p]];
+      }
+      const bool neg = (x >> b) & 1u;   // X RY(b) X = RY(-b)
+      t = (float)(neg ? -s_t[b] : s_t[b]);
+      double* gp = T.gpar + (size_t)my_gate * kGP;
+      gp[0] = s_c[b].x; gp[1] = s_c[b].y;
+      gp[2] = sc;
+      gp[3] = neg ? -mag * mag : mag * mag;
+    }
+    T.tcoef[(size_t)l * kTC + ti] = t;
+  }
+  if (i >= (1 << n)) return;
+  const uint32_t j = ji ^ x, jo = l < S ? joi ^ s_xo : j;   // basis index of this entry, and before the index map
+  // two products, so that their chains overlap
+  double2 ph = make_double2(mag, 0.0), pa = make_double2(1.0, 0.0);
+  int half = 0;     // half turns
+  for (int b0 = 0; b0 < n; b0 += 4)
+#pragma unroll
+    for (int b = b0; b < b0 + 4; ++b) {
+      if ((j >> b) & 1u) ph = cmul(ph, s_c[b]);
+      if ((jo >> b) & 1u) pa = cmul(pa, s_a[b]);
+      else half += s_flip[b];   // RY(pi) = diag(-1, 1) X
+    }
+  ph = cmul(ph, pa);
+  if (l < S) {
+    CP<uint32_t> terms = reinterpret_cast<CP<uint32_t>>(pb + plan->off_terms) + 2 * L->term0;
+    for (int t = 0; t < L->nterms; ++t) half += __popc(terms[2 * t] & j) & __popc(terms[2 * t + 1] & j) & 1;
+    if (L->phase >= 0) {
+      CP<QPhaseStage> st = reinterpret_cast<CP<QPhaseStage>>(pb + plan->off_phase) + L->phase;
+      CP<QPhaseGate> pg = reinterpret_cast<CP<QPhaseGate>>(pb + plan->off_phase_gates) + st->gate0;
+      double turn = 0.0;   // in units of pi
+      for (int g = 0; g < st->ngates; ++g)
+        if ((j >> (n - 1 - pg[g].c)) & 1u) {
+          const double th = 0.5 * 0.31830988618379067154 * (double)params[pg[g].param];
+          turn += ((j >> (n - 1 - pg[g].t)) & 1u) ? th : -th;
+        }
+      double2 e;
+      sincospi(turn, &e.y, &e.x);
+      ph = cmul(ph, e);
+    }
+  }
+  if (half & 1) ph = make_double2(-ph.x, -ph.y);
+  T.ptab[((size_t)(l - L0) << n) + i] = make_float2((float)ph.x, (float)ph.y);
+}
+
+}  // namespace qp
