@@ -152,6 +152,7 @@ extern "C" qp_status qp_circuit_set_launch(qp_circuit* c, int32_t exchange_plane
     return fail(c->ctx, QP_EINVAL, "qp_circuit_set_launch: %d workgroups of %zu LDS bytes do not fit a CU", wg_per_cu, lds);
   c->exs = exchange_planes;
   c->wg_per_cu = wg_per_cu;
+  c->launch_set = true;
   c->use_dense = false;   // an explicit launch shape of the fused kernel
   return QP_OK;
 }
@@ -441,12 +442,16 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   }
   // packed modes: four points per thread group, so a tile covers four times the points
   const int64_t P_slots = mode_packed(mode) ? (P + 3) / 4 : P;
+  const bool fwd = mode_fwd_only(mode);   // no statistics
+  int exs = NM > 0 ? 2 : (exs_override > 0 ? exs_override : c->exs);   // phases: unpipelined kernel
   int grid = fused_grid(ctx, c, P_slots);
+  if (fwd && !c->launch_set && n < 12) {   // as many workgroups as the registers hold (4 waves each)
+    exs = 2;
+    grid = (int)std::min<int64_t>((int64_t)ctx->cu_count * fwd_waves(n, exs), (P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
+  }
   if (grid_override > 0)
     grid = (int)std::min<int64_t>(grid_override, (P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
   grid = std::min(grid, cap);
-  const int exs = NM > 0 ? 2 : (exs_override > 0 ? exs_override : c->exs);   // phases: unpipelined kernel
-  const bool fwd = mode_fwd_only(mode);   // no statistics
   FusedArgs a{};
   a.plan = c->dplan;
   a.gtab = tabs.gtab;

@@ -31,6 +31,7 @@ struct qp_circuit {
   qp::PlainGate* dpgates = nullptr;
   int exs = 4;         // exchange planes per LDS phase
   int wg_per_cu = 1;   // persistent workgroups per CU
+  bool launch_set = false;   // the two above were set by qp_circuit_set_launch
   int dense_chunk = 0; // points per chunk of the dense-block path (0: about 2 GiB of statevectors)
   bool use_dense = false;   // the tuner's fusion width for Maxwell calls: dense 32x32 blocks
 };

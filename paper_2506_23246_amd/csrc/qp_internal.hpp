@@ -193,6 +193,11 @@ QP_HD inline constexpr int phase_terms(int n) { return n + n * (n - 1) / 2; }
 enum Mode : int { kModeFwd = 0, kModeMaxwell = 1, kModeVjp = 2, kModeFwdPk = 3, kModeVjpPk = 4, kModeTotal = 5, kModeFieldsPk = 6 };
 QP_HD inline constexpr bool mode_packed(int mode) { return mode == kModeFwdPk || mode == kModeVjpPk || mode == kModeFieldsPk; }
 QP_HD inline constexpr bool mode_fwd_only(int mode) { return mode == kModeFwd || mode == kModeFwdPk || mode == kModeFieldsPk; }
+// Waves per SIMD of the forward-only kernels: half the statevectors of an adjoint, so more waves fit.
+// 7 qubits, 64000 points, forward: 155 us at 2 waves, 112 at 4; 10 qubits, 20000 points, outputs only: 175 us
+// at 2 waves (4 exchange planes), 150 at 3.  At 12 qubits a workgroup is 2 waves per SIMD, and two of them
+// leave 128 registers, where the kernel spills 200.
+QP_HD inline constexpr int fwd_waves(int n, int exs) { return n < 10 ? 4 : (n < 12 && exs == 2 ? 3 : 2); }
 // Modes whose results enter an FP64 loss: their forward runs the rounds.
 QP_HD inline constexpr bool mode_rounds(int mode) { return mode == kModeMaxwell || mode == kModeTotal || mode == kModeFieldsPk; }
 
