@@ -90,7 +90,7 @@ __device__ __forceinline__ void rot_lane(float (&sr)[8][8], float (&si)[8][8], f
 // Statistics of a statevector pair (x: lambda-family 4 + C, y: psi-family C):
 //   S_x = sum Im(conj(x) y'), S_y = sum +-Re(conj(x) y') (+ where the bit is set), y' the amplitude with
 // the gate's bit flipped.  Register bit B:
-template <int B, int C>
+template <int B, int C, int X = 4 + C>
 __device__ __forceinline__ void stat_reg(const float (&sr)[8][8], const float (&si)[8][8], float& sx, float& sy) {
   float a[2] = {0.f, 0.f}, b[2] = {0.f, 0.f};   // two partial sums: shorter dependent chains
   int np = 0;
@@ -98,7 +98,7 @@ __device__ __forceinline__ void stat_reg(const float (&sr)[8][8], const float (&
   for (int r = 0; r < 8; ++r) {
     if (r & (1 << B)) continue;
     const int r1 = r | (1 << B), h = np++ & 1;
-    const float x0r = sr[4 + C][r], x0i = si[4 + C][r], x1r = sr[4 + C][r1], x1i = si[4 + C][r1];
+    const float x0r = sr[X][r], x0i = si[X][r], x1r = sr[X][r1], x1i = si[X][r1];
     const float y0r = sr[C][r], y0i = si[C][r], y1r = sr[C][r1], y1i = si[C][r1];
     a[h] = fmaf(x0r, y1i, a[h]); a[h] = fmaf(-x0i, y1r, a[h]);
     a[h] = fmaf(x1r, y0i, a[h]); a[h] = fmaf(-x1i, y0r, a[h]);
@@ -122,10 +122,10 @@ __device__ __forceinline__ void stat_reg(const float (&sr)[8][8], const float (&
       "v_fmac_f32_dpp %2, -%7, %19" D "v_fmac_f32_dpp %3, %11, %19" D                                          \
       : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1)                                                                \
       : "v"(sr[C][R]), "v"(sr[C][R + 1]), "v"(sr[C][R + 2]), "v"(sr[C][R + 3]), "v"(si[C][R]),                 \
-        "v"(si[C][R + 1]), "v"(si[C][R + 2]), "v"(si[C][R + 3]), "v"(sr[4 + C][R]), "v"(sr[4 + C][R + 1]),     \
-        "v"(sr[4 + C][R + 2]), "v"(sr[4 + C][R + 3]), "v"(si[4 + C][R]), "v"(si[4 + C][R + 1]),                \
-        "v"(si[4 + C][R + 2]), "v"(si[4 + C][R + 3]))
-template <int K, int C, int R>
+        "v"(si[C][R + 1]), "v"(si[C][R + 2]), "v"(si[C][R + 3]), "v"(sr[X][R]), "v"(sr[X][R + 1]),     \
+        "v"(sr[X][R + 2]), "v"(sr[X][R + 3]), "v"(si[X][R]), "v"(si[X][R + 1]),                \
+        "v"(si[X][R + 2]), "v"(si[X][R + 3]))
+template <int K, int C, int X, int R>
 __device__ __forceinline__ void stat_lane4(const float (&sr)[8][8], const float (&si)[8][8], float& a0, float& b0,
                                            float& a1, float& b1) {
   if constexpr (K == 0) QP_STAT_LANE(QP_DPP_0);
@@ -133,21 +133,21 @@ __device__ __forceinline__ void stat_lane4(const float (&sr)[8][8], const float 
   else if constexpr (K == 2) QP_STAT_LANE(QP_DPP_2);
   else QP_STAT_LANE(QP_DPP_3);
 }
-template <int K, int C>
+template <int K, int C, int X = 4 + C>
 __device__ __forceinline__ void stat_lane(const float (&sr)[8][8], const float (&si)[8][8], float& sx, float& sy) {
   float a0 = 0.f, b0 = 0.f, a1 = 0.f, b1 = 0.f;   // two partial sums: shorter dependent chains
-  stat_lane4<K, C, 0>(sr, si, a0, b0, a1, b1);
-  stat_lane4<K, C, 4>(sr, si, a0, b0, a1, b1);
+  stat_lane4<K, C, X, 0>(sr, si, a0, b0, a1, b1);
+  stat_lane4<K, C, X, 4>(sr, si, a0, b0, a1, b1);
   sx += a0 + a1;
   sy += b0 + b1;
 }
 // w_r += Im(conj(x_r) y_r): its signed sums are the S_z of every qubit and the moments of CRZ phases.
-template <int C>
+template <int C, int X = 4 + C>
 __device__ __forceinline__ void stat_diag(const float (&sr)[8][8], const float (&si)[8][8], float (&w)[8]) {
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    w[r] = fmaf(sr[4 + C][r], si[C][r], w[r]);
-    w[r] = fmaf(-si[4 + C][r], sr[C][r], w[r]);
+    w[r] = fmaf(sr[X][r], si[C][r], w[r]);
+    w[r] = fmaf(-si[X][r], sr[C][r], w[r]);
   }
 }
 
@@ -946,9 +946,7 @@ __device__ __forceinline__ void static_for(const Fn& f) {
 // opening rotation stage is folded into the encoding, the sweep ends at that stage's output, and
 // G_q is replaced by U_q G_q U_q^H (U_q the stage's gate on qubit q), which the statistics
 // contract with as an axis (n_x, n_y, n_z).  At the end of the sweep the statevectors sit in mapping
-// gtpos.  The partner amplitude of a pair (index bit of qubit q flipped) lies in the
-// same thread (register bit) or in another thread of the point (thread bit); it is read back from
-// the LDS planes, where the psi-family is staged two statevectors at a time.
+// gtpos.
 template <int N, int T>
 __device__ __forceinline__ float enc_pair(float nx, float ny, float nz, float sb, float xr, float xi, float yor,
                                           float yoi, float2 yp) {
@@ -958,7 +956,142 @@ __device__ __forceinline__ float enc_pair(float nx, float ny, float nz, float sb
   return nx * im_p + sb * (ny * re_p - nz * im_o);
 }
 
-// One of two passes (PASS 0: partners of psi and dpsi_t; PASS 1: of dpsi_x and dpsi_y).  The
+// Axis (n_x, n_y, n_z) of U G U^H (U: the opening-stage gate on q, identity if none; G = X or Y).
+__device__ __forceinline__ void enc_axis(CP<QPlanDev> plan, CP<float> gtab, int q, float& nx, float& ny, float& nz) {
+  const bool rx = plan->enc_gate == QP_ENC_RX;
+  float u8[8] = {1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 1.f, 0.f};
+  const int hg = plan->hgate[q];
+  if (hg >= 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u8[i] = gtab[hg * kGT + i];
+  }
+  // W = U G: X swaps U's columns; Y gives [[i u01, -i u00], [i u11, -i u10]]
+  float w00r, w00i, w01r, w01i;
+  if (rx) {
+    w00r = u8[2]; w00i = u8[3]; w01r = u8[0]; w01i = u8[1];
+  } else {
+    w00r = -u8[3]; w00i = u8[2]; w01r = u8[1]; w01i = -u8[0];
+  }
+  // M = W U^H: M00 = W00 conj(u00) + W01 conj(u01), M01 = W00 conj(u10) + W01 conj(u11)
+  const float m00r = w00r * u8[0] + w00i * u8[1] + w01r * u8[2] + w01i * u8[3];
+  const float m01r = w00r * u8[4] + w00i * u8[5] + w01r * u8[6] + w01i * u8[7];
+  const float m01i = w00i * u8[4] - w00r * u8[5] + w01i * u8[6] - w01r * u8[7];
+  nx = m01r; ny = -m01i; nz = m00r;
+}
+
+// Sum over the point's lanes (up to 9 qubits), in all of them.
+template <int N>
+__device__ __forceinline__ float point_sum(float v) {
+  if constexpr (N > 3) v += dppf<0xB1>(v);    // lane ^ 1
+  if constexpr (N > 4) v += dppf<0x4E>(v);    // lane ^ 2
+  if constexpr (N > 5) v += dppf<0x141>(v);   // the other four of eight lanes
+  if constexpr (N > 6) v += dppf<0x128>(v);   // lane ^ 8
+  if constexpr (N > 7) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = __int_as_float(sw[0]) + __int_as_float(sw[1]);
+  }
+  if constexpr (N > 8) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = __int_as_float(sw[0]) + __int_as_float(sw[1]);
+  }
+  return v;
+}
+
+// Up to 9 qubits a point's lanes are in one wave, and the sums are those of a layer's statistics, per
+// point and contracted with the axis: G = 0 of all pairs (in Q already if the circuit opens with
+// rotations, whose statistics are taken of the same statevectors), G = 1 .. 3 of psi with mu_(G-1).
+// (Forward and backward at 7 qubits, 64000 points: 738 us with the staging below, 663 so.)
+template <int N, int C, int X>
+__device__ __forceinline__ void enc_stat(const float (&sr)[8][8], const float (&si)[8][8], Stats<N>& Q) {
+  stat_reg<0, C, X>(sr, si, Q.x[0], Q.y[0]);
+  stat_reg<1, C, X>(sr, si, Q.x[1], Q.y[1]);
+  stat_reg<2, C, X>(sr, si, Q.x[2], Q.y[2]);
+  if constexpr (N > 3) stat_lane<0, C, X>(sr, si, Q.x[3], Q.y[3]);
+  if constexpr (N > 4) stat_lane<1, C, X>(sr, si, Q.x[4], Q.y[4]);
+  if constexpr (N > 5) stat_lane<2, C, X>(sr, si, Q.x[5], Q.y[5]);
+  if constexpr (N > 6) stat_lane<3, C, X>(sr, si, Q.x[6], Q.y[6]);
+  stat_diag<C, X>(sr, si, Q.w);
+}
+template <int N, int C, int X>
+__device__ __forceinline__ void enc_stat_slots(const float (&sr)[8][8], const float (&si)[8][8], Stats<N>& Q) {
+  if constexpr (N > 7) stat_reg<0, C, X>(sr, si, Q.x[7], Q.y[7]);
+  if constexpr (N > 8) stat_reg<1, C, X>(sr, si, Q.x[8], Q.y[8]);
+}
+template <int N, int P0, int P1>
+__device__ __forceinline__ void enc_write(const Stats<N>& Q, CP<QPlanDev> plan, CP<float> gtab, uint32_t x, uint32_t v,
+                                          float* __restrict__ out, int stride, bool first) {
+  float w0 = 0.f;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) w0 += Q.w[r];
+#pragma unroll
+  for (int p = P0; p < P1; ++p) {
+    const int b = plan->gtpos[p], q = N - 1 - b;
+    float nx, ny, nz;
+    enc_axis(plan, gtab, q, nx, ny, nz);
+    float y = Q.y[p], z = 0.f;
+    if (p < 3) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) z += ((r >> (p < 3 ? p : 0)) & 1) ? -Q.w[r] : Q.w[r];
+    } else {
+      const bool set = (v >> (p - 3)) & 1u;
+      z = set ? -w0 : w0;
+      if (p < 7) y = set ? y : -y;
+    }
+    const float yz = ny * y + nz * z;
+    const float s = point_sum<N>(nx * Q.x[p] + (((x >> b) & 1u) ? -yz : yz));
+    if (first) out[(long long)q * stride] = s;
+  }
+}
+template <int N>
+__device__ __forceinline__ void encoding_grads_wave(float (&sr)[8][8], float (&si)[8][8], Stats<N>& Q, CP<QPlanDev> plan,
+                                                    CP<float> gtab, const FusedArgs& a, long long pt, bool first, uint32_t v) {
+  constexpr int NB = N < 7 ? N : 7;   // positions in place; the rest in the swap slots
+  const uint32_t x = to_const(a.xmask)[plan->n_sweeps];
+  float* da = a.d_angles + pt * N;
+  float* dj = a.d_jac + pt * N * 3;
+  const bool head = plan->sweep_first > 0;
+  if (a.d_angles) {
+    if (!head) {
+      clear(Q);
+      enc_stat<N, 0, 4>(sr, si, Q); enc_stat<N, 1, 5>(sr, si, Q); enc_stat<N, 2, 6>(sr, si, Q); enc_stat<N, 3, 7>(sr, si, Q);
+    }
+    enc_write<N, 0, NB>(Q, plan, gtab, x, v, da, 1, first);
+    if (N > 7 && head) enc_write<N, NB, N>(Q, plan, gtab, x, v, da, 1, first);
+  }
+  float w[4][8];   // the diagonal products, kept for the swap slots
+#pragma unroll
+  for (int r = 0; r < 8; ++r) w[0][r] = Q.w[r];
+  auto jac = [&](auto c) {
+    constexpr int G = decltype(c)::value;
+    clear(Q);
+    enc_stat<N, 0, 4 + G>(sr, si, Q);
+    enc_write<N, 0, NB>(Q, plan, gtab, x, v, dj + G - 1, 3, first);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) w[G][r] = Q.w[r];
+  };
+  if (a.d_jac) { jac(IntC<1>{}); jac(IntC<2>{}); jac(IntC<3>{}); }
+  if constexpr (N > 7) {
+    static_for<0, 8>([&](auto c) { swap_all<N, decltype(c)::value>(sr, si); });
+    auto slots = [&](auto c) {
+      constexpr int G = decltype(c)::value;
+      clear<N, 7, N>(Q);
+      if constexpr (G == 0) {
+        enc_stat_slots<N, 0, 4>(sr, si, Q); enc_stat_slots<N, 1, 5>(sr, si, Q);
+        enc_stat_slots<N, 2, 6>(sr, si, Q); enc_stat_slots<N, 3, 7>(sr, si, Q);
+      } else {
+        enc_stat_slots<N, 0, 4 + G>(sr, si, Q);
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) Q.w[r] = w[G][r];
+      enc_write<N, NB, N>(Q, plan, gtab, x, v, G == 0 ? da : dj + G - 1, G == 0 ? 1 : 3, first);
+    };
+    if (a.d_angles && !head) slots(IntC<0>{});
+    if (a.d_jac) { slots(IntC<1>{}); slots(IntC<2>{}); slots(IntC<3>{}); }
+  }
+}
+
+// From 10 qubits on the partner amplitude of a pair (index bit of qubit q flipped) is read back from the
+// LDS planes, where the psi-family is staged two statevectors at a time.  One of two passes (PASS 0: partners of psi and dpsi_t; PASS 1: of dpsi_x and dpsi_y).  The
 // qubits are taken one at a time (a loop, so no per-qubit register arrays), each qubit's sums are
 // reduced over the point's threads at once, and the point's first thread writes them (PASS 0) or
 // adds its share (PASS 1).
@@ -981,7 +1114,6 @@ __device__ __forceinline__ void enc_grad_pass(const float (&sr)[8][8], const flo
     buf[PLANE + e] = make_float2(sr[2 * PASS + 1][r], si[2 * PASS + 1][r]);
   }
   point_fence<N>();
-  const bool rx = plan->enc_gate == QP_ENC_RX;
 #pragma unroll 1
   for (int q = 0; q < N; ++q) {
     const int pos = N - 1 - q;
@@ -993,25 +1125,8 @@ __device__ __forceinline__ void enc_grad_pass(const float (&sr)[8][8], const flo
         else tmask = sweep_xor(k - 3);
       }
     }
-    // axis of U G U^H (U: the opening-stage gate on q, identity if none; G = X or Y)
-    float u8[8] = {1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 1.f, 0.f};
-    const int hg = plan->hgate[q];
-    if (hg >= 0) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) u8[i] = gtab[hg * kGT + i];
-    }
-    // W = U G: X swaps U's columns; Y gives [[i u01, -i u00], [i u11, -i u10]]
-    float w00r, w00i, w01r, w01i;
-    if (rx) {
-      w00r = u8[2]; w00i = u8[3]; w01r = u8[0]; w01i = u8[1];
-    } else {
-      w00r = -u8[3]; w00i = u8[2]; w01r = u8[1]; w01i = -u8[0];
-    }
-    // M = W U^H: M00 = W00 conj(u00) + W01 conj(u01), M01 = W00 conj(u10) + W01 conj(u11)
-    const float m00r = w00r * u8[0] + w00i * u8[1] + w01r * u8[2] + w01i * u8[3];
-    const float m01r = w00r * u8[4] + w00i * u8[5] + w01r * u8[6] + w01i * u8[7];
-    const float m01i = w00i * u8[4] - w00r * u8[5] + w01i * u8[6] - w01r * u8[7];
-    const float nx = m01r, ny = -m01i, nz = m00r;
+    float nx, ny, nz;
+    enc_axis(plan, gtab, q, nx, ny, nz);
     const uint32_t ptid = tid ^ tmask;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll
@@ -1763,7 +1878,8 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
       uint32_t t2 = threadIdx.x;
       asm volatile("" : "+v"(t2));
       const long long pt2 = PK ? 0 : (long long)tile * PPW + (long long)(t2 / TP);
-      encoding_grads<N, T>(sr, si, buf, red, plan, gtab, a, pt2, pt2 < a.P, u);
+      if constexpr (N < 10) encoding_grads_wave<N>(sr, si, Q, plan, gtab, a, pt2, pt2 < a.P && u == 0, v);
+      else encoding_grads<N, T>(sr, si, buf, red, plan, gtab, a, pt2, pt2 < a.P, u);
     }
   }
 }
@@ -1775,7 +1891,7 @@ __global__ __launch_bounds__(T, mode_fwd_only(MODE) ? fwd_waves(N, EXS) : 2) voi
   constexpr int PLANE = T * 8;
   // Exchange planes in static LDS (their address is a link-time constant, so every access is
   // one XOR of a byte offset); gate statistics and readout scratch in the dynamic part.
-  __shared__ float4 planes[sweep_planes(N, EXS, EG || mode_rounds(MODE)) * PLANE / 2];
+  __shared__ float4 planes[sweep_planes(N, EXS, mode_rounds(MODE)) * PLANE / 2];
   extern __shared__ float4 smem4[];
   float2* buf = reinterpret_cast<float2*>(planes);
   float* slots = reinterpret_cast<float*>(smem4);                   // [WAVES][F][kGS]
