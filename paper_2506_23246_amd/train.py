@@ -73,28 +73,36 @@ def hybrid_total_loss(model: HybridQPINN, points: torch.Tensor, ic_xy: torch.Ten
     phys_kind = int(desc.phys.kind)
     fields, dfields = model(points)
     phys = maxwell_residual_loss(dfields, points, phys_kind, desc.phys.eps_r, desc.phys.x_interface)
-    E, Hx, Hy = fields[:, 0], fields[:, 1], fields[:, 2]
+    E, Hx, Hy = fields[:, :3].unbind(1)
     eps = torch.ones_like(E)
     if phys_kind:
         eps = torch.where(points[:, 1] >= desc.phys.x_interface, torch.full_like(E, desc.phys.eps_r), eps)
-    g = dfields
-    e = (eps * E * g[:, 0, 0] + Hx * g[:, 1, 0] + Hy * g[:, 2, 0]) - (g[:, 0, 1] * Hy + E * g[:, 2, 1]) \
-        + (g[:, 0, 2] * Hx + E * g[:, 1, 2])
+    Et, Ex, Ey, Hxt, _, Hxy, Hyt, Hyx, _ = dfields[:, :3, :3].flatten(1).unbind(1)
+    e = (eps * E * Et + Hx * Hxt + Hy * Hyt) - (Ex * Hy + E * Hyx) + (Ey * Hx + E * Hxy)
     energy = torch.mean(e ** 2)
     my = points.clone()
     my[:, 2] = -my[:, 2]
-    f_my = model.fields(my)
-    sym = (E - f_my[:, 0]) ** 2 + (Hx + f_my[:, 1]) ** 2 + (Hy - f_my[:, 2]) ** 2
+    at = [my]
     if phys_kind == 0:
         mx = points.clone()
         mx[:, 1] = -mx[:, 1]
-        f_mx = model.fields(mx)
-        sym = sym + (E - f_mx[:, 0]) ** 2 + (Hx - f_mx[:, 1]) ** 2 + (Hy + f_mx[:, 2]) ** 2
+        at.append(mx)
+    at.append(torch.cat([torch.zeros_like(ic_xy[:, :1]), ic_xy], dim=1))
+    # the fields away from the collocation points in one evaluation, where the model is a map point by point
+    plain = getattr(model, "plain_network", None)
+    if plain is not None and plain():
+        f = torch.split(model.fields(torch.cat(at)), [len(p) for p in at])
+    else:
+        f = [model.fields(p) for p in at]
+    E1, Hx1, Hy1 = f[0][:, :3].unbind(1)
+    sym = (E - E1) ** 2 + (Hx + Hx1) ** 2 + (Hy - Hy1) ** 2
+    if phys_kind == 0:
+        E2, Hx2, Hy2 = f[1][:, :3].unbind(1)
+        sym = sym + (E - E2) ** 2 + (Hx - Hx2) ** 2 + (Hy + Hy2) ** 2
     sym = torch.mean(sym)
-    ic_pts = torch.cat([torch.zeros_like(ic_xy[:, :1]), ic_xy], dim=1)
-    f_ic = model.fields(ic_pts)
+    Ei, Hxi, Hyi = f[-1][:, :3].unbind(1)
     E0 = torch.exp(-desc.ic_a * (ic_xy[:, 0] ** 2 + ic_xy[:, 1] ** 2))
-    ic = torch.mean((f_ic[:, 0] - E0) ** 2 + f_ic[:, 1] ** 2 + f_ic[:, 2] ** 2)
+    ic = torch.mean((Ei - E0) ** 2 + Hxi ** 2 + Hyi ** 2)
     total = phys + desc.w_ic * ic + desc.w_sym * sym + desc.w_energy * energy
     return {"total": total, "phys": phys, "ic": ic, "sym": sym, "energy": energy}
 
