@@ -52,12 +52,21 @@ def executed_flops_per_point(n_fused: int, n: int, n_folded: int = 0) -> float:
     return (2 ** n) * (float(n_fused) * 216 - float(n_folded) * 168)
 
 
-def matrix_core_share(n_fused: int, n_folded: int = 0) -> float:
-    """Share of executed_flops_per_point done on the matrix cores: the 2x2 gate products (12 x 14
-    per amplitude per applied gate) run as v_mfma_f32_4x4x1f32, the gate statistics (48) on the
-    vector ALU."""
-    total = float(n_fused) * 216 - float(n_folded) * 168
-    return 168.0 * (n_fused - n_folded) / total if total > 0 else 0.0
+def layer_flops_per_point(n_fused: int, n: int, n_folded: int = 0) -> float:
+    """Flops the fused kernel's algorithm needs (mul = 1, fma = 2), per amplitude.  Applied gate: the
+    forward's 2x2 products on 4 statevectors (4 x 14) and the adjoint's real rotations on 8 (8 x 4); every
+    gate: S_x and S_y (4 pairs x 4 fma x 2 = 32).  Layer of n gates: the conjugate phase of 8
+    statevectors (8 x 6) and the diagonal products that give every S_z (4 x 4).  Smaller than
+    executed_flops_per_point, which counts 2x2 products both ways and three sums per gate."""
+    applied = float(n_fused - n_folded)
+    return (2 ** n) * (applied * (4 * 14 + 8 * 4) + float(n_fused) * 32 + applied / n * (8 * 6) + float(n_fused) / n * 16)
+
+
+def matrix_core_share(n_fused: int, n_folded: int = 0, n: int = 12) -> float:
+    """Share of layer_flops_per_point done on the matrix cores: the forward's 2x2 products (4 x 14 per
+    amplitude per applied gate) run as v_mfma_f32_4x4x1f32, the rest on the vector ALU."""
+    total = layer_flops_per_point(n_fused, n, n_folded)
+    return 56.0 * (2 ** n) * (n_fused - n_folded) / total if total > 0 else 0.0
 
 
 # Sources that determine each kernel's code and memory accesses (device code and the planner
@@ -256,9 +265,9 @@ def main():
         flops_mc = 0.0
         for w in ws_list:
             cq = Circuit(ctx, w.circuit)
-            fx = executed_flops_per_point(cq.info(3), w.circuit.n, cq.info(12)) * len(w.points)
+            fx = layer_flops_per_point(cq.info(3), w.circuit.n, cq.info(12)) * len(w.points)
             flops_x += fx
-            flops_mc += fx * matrix_core_share(cq.info(3), cq.info(12))
+            flops_mc += fx * matrix_core_share(cq.info(3), cq.info(12), w.circuit.n)
             cq.close()
         mc_share = flops_mc / flops_x if flops_x > 0 else 0.0
 
@@ -282,8 +291,8 @@ def main():
                 "grad": torch.empty(w.circuit.n_params, dtype=torch.float32, device=dev)}
         F = c.info(3)
         flops = flops_per_point(F, w.circuit.n) * P_total
-        flops_x = executed_flops_per_point(F, w.circuit.n, c.info(12)) * P_total
-        mc_share = matrix_core_share(F, c.info(12))
+        flops_x = layer_flops_per_point(F, w.circuit.n, c.info(12)) * P_total
+        mc_share = matrix_core_share(F, c.info(12), w.circuit.n)
 
         def step():
             c.maxwell(prm, pts, w.loss, bufs=bufs)
@@ -343,14 +352,13 @@ def main():
     ctx.use_stream(torch.cuda.current_stream(dev))   # the extra legs below run on torch's stream
     ctx.kernel_timing(False)
     kms_avg = float(np.mean(kms))
-    # the roofline's work is the arithmetic the kernel's algorithm needs (executed-flop count:
-    # mul = 1, fma = 2, three-component gate statistic, opening stage folded); the larger
-    # 256-flop-per-amplitude model of a gate-by-gate 2x2 product is reported beside it
+    # the roofline's work is the arithmetic the kernel's algorithm needs (layer_flops_per_point); the
+    # larger 256-flop-per-amplitude model of a gate-by-gate 2x2 product is reported beside it
     achieved = flops_x / (kms_avg / 1e3) / 1e12
     kname = "k_fused" if k != 3 else "k_batch"
     traffic, traffic_src = recorded_traffic(kname, cfg["workload"])
-    # FP32 compute-bound: most of the arithmetic runs on the matrix cores (the gate products), the
-    # rest (gate statistics) on the vector ALU; both units' FP32 peak is 157.3 TFLOP/s
+    # FP32 compute-bound: the forward's gate products run on the matrix cores, the adjoint on the vector
+    # ALU; both share one FP32 pipe, whose peak is 157.3 TFLOP/s
     roofline = {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
                 "kernel": kname, "kernel_ms": round(kms_avg, 4),

@@ -54,8 +54,6 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
     b->P.push_back(P[i]);
     int& mc = c->hp.n >= kBatchBig ? b->max_cols_big : b->max_cols;
     mc = std::max(mc, (int)c->hp.fused.size() * kGS + n_moments(c));
-    if ((int)c->hp.sweeps.size() > kMaxSweeps)
-      return cleanup(fail(ctx, QP_EUNSUPPORTED, "qp_batch_compile: circuit %d has too many layers", i));
     if (c->hp.enc_kind == QP_ENC_RFF) b->rff_circs.push_back(i);
   }
   if ((b->max_cols > 0 && batch_lds_bytes(3, b->max_cols) > 160 * 1024) ||

@@ -423,8 +423,6 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   char* w = static_cast<char*>(ws);
   int* counts = reinterpret_cast<int*>(w + L.counts);
   const int NM = n_moments(c);
-  const int layers = (int)c->hp.sweeps.size();
-  if (layers > kMaxSweeps) return hipcheck(ctx, hipErrorInvalidValue, "fused kernel");
   const SweepTabs tabs = sweep_tabs(c, w + L.tabs);
   hipError_t e = launch_sweep_tables(sweep_plan(c), NM > 0, params, tabs,
                                      (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st);

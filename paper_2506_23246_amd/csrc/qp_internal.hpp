@@ -159,7 +159,6 @@ QP_HD inline constexpr uint32_t sweep_xor(int k) { return k == 2 ? 7u : 1u << k;
 QP_HD inline constexpr int sweep_planes(int n, int exs, bool two) { return n >= 10 ? exs : (two ? 2 : 1); }
 constexpr int kTC = 16;            // floats per layer of the coefficient table (kPos used)
 constexpr int kGP = 4;             // doubles per gate: cos c, sin c, scale of S_x and S_y, scale of S_z (sign: X mask)
-constexpr int kMaxSweeps = 4096;   // layers the table kernel can scan
 
 // Phase stage: a run of CRZ gates (with any CZ of the same stage), all diagonal, applied as one
 // phase e^{i phi(j)} per basis index after the exchange that precedes a round.  With

@@ -106,6 +106,7 @@ __device__ inline Zyz zyz_split(const double* u) {
 }
 
 constexpr int kTabThreads = 256;
+constexpr int kFlipLayers = 1024;   // layers whose flips the table kernel holds at a time
 
 // Block blk of a circuit's tables (kTabThreads threads; all of them call this).  What bounds it is
 // latency: dependent loads, barriers, and code run once from a cold instruction cache.  So everything
@@ -113,7 +114,7 @@ constexpr int kTabThreads = 256;
 // layer's rotations are written by another wave than the first entries.
 __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict__ params, const SweepTabs& T, int blk,
                                     int fp32) {
-  __shared__ uint32_t flips[kMaxSweeps];
+  __shared__ uint32_t flips[kFlipLayers];
   __shared__ double2 s_c[kMaxQubits], s_a[kMaxQubits];   // by the qubit's index bit, as the three below
   __shared__ double s_cos[kMaxQubits], s_t[kMaxQubits];
   __shared__ int s_flip[kMaxQubits];
@@ -176,60 +177,70 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
 #pragma unroll
     for (int b = 0; b < kMaxQubits; ++b)
       if (b < n) joi |= ((uint32_t)__popc(L->arow[b] & ji) & 1u) << b;
-  for (int k = l + tid; k < S; k += kTabThreads) flips[k] = 0;
   if (tid < kMaxQubits) {
     s_c[tid] = s_a[tid] = make_double2(1.0, 0.0);
     s_t[tid] = 0.0; s_cos[tid] = 1.0; s_flip[tid] = 0;
   }
-  // flips from layer l on; layer l's gates, and those before it (sincospi: no long argument reduction, and
-  // good to FP64 rounding all the same)
-  for (int f0 = 0; f0 < F; f0 += kGates) {
-    const int f = f0 + tid, fr = f0 + tid / 3;
-    if (f0) {
-      fu = fused[f < F ? f : 0];
-      nc = fused[fr < F ? fr : 0].ncomp, pi = fused[fr < F ? fr : 0].param[rc];
-      th = params[rc < nc ? pi : 0];
-    }
-    if (tid < 3 * kGates && fr < F) {
-      double sn, cn;
-      if (fp32) {
-        float sf, cf;
-        sincosf(0.5f * th, &sf, &cf);
-        sn = sf; cn = cf;
-      } else {
-        sincospi(0.5 * 0.31830988618379067154 * (double)th, &sn, &cn);
+  // Flips from layer l on, kFlipLayers layers at a time from the last one back; layer l's gates, and those
+  // before it (sincospi: no long argument reduction, and good to FP64 rounding all the same).
+  uint32_t x = 0;      // the X mask, carried back from the readout through the index maps (first wave)
+  int hi = S;
+  do {
+    const int lo = hi - kFlipLayers > l ? hi - kFlipLayers : l;
+    for (int k = lo + tid; k < hi; k += kTabThreads) flips[k - lo] = 0;
+    if (F == 0) __syncthreads();
+    for (int f0 = 0; f0 < F; f0 += kGates) {
+      const int f = f0 + tid, fr = f0 + tid / 3;
+      if (f0 || hi < S) {
+        fu = fused[f < F ? f : 0];
+        nc = fused[fr < F ? fr : 0].ncomp, pi = fused[fr < F ? fr : 0].param[rc];
+        th = params[rc < nc ? pi : 0];
       }
-      s_trig[tid] = make_double2(cn, sn);
-    }
-    __syncthreads();
-    if (tid < kGates && f < F && !fu.head && fu.layer >= l - 1) {
-      double u[8];
-      set_identity(u);
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        if (k < fu.ncomp) left_mul_rot<double>(fu.kind[k], s_trig[3 * tid + k].x, s_trig[3 * tid + k].y, u);
-      const int b = n - 1 - fu.qubit, flip = zyz_flip(u);
-      if (fu.layer >= l && flip) atomicOr(&flips[fu.layer], 1u << b);
-      if (fu.layer <= l) {
-        const Zyz z = zyz_split(u);
-        if (fu.layer == l) { s_c[b] = z.c; s_cos[b] = z.cosb; s_t[b] = z.t; }
-        else { s_a[b] = z.a; s_flip[b] = flip; }
+      if (tid < 3 * kGates && fr < F) {
+        double sn, cn;
+        if (fp32) {
+          float sf, cf;
+          sincosf(0.5f * th, &sf, &cf);
+          sn = sf; cn = cf;
+        } else {
+          sincospi(0.5 * 0.31830988618379067154 * (double)th, &sn, &cn);
+        }
+        s_trig[tid] = make_double2(cn, sn);
       }
-    }
-    __syncthreads();
-  }
-  if (F == 0) __syncthreads();
-  if (tid < 64) {   // layer l's X mask, carried back from the readout through the index maps (ballots of row parities)
-    uint32_t x = 0;
-    auto step = [&](int k, uint32_t row) {
-      x ^= __builtin_amdgcn_readfirstlane(flips[k]);
-      if (k > l) x = (uint32_t)__ballot((int)(__popc(x & row) & 1u));
-    };
+      __syncthreads();
+      if (tid < kGates && f < F && !fu.head && fu.layer >= l - 1) {
+        double u[8];
+        set_identity(u);
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i)
-      if (S - 1 - i >= l) step(S - 1 - i, ahead[i]);
+        for (int k = 0; k < 3; ++k)
+          if (k < fu.ncomp) left_mul_rot<double>(fu.kind[k], s_trig[3 * tid + k].x, s_trig[3 * tid + k].y, u);
+        const int b = n - 1 - fu.qubit, flip = zyz_flip(u);
+        if (fu.layer >= lo && fu.layer < hi && flip) atomicOr(&flips[fu.layer - lo], 1u << b);
+        if (fu.layer <= l) {
+          const Zyz z = zyz_split(u);
+          if (fu.layer == l) { s_c[b] = z.c; s_cos[b] = z.cosb; s_t[b] = z.t; }
+          else { s_a[b] = z.a; s_flip[b] = flip; }
+        }
+      }
+      __syncthreads();
+    }
+    if (tid < 64) {   // (ballots of row parities)
+      auto step = [&](int k, uint32_t row) {
+        x ^= __builtin_amdgcn_readfirstlane(flips[k - lo]);
+        if (k > l) x = (uint32_t)__ballot((int)(__popc(x & row) & 1u));
+      };
+      if (hi == S) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+          if (S - 1 - i >= lo) step(S - 1 - i, ahead[i]);
+      }
 #pragma unroll 1
-    for (int k = S - 1 - kAhead; k >= l; --k) step(k, row_of(k));
+      for (int k = hi == S ? S - 1 - kAhead : hi - 1; k >= lo; --k) step(k, row_of(k));
+    }
+    hi = lo;
+    if (hi > l) __syncthreads();   // the flips are read
+  } while (hi > l);
+  if (tid < 64) {
     const uint32_t xo = l < S ? (uint32_t)__ballot((int)(__popc(x & row_l) & 1u)) : x;   // before the index map
     if (tid == 0) {
       s_x = x;
@@ -241,7 +252,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
 #pragma unroll
   for (int b = 0; b < kMaxQubits; ++b) mag *= s_cos[b];
   __syncthreads();
-  const uint32_t x = s_x;
+  x = s_x;
   if (l == L0 && chunk == 0 && L0 > 0) {   // the opening layer: nothing is pulled back
     if (tid < kTC) T.tcoef[tid] = 0.f;
     if (tid == 0) { T.xmask[0] = s_xo; T.lscale[0] = 1.0; }
