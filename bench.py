@@ -359,7 +359,7 @@ def main():
     traffic, traffic_src = recorded_traffic(kname, cfg["workload"])
     # FP32 compute-bound: the forward's gate products run on the matrix cores, the adjoint on the vector
     # ALU; both share one FP32 pipe, whose peak is 157.3 TFLOP/s
-    roofline = {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
+    roofline = {"bound": "valu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
                 "kernel": kname, "kernel_ms": round(kms_avg, 4),
                 "algorithmic_flops_per_launch": flops_x, "matrix_core_flop_share": round(mc_share, 3),

@@ -111,7 +111,8 @@ constexpr int kFlipLayers = 1024;   // layers whose flips the table kernel holds
 // Block blk of a circuit's tables (kTabThreads threads; all of them call this).  What bounds it is
 // latency: dependent loads, barriers, and code run once from a cold instruction cache.  So everything
 // that comes from the plan is fetched before anything is formed, uniform data by scalar loads, and the
-// layer's rotations are written by another wave than the first entries.
+// layer's rotations are written by another wave than the first entries (4 qubits, 2 layers: 6.8 -> 5.1 us;
+// the bare gate matrices take 2.8).
 __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict__ params, const SweepTabs& T, int blk,
                                     int fp32) {
   __shared__ uint32_t flips[kFlipLayers];
