@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <type_traits>
 
 #include "const_dev.hpp"
 #include "fused.hpp"
@@ -185,14 +186,14 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   // Flips from layer l on, kFlipLayers layers at a time from the last one back; layer l's gates, and those
   // before it (sincospi: no long argument reduction, and good to FP64 rounding all the same).
   uint32_t x = 0;      // the X mask, carried back from the readout through the index maps (first wave)
-  int hi = S;
-  do {
+  auto pass = [&](int hi, auto first) {
+    constexpr bool FIRST = decltype(first)::value;   // (its gates and rows are fetched already)
     const int lo = hi - kFlipLayers > l ? hi - kFlipLayers : l;
     for (int k = lo + tid; k < hi; k += kTabThreads) flips[k - lo] = 0;
     if (F == 0) __syncthreads();
     for (int f0 = 0; f0 < F; f0 += kGates) {
       const int f = f0 + tid, fr = f0 + tid / 3;
-      if (f0 || hi < S) {
+      if (f0 || !FIRST) {
         fu = fused[f < F ? f : 0];
         nc = fused[fr < F ? fr : 0].ncomp, pi = fused[fr < F ? fr : 0].param[rc];
         th = params[rc < nc ? pi : 0];
@@ -230,17 +231,20 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
         x ^= __builtin_amdgcn_readfirstlane(flips[k - lo]);
         if (k > l) x = (uint32_t)__ballot((int)(__popc(x & row) & 1u));
       };
-      if (hi == S) {
+      if constexpr (FIRST) {
 #pragma unroll
         for (int i = 0; i < kAhead; ++i)
           if (S - 1 - i >= lo) step(S - 1 - i, ahead[i]);
       }
 #pragma unroll 1
-      for (int k = hi == S ? S - 1 - kAhead : hi - 1; k >= lo; --k) step(k, row_of(k));
+      for (int k = FIRST ? S - 1 - kAhead : hi - 1; k >= lo; --k) step(k, row_of(k));
     }
-    hi = lo;
-    if (hi > l) __syncthreads();   // the flips are read
-  } while (hi > l);
+    return lo;
+  };
+  for (int hi = pass(S, std::true_type{}); hi > l;) {
+    __syncthreads();   // the flips are read
+    hi = pass(hi, std::false_type{});
+  }
   if (tid < 64) {
     const uint32_t xo = l < S ? (uint32_t)__ballot((int)(__popc(x & row_l) & 1u)) : x;   // before the index map
     if (tid == 0) {
