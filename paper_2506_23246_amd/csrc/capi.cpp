@@ -413,7 +413,7 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
                         const float* angles, const float* jac, int64_t P, const qp_maxwell_desc* ld, float* out,
                         float* tan, const float* d_out, const float* d_tan, double* loss, float* d_params,
                         float* d_angles, float* d_jac, void* ws, uint32_t flags, int exs_override, int grid_override,
-                        const float* f_mir, int n_mir, float w_sym, float w_energy) {
+                        const float* f_mir, int n_mir, float w_sym, float w_energy, bool tabs_formed) {
   hipSetDevice(ctx->device);
   hipStream_t st = ctx->stream;
   const int n = c->hp.n;
@@ -424,8 +424,9 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   int* counts = reinterpret_cast<int*>(w + L.counts);
   const int NM = n_moments(c);
   const SweepTabs tabs = sweep_tabs(c, w + L.tabs);
-  hipError_t e = launch_sweep_tables(sweep_plan(c), NM > 0, params, tabs,
-                                     (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st);
+  hipError_t e = hipSuccess;
+  if (!tabs_formed)
+    e = launch_sweep_tables(sweep_plan(c), NM > 0, params, tabs, (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st);
   if (e != hipSuccess) return hipcheck(ctx, e, "gate table");
   const float* ang = angles;
   const float* jc = jac;
@@ -722,6 +723,10 @@ extern "C" qp_status qp_total_loss(qp_ctx* ctx, const qp_circuit* c, const float
   const int64_t P_rest = L.P_ext - P;
   const int m = c->hp.m;
   qp_status s = QP_OK;
+  // the three evaluations share the tables the first one forms, where their layouts put them at one place
+  // (7 qubits, 64000 points: 921 -> 911 us)
+  auto tabs_at = [&](int64_t points_of) { return fused_layout(c, points_of, ctx->cu_count * 4).tabs; };
+  const bool shared = P > 0 && P_rest > 0 && tabs_at(P) == tabs_at(P_rest);
   if (P_rest > 0 && (s = run_fused(ctx, c, kModeFieldsPk, params, ext + 3 * P, nullptr, nullptr, P_rest, nullptr,
                                    fo + (size_t)m * P, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                    fws, gflags, 0, 0)) != QP_OK)
@@ -732,7 +737,7 @@ extern "C" qp_status qp_total_loss(qp_ctx* ctx, const qp_circuit* c, const float
   if ((P > 0 || P_rest == 0) &&
       (s = run_fused(ctx, c, kModeTotal, params, ext, nullptr, nullptr, P, &d->phys, fo, fg, nullptr, nullptr, nullptr,
                      c->hp.K > 0 ? d_params : nullptr, nullptr, nullptr, fws, gflags, 0, 0, fo + (size_t)m * P,
-                     L.with_mx ? 2 : 1, d->w_sym, d->w_energy)) != QP_OK)
+                     L.with_mx ? 2 : 1, d->w_sym, d->w_energy, shared)) != QP_OK)
     return s;
   // 3. The four terms, and the seeds of the mirrored and initial-condition points (the kernel also
   //    writes the collocation points' seeds, which step 2 formed itself and nothing reads).
@@ -758,7 +763,7 @@ extern "C" qp_status qp_total_loss(qp_ctx* ctx, const qp_circuit* c, const float
   if (P_rest > 0 &&
       (s = run_fused(ctx, c, kModeVjpPk, params, ext + 3 * P, nullptr, nullptr, P_rest, nullptr, nullptr, nullptr,
                      dout + (size_t)m * P, nullptr, nullptr, two ? dtmp : d_params, nullptr, nullptr, fws, gflags, 0,
-                     0)) != QP_OK)
+                     0, nullptr, 0, 0.f, 0.f, shared || P == 0)) != QP_OK)
     return s;
   if (two && (e = launch_add(d_params, dtmp, c->hp.K, st)) != hipSuccess) return hipcheck(ctx, e, "gradient sum");
   return QP_OK;
