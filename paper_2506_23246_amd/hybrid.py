@@ -24,6 +24,9 @@ import math
 
 import torch
 from torch import nn
+from torch.nn.modules.module import _has_any_global_hook
+from torch.overrides import _get_current_function_mode_stack
+from torch.utils._device import DeviceContext
 
 from .api import Circuit, Context
 from .autograd import qcircuit_angles
@@ -65,6 +68,16 @@ def scale_derivative(kind: int, a: torch.Tensor):
     return r if kind == SCALE_ASIN else -r
 
 
+_FORWARD = {nn.Linear: nn.Linear.forward}
+
+
+def _as_defined(mod: nn.Module, cls) -> bool:
+    """mod computes what cls defines: no subclass, no forward set on the instance (as adapters and offloading
+    wrappers do) or into the class, no hooks."""
+    return (type(mod) is cls and "forward" not in vars(mod) and cls.forward is _FORWARD[cls]
+            and not (mod._forward_hooks or mod._forward_pre_hooks or mod._backward_hooks or mod._backward_pre_hooks))
+
+
 class QuantumLayer(nn.Module):
     """Angle embedding + ansatz + Pauli-Z readout on the circuit engine.
 
@@ -88,6 +101,9 @@ class QuantumLayer(nn.Module):
         if self._fn is not None:      # another implementation of the same layer (a reference)
             return self._fn(self.params, theta, jac)
         return qcircuit_angles(self.params, theta.float().contiguous(), jac.float().contiguous(), self._circ)
+
+
+_FORWARD[QuantumLayer] = QuantumLayer.forward
 
 
 class HybridQPINN(nn.Module):
@@ -114,11 +130,22 @@ class HybridQPINN(nn.Module):
         return scale_angles(self.scale, h)
 
     def plain_network(self) -> bool:
-        """The classical part is the one defined here: nothing overridden, replaced or hooked."""
-        t = type(self)
+        """The classical part is the one defined here, nothing overridden, replaced, patched or hooked, and
+        computes in 32 or 64 bits: angles_jacobian, which repeats its formulas, then differentiates what
+        angles() computes, no less precisely than autograd would."""
+        t, dt = type(self), self.B.dtype
         return (t.angles is HybridQPINN.angles and t.fields is HybridQPINN.fields
-                and all(type(l) is nn.Linear and not (l._forward_hooks or l._forward_pre_hooks or l._backward_hooks
-                                                      or l._backward_pre_hooks) for l in self.layers))
+                and not {"angles", "fields", "angles_jacobian"} & vars(self).keys()
+                and not _has_any_global_hook()
+                and all(type(m) is DeviceContext for m in _get_current_function_mode_stack())
+                and dt in (torch.float32, torch.float64) and not torch.is_autocast_enabled(self.B.device.type)
+                and all(_as_defined(l, nn.Linear) and type(l.weight) in (nn.Parameter, torch.Tensor)
+                        and l.weight.dtype == dt for l in self.layers))
+
+    def plain_model(self) -> bool:
+        """plain_network, and the circuit and the head as defined here too: fields() maps point by point, and
+        nobody sees how many points a call has."""
+        return self.plain_network() and _as_defined(self.quantum, QuantumLayer) and _as_defined(self.head, nn.Linear)
 
     def angles_jacobian(self, x):
         """angles(x) and its Jacobian [P, n, 3], the three tangents carried forward with the activations.

@@ -89,7 +89,7 @@ def hybrid_total_loss(model: HybridQPINN, points: torch.Tensor, ic_xy: torch.Ten
         at.append(mx)
     at.append(torch.cat([torch.zeros_like(ic_xy[:, :1]), ic_xy], dim=1))
     # the fields away from the collocation points in one evaluation, where the model is a map point by point
-    plain = getattr(model, "plain_network", None)
+    plain = getattr(model, "plain_model", None)
     if plain is not None and plain():
         f = torch.split(model.fields(torch.cat(at)), [len(p) for p in at])
     else:
