@@ -42,7 +42,9 @@ __device__ __forceinline__ void pin_vgpr(V& v) { asm volatile("" : "+v"(v)); }
 // permutation as a move of its own (half the rate, and a register for every moved value: the Maxwell
 // kernels spilled 700 and 1400 registers).  A VALU result may be read through DPP, or by a permlane
 // swap, two wait states after it was written; the compiler does not see into the blocks, so each one
-// starts (and, where it writes what a swap may read, ends) with that wait.
+// starts (and, where it writes what a swap may read, ends) with that wait.  What a block writes is marked
+// early-clobber: it is written before the last input is read, and an input that the compiler knows to hold
+// the same value would else be given the same register.
 #define QP_DPP_0 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
 #define QP_DPP_1 " quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
 #define QP_DPP_2 " row_half_mirror row_mask:0xf bank_mask:0xf\n"
@@ -75,9 +77,9 @@ __device__ __forceinline__ void rot_reg(float (&sr)[8][8], float (&si)[8][8], fl
       "v_fmac_f32_dpp %9, %9, %16" D "v_fmac_f32_dpp %10, %10, %16" D "v_fmac_f32_dpp %11, %11, %16" D         \
       "v_fmac_f32_dpp %12, %12, %16" D "v_fmac_f32_dpp %13, %13, %16" D "v_fmac_f32_dpp %14, %14, %16" D       \
       "v_fmac_f32_dpp %15, %15, %16" D "s_nop 1"                                                              \
-      : "+v"(sr[S][0]), "+v"(sr[S][1]), "+v"(sr[S][2]), "+v"(sr[S][3]), "+v"(sr[S][4]), "+v"(sr[S][5]),        \
-        "+v"(sr[S][6]), "+v"(sr[S][7]), "+v"(si[S][0]), "+v"(si[S][1]), "+v"(si[S][2]), "+v"(si[S][3]),        \
-        "+v"(si[S][4]), "+v"(si[S][5]), "+v"(si[S][6]), "+v"(si[S][7])                                        \
+      : "+&v"(sr[S][0]), "+&v"(sr[S][1]), "+&v"(sr[S][2]), "+&v"(sr[S][3]), "+&v"(sr[S][4]), "+&v"(sr[S][5]), \
+        "+&v"(sr[S][6]), "+&v"(sr[S][7]), "+&v"(si[S][0]), "+&v"(si[S][1]), "+&v"(si[S][2]), "+&v"(si[S][3]), \
+        "+&v"(si[S][4]), "+&v"(si[S][5]), "+&v"(si[S][6]), "+&v"(si[S][7]) \
       : "v"(ts))
 template <int K, int S>
 __device__ __forceinline__ void rot_lane(float (&sr)[8][8], float (&si)[8][8], float ts) {
@@ -120,7 +122,7 @@ __device__ __forceinline__ void stat_reg(const float (&sr)[8][8], const float (&
       "v_fmac_f32_dpp %2, %11, %15" D "v_fmac_f32_dpp %3, %7, %15" D                                           \
       "v_fmac_f32_dpp %0, -%6, %18" D "v_fmac_f32_dpp %1, %10, %18" D                                          \
       "v_fmac_f32_dpp %2, -%7, %19" D "v_fmac_f32_dpp %3, %11, %19" D                                          \
-      : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1)                                                                \
+      : "+&v"(a0), "+&v"(b0), "+&v"(a1), "+&v"(b1) \
       : "v"(sr[C][R]), "v"(sr[C][R + 1]), "v"(sr[C][R + 2]), "v"(sr[C][R + 3]), "v"(si[C][R]),                 \
         "v"(si[C][R + 1]), "v"(si[C][R + 2]), "v"(si[C][R + 3]), "v"(sr[X][R]), "v"(sr[X][R + 1]),     \
         "v"(sr[X][R + 2]), "v"(sr[X][R + 3]), "v"(si[X][R]), "v"(si[X][R + 1]),                \
