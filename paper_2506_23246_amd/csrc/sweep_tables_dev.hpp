@@ -28,6 +28,25 @@ __device__ inline void fused_product(const QFused& fu, const float* __restrict__
   }
 }
 
+// Half angles in FP64.  sincospi of theta / (2 pi) needs no long argument reduction, but the rounding of that
+// product grows with theta: up to 2^20 it is below 2^-33 turns, 2^-9 of an FP32 rounding; beyond, sincos's
+// exact reduction.  (The rounds' matrices come from sincos: adjoint and forward have to be of one circuit.)
+constexpr double kInv2Pi = 0.15915494309189533577;
+__device__ __forceinline__ bool long_angle(float theta) { return !(fabsf(theta) <= 1048576.f); }
+__device__ __forceinline__ void half_angle(float theta, double* s, double* c) {
+  if (__builtin_expect(long_angle(theta), 0)) sincos(0.5 * (double)theta, s, c);
+  else sincospi(kInv2Pi * (double)theta, s, c);
+}
+// theta / (2 pi), less a multiple of 2 (theta / 2 less whole turns) for a long angle.
+__device__ __forceinline__ double turns_of(float theta) {
+  if (__builtin_expect(long_angle(theta), 0)) {
+    double s, c;
+    sincos(0.5 * (double)theta, &s, &c);
+    return 2.0 * kInv2Pi * atan2(s, c);
+  }
+  return kInv2Pi * (double)theta;
+}
+
 // The matrix of gate f for the rounds and the encoding, formed in FP64 and rounded once (fp32: in FP32,
 // kept for comparison); f = n_fused: the identity (absent gates of a round).
 __device__ inline void gate_entry(const QPlanDev* __restrict__ plan, const float* __restrict__ params, int f, int fp32,
@@ -68,13 +87,12 @@ __device__ inline void phase_entry(const QPlanDev* __restrict__ plan, const floa
     qb = qa + 1 + r;
   }
   double turns = 0.0;
-  const double inv2pi = 0.15915494309189533577;
   for (int g = 0; g < st.ngates; ++g) {
-    const double th = (double)params[gates[g].param];
+    const double th = turns_of(params[gates[g].param]);
     if (qb < 0) {
-      if (gates[g].c == qa) turns -= 0.5 * th * inv2pi;
+      if (gates[g].c == qa) turns -= 0.5 * th;
     } else if ((gates[g].c == qa && gates[g].t == qb) || (gates[g].c == qb && gates[g].t == qa)) {
-      turns += th * inv2pi;
+      turns += th;
     }
   }
   const double frac = turns - floor(turns);                 // [0, 1)
@@ -184,7 +202,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
     s_t[tid] = 0.0; s_cos[tid] = 1.0; s_flip[tid] = 0;
   }
   // Flips from layer l on, kFlipLayers layers at a time from the last one back; layer l's gates, and those
-  // before it (sincospi: no long argument reduction, and good to FP64 rounding all the same).
+  // before it.
   uint32_t x = 0;      // the X mask, carried back from the readout through the index maps (first wave)
   auto pass = [&](int hi, auto first) {
     constexpr bool FIRST = decltype(first)::value;   // (its gates and rows are fetched already)
@@ -205,7 +223,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
           sincosf(0.5f * th, &sf, &cf);
           sn = sf; cn = cf;
         } else {
-          sincospi(0.5 * 0.31830988618379067154 * (double)th, &sn, &cn);
+          half_angle(th, &sn, &cn);
         }
         s_trig[tid] = make_double2(cn, sn);
       }
@@ -313,7 +331,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
       double turn = 0.0;   // in units of pi
       for (int g = 0; g < st->ngates; ++g)
         if ((j >> (n - 1 - pg[g].c)) & 1u) {
-          const double th = 0.5 * 0.31830988618379067154 * (double)params[pg[g].param];
+          const double th = turns_of(params[pg[g].param]);
           turn += ((j >> (n - 1 - pg[g].t)) & 1u) ? th : -th;
         }
       double2 e;
