@@ -145,8 +145,9 @@ void qp_circuit_destroy(qp_circuit* c);
  *       8 LDS exchange planes, 9 persistent workgroups per CU, 10 dense 2^5 blocks,
  *       11 leading rounds folded into the encoding (an opening rotation stage acts on the
  *       product state), 12 fused gates in those rounds, 13 fusion width chosen by the tuner
- *       for Maxwell calls (1: dense 32x32 blocks, 0: 2x2 gates in the fused kernel).  -1 for
- *       an unknown code.                                                                     */
+ *       for Maxwell calls (1: dense 32x32 blocks, 0: 2x2 gates in the fused kernel), 14 bytes
+ *       of the layers' tables within qp_workspace_bytes (the same for every P).  -1 for an
+ *       unknown code.                                                                        */
 int64_t qp_circuit_info(const qp_circuit* c, int32_t what);
 
 /* Launch shape of the fused kernel for this circuit (what the autotuner sets): exchange_planes
@@ -275,15 +276,18 @@ qp_status qp_energy_profile(qp_ctx* ctx, const qp_circuit* c, const float* param
  * For callers that cannot allocate device memory or pass a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, checks and
  * results as qp_maxwell_fused minus the workspace: the per-call scratch (gate table, dielectric
- * counts, random-Fourier-feature angles, per-workgroup partials, FP64 reductions) lives in a
- * fixed device array of QP_NOALLOC_SCRATCH_BYTES inside the library, one copy per device, held
- * until the process ends.  Nothing in it needs to start at zero: every call writes what it reads.
- * Errors: QP_EWORKSPACE when the call needs more scratch than the array holds
- * (qp_workspace_bytes(c, P, 0) > QP_NOALLOC_SCRATCH_BYTES; only random-Fourier-feature circuits
- * grow with P, by 16 n bytes per point), QP_EUNSUPPORTED with QP_FLAG_TUNE or QP_FLAG_DENSE_MFMA
- * (they need a caller workspace), otherwise as qp_maxwell_fused.  All calls on one device share
- * the array: calls that overlap on one device (several streams or threads) race and must be
- * serialised by the caller.  qp_noalloc_scratch_bytes() returns the array size.            */
+ * counts, random-Fourier-feature angles, per-workgroup partials, FP64 reductions, the layers'
+ * tables) lives in a fixed device array inside the library, one copy per device, held until the
+ * process ends.  Nothing in it needs to start at zero: every call writes what it reads.
+ * The array has QP_NOALLOC_SCRATCH_BYTES for all but the tables, and 32 MiB for these, more than
+ * any circuit's that the rest has room for and the fused kernels run (25 MiB).  Errors:
+ * QP_EWORKSPACE when the call needs more scratch than that,
+ *   qp_workspace_bytes(c, P, 0) - qp_circuit_info(c, 14) > QP_NOALLOC_SCRATCH_BYTES
+ * (only random-Fourier-feature circuits grow with P, by 16 n bytes per point), QP_EUNSUPPORTED
+ * with QP_FLAG_TUNE or QP_FLAG_DENSE_MFMA (they need a caller workspace), otherwise as
+ * qp_maxwell_fused.  All calls on one device share the array: calls that overlap on one device
+ * (several streams or threads) race and must be serialised by the caller.
+ * qp_noalloc_scratch_bytes() returns QP_NOALLOC_SCRATCH_BYTES.                              */
 #define QP_NOALLOC_SCRATCH_BYTES (16u << 20)
 size_t qp_noalloc_scratch_bytes(void);
 qp_status qp_maxwell_fused_noalloc(qp_ctx* ctx, const qp_circuit* c, const float* params,

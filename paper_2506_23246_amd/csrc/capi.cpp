@@ -206,6 +206,7 @@ extern "C" int64_t qp_circuit_info(const qp_circuit* c, int32_t what) {
       return h;
     }
     case 13: return c->use_dense ? 1 : 0;
+    case 14: return c->hp.fused_ok ? (int64_t)layer_tab_bytes(c) : 0;
     default: return -1;
   }
 }
@@ -264,6 +265,10 @@ TabLayout tab_layout(const qp_circuit* c) {
 }  // namespace
 
 size_t qp::sweep_tab_bytes(const qp_circuit* c) { return tab_layout(c).total; }
+size_t qp::layer_tab_bytes(const qp_circuit* c) {
+  const TabLayout L = tab_layout(c);
+  return L.total - L.tcoef;
+}
 
 SweepTabs qp::sweep_tabs(const qp_circuit* c, void* base) {
   const TabLayout L = tab_layout(c);

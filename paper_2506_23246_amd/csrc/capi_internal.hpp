@@ -45,8 +45,10 @@ qp_status hipcheck(qp_ctx* c, hipError_t e, const char* what);
 void choose_launch(qp_ctx* ctx, qp_circuit* c);
 int fused_grid(const qp_ctx* ctx, const qp_circuit* c, int64_t P);
 WsLayout fused_layout(const qp_circuit* c, int64_t P, int grid_cap);
-// Tables of the sweep layers: bytes, and their pointers in a 256-byte aligned buffer.
+// Tables of the sweep layers: bytes (with and without the rounds' gate matrices and phase coefficients),
+// and their pointers in a 256-byte aligned buffer.
 size_t sweep_tab_bytes(const qp_circuit* c);
+size_t layer_tab_bytes(const qp_circuit* c);
 SweepTabs sweep_tabs(const qp_circuit* c, void* base);
 SweepPlan sweep_plan(const qp_circuit* c);
 int n_moments(const qp_circuit* c);   // phase-stage moments of the fused adjoint (0 without CRZ)

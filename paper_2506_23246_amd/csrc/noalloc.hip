@@ -17,9 +17,8 @@ namespace {
 
 static_assert(QP_NOALLOC_SCRATCH_BYTES % 256 == 0, "scratch size must keep 256-byte alignment");
 
-// The tables of the sweep layers lie behind the rest of a call's scratch and are counted apart:
-// 2^n entries of 8 bytes per layer, 24 MiB for the most layers whose statistics fit the LDS and the
-// fixed scratch (744 at 12 qubits).
+// The layers' tables are counted apart from the rest of a call's scratch: 2^n entries of 8 bytes per
+// layer, 25 MiB for the most layers whose statistics fit the LDS (758 at 12 qubits).
 constexpr size_t kTableBytes = 32u << 20;
 __device__ __align__(256) unsigned char scratch[QP_NOALLOC_SCRATCH_BYTES + kTableBytes];
 
@@ -56,10 +55,13 @@ extern "C" qp_status qp_maxwell_fused_noalloc(qp_ctx* ctx, const qp_circuit* c, 
   if (P < 0) return qp::fail(ctx, QP_EINVAL, "%s: P < 0", who);
   if (ctx->device < 0 || ctx->device >= qp::kMaxDevices)
     return qp::fail(ctx, QP_EUNSUPPORTED, "%s: device index %d out of range", who, ctx->device);
-  const size_t tables = qp::sweep_tab_bytes(c), need = qp::ws_required(c, P, 0) - tables;
-  if (need > QP_NOALLOC_SCRATCH_BYTES || tables > kTableBytes)
+  const size_t tables = qp::layer_tab_bytes(c), need = qp::ws_required(c, P, 0) - tables;
+  if (need > QP_NOALLOC_SCRATCH_BYTES)
     return qp::fail(ctx, QP_EWORKSPACE, "%s: this call needs %zu scratch bytes, above the fixed %zu; use qp_maxwell_fused "
                     "with a workspace or split the points", who, need, (size_t)QP_NOALLOC_SCRATCH_BYTES);
+  if (tables > kTableBytes)
+    return qp::fail(ctx, QP_EWORKSPACE, "%s: the tables of this circuit's layers need %zu scratch bytes, above the fixed "
+                    "%zu; use qp_maxwell_fused with a workspace", who, tables, kTableBytes);
   hipError_t e = hipSetDevice(ctx->device);
   void* ws = nullptr;
   if (e == hipSuccess) e = scratch_address(ctx->device, &ws);
