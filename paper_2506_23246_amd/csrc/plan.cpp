@@ -191,38 +191,45 @@ bool gf2_invertible(const uint32_t* cols, int n) {
   return gf2_inverse(cols, n, inv);
 }
 
+// What one side of an exchange contributes to a lane's index, by lane bit of a group of 16: the thread's index
+// bits where they come from u (J, linear in u), else its point's base.
+struct LaneBasis {
+  uint32_t j[4];
+  template <typename Fn>
+  LaneBasis(int n, const Fn& J) {
+    for (int k = 0; k < 4; ++k) j[k] = k < n - 3 ? J(1u << k) : 1u << (n + k - (n - 3));
+  }
+};
+
 // Sum and minimum over the 16-lane groups of a workgroup of the number of distinct banks (low four
-// bits of the entry), writer side and reader side.
-void bank_score(int n, int T, const uint32_t* M, const std::vector<uint32_t>& wj,
-                const std::vector<uint32_t>& rj, int* minv, int* sum) {
-  const int TP = 1 << (n - 3);
+// bits of the entry), writer side and reader side.  A lane's bank is linear over GF(2) in its lane bits
+// and the rest of its index adds a constant to the group, so every group has as many as the four lane
+// bits' banks span.  (Counted lane by lane, as a map is tried up to 400 times per exchange, the count was
+// most of what compiling a circuit took: 8 layers with CNOT rings, 10 qubits 4.6 -> 1.3 ms, 12 qubits 25 -> 4.9 ms.)
+void bank_score(int n, int T, const uint32_t* M, const LaneBasis& w, const LaneBasis& r, int* minv, int* sum) {
   *minv = 64;
   *sum = 0;
-  for (int side = 0; side < 2; ++side) {
-    const std::vector<uint32_t>& J = side ? rj : wj;
-    for (int h0 = 0; h0 < T; h0 += 16) {
-      uint32_t seen = 0;
-      for (int t = h0; t < h0 + 16 && t < T; ++t) {
-        const uint32_t pbase = (uint32_t)(t / TP) << n;
-        seen |= 1u << (lds_swizzle(pbase ^ apply_cols(M, n, J[t % TP])) & 15u);
-      }
-      const int d = __builtin_popcount(seen);
-      *minv = std::min(*minv, d);
-      *sum += d;
+  for (const LaneBasis* B : {&w, &r}) {
+    uint32_t span = 1;   // bit b: bank b is reached
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t x = B->j[k], hi = x >> n << n;   // (the map leaves a point's base as it is)
+      const uint32_t bank = lds_swizzle(hi ^ apply_cols(M, n, x)) & 15u;
+      uint32_t moved = 0;
+      for (int b = 0; b < 16; ++b) moved |= ((span >> b) & 1u) << (b ^ bank);
+      span |= moved;
     }
+    const int d = __builtin_popcount(span);
+    *minv = std::min(*minv, d);
+    *sum += d * (T / 16);
   }
 }
 
 void choose_index_map(int n, int T, const int32_t* wmap, const int32_t* rmap, const uint32_t* Acols, int salt,
                       uint32_t* M, bool sweep = false) {
-  const int TP = 1 << (n - 3);
-  std::vector<uint32_t> wj(TP), rj(TP);
-  for (int u = 0; u < TP; ++u) {
-    const uint32_t v = sweep ? sweep_thread((uint32_t)u, n) : (uint32_t)u;
-    wj[u] = deposit_host(v, wmap, n);
-    rj[u] = apply_cols(Acols, n, deposit_host(v, rmap, n));
-  }
-  const int target = std::min(16, T);
+  auto index = [&](uint32_t u) { return sweep ? sweep_thread(u, n) : u; };
+  const LaneBasis wj(n, [&](uint32_t u) { return deposit_host(index(u), wmap, n); });
+  const LaneBasis rj(n, [&](uint32_t u) { return apply_cols(Acols, n, deposit_host(index(u), rmap, n)); });
+  const int target = 16;
   uint32_t best[16];
   for (int k = 0; k < 16; ++k) best[k] = k < n ? (1u << k) : 0u;
   int bmin, bsum;
@@ -821,11 +828,8 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
     if (it > 0)
       for (int k = n - 1; k > 0; --k) std::swap(perm[k], perm[rng.next() % (uint32_t)(k + 1)]);
     for (int k = 0; k < 16; ++k) M[k] = k < n ? 1u << perm[k] : 0u;
-    std::vector<uint32_t> wj(TP), rj(TP);
-    for (int u = 0; u < TP; ++u) {
-      wj[u] = deposit_host((uint32_t)u, rpos, n);
-      rj[u] = deposit_host(sweep_thread((uint32_t)u, n), hp->ftpos, n);
-    }
+    const LaneBasis wj(n, [&](uint32_t u) { return deposit_host(u, rpos, n); });
+    const LaneBasis rj(n, [&](uint32_t u) { return deposit_host(sweep_thread(u, n), hp->ftpos, n); });
     int mv, sm;
     bank_score(n, T, M, wj, rj, &mv, &sm);
     if (mv > bmin || (mv == bmin && sm > bsum)) {
