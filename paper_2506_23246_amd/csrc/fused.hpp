@@ -12,7 +12,7 @@ namespace qp {
 
 // Per-call tables of the sweep layers (sweep_tables_dev.hpp).
 struct SweepTabs {
-  float* gtab;       // [F + 1][kGT] gate matrices U, U^H (entry F: identity), then the coefficients of the
+  float* gtab;       // [F + 1][kGT] gate matrices U (entry F: identity), then the coefficients of the
                      // rounds' phase stages (32-bit fractions of a turn)
   float* tcoef;      // [n_sweeps][kTC] tan(b/2) by position
   float2* ptab;      // [n_sweeps - sweep_first + 1][2^n] phase times cosines, [thread][register]; last: behind the last layer

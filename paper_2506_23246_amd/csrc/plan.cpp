@@ -694,15 +694,12 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
   const int R = (int)hp->rounds.size();
   const int TP = 1 << (n - 3);
   hp->xf.assign(R, QXchg{});
-  hp->xb.assign(R, QXchg{});
+  hp->xb.assign(rounds_image ? R : 0, QXchg{});
   hp->lanes.assign((size_t)(rounds_image ? 2 : 1) * R * TP, QLane{});
   hp->n_exchanges = R > 1 ? R - 1 : 0;
   for (int k = 1; k < R; ++k) {
     const Affine& a = round_ent[k];
     fill_xchg(&hp->xf[k], n, a.acol, a, false, hp->rounds[k].tpos);
-    uint32_t inv[16];
-    if (!gf2_inverse(a.acol, n, inv)) { *status = QP_EINVAL; return "singular entangler map"; }
-    fill_xchg(&hp->xb[k], n, inv, a, true, hp->rounds[k - 1].tpost);
     // forward: round k-1's output mapping -> round k's input mapping; reverse: the other way
     const int T = fused_wg_threads(n);
     uint32_t Mf[16], Mb[16];
@@ -712,6 +709,9 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
       hp->lanes[((size_t)0 * R + k) * TP + u] =
           lane_words(n, a.acol, a, false, hp->rounds[k - 1].tpost, hp->rounds[k].tpos, Mf, (uint32_t)u);
     if (!rounds_image) continue;   // the kernels' adjoint runs the sweep layers
+    uint32_t inv[16];
+    if (!gf2_inverse(a.acol, n, inv)) { *status = QP_EINVAL; return "singular entangler map"; }
+    fill_xchg(&hp->xb[k], n, inv, a, true, hp->rounds[k - 1].tpost);
     choose_index_map(n, T, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, inv, 2 * k + 1, Mb);
     set_lds_layout(&hp->xb[k], n, Mb, hp->rounds[k].tpos, hp->rounds[k - 1].tpost, inv);
     for (int u = 0; u < TP; ++u)
@@ -852,7 +852,7 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
 image:
   // device image
   const int R = (int)hp->rounds.size();
-  if (hp->xf.size() < (size_t)R) { hp->xf.assign(R, QXchg{}); hp->xb.assign(R, QXchg{}); }
+  if (hp->xf.size() < (size_t)R) hp->xf.assign(R, QXchg{});
   QPlanDev h{};
   h.n = n;
   h.n_params = hp->K;
@@ -871,7 +871,7 @@ image:
   size_t off = align16(sizeof(QPlanDev));
   h.off_rounds = (int)off; off = align16(off + sizeof(QRound) * R);
   h.off_xf = (int)off; off = align16(off + sizeof(QXchg) * R);
-  h.off_xb = (int)off; off = align16(off + sizeof(QXchg) * R);
+  h.off_xb = (int)off; off = align16(off + sizeof(QXchg) * hp->xb.size());
   h.off_fused = (int)off; off = align16(off + sizeof(QFused) * hp->fused.size());
   h.off_csr_ptr = (int)off; off = align16(off + sizeof(int32_t) * hp->csr_ptr.size());
   h.off_csr_idx = (int)off; off = align16(off + sizeof(int32_t) * std::max<size_t>(1, hp->csr_idx.size()));
@@ -910,7 +910,7 @@ image:
   std::memcpy(hp->blob.data(), &h, sizeof(h));
   std::memcpy(hp->blob.data() + h.off_rounds, hp->rounds.data(), sizeof(QRound) * R);
   std::memcpy(hp->blob.data() + h.off_xf, hp->xf.data(), sizeof(QXchg) * R);
-  std::memcpy(hp->blob.data() + h.off_xb, hp->xb.data(), sizeof(QXchg) * R);
+  if (!hp->xb.empty()) std::memcpy(hp->blob.data() + h.off_xb, hp->xb.data(), sizeof(QXchg) * hp->xb.size());
   if (!hp->fused.empty())
     std::memcpy(hp->blob.data() + h.off_fused, hp->fused.data(), sizeof(QFused) * hp->fused.size());
   std::memcpy(hp->blob.data() + h.off_csr_ptr, hp->csr_ptr.data(), sizeof(int32_t) * hp->csr_ptr.size());

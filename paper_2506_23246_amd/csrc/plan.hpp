@@ -23,7 +23,7 @@ struct HostPlan {
   std::string fused_reason;
   std::vector<QFused> fused;
   std::vector<QRound> rounds;
-  std::vector<QXchg> xf, xb;          // indexed by round (entry 0 unused)
+  std::vector<QXchg> xf, xb;          // indexed by round (entry 0 unused); xb: with rounds_image only
   std::vector<QLane> lanes;            // [2][rounds][2^(n-3)] per-lane exchange words
   uint32_t zmask[kMaxOut] = {0};
   std::vector<int32_t> csr_ptr, csr_idx;

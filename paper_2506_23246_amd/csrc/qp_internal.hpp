@@ -33,9 +33,8 @@ constexpr int kRegBits = 3;        // 8 amplitudes per thread per statevector
 // Per fused gate the adjoint sweep accumulates S_k = Im <lambda|sigma_k|psi> (k = x, y, z) over
 // all points and statevector pairs, stored as kGS floats/doubles per gate (the last unused).
 constexpr int kGS = 4;
-// Gate-table entry: U (8 floats, row-major complex) followed by U^H (8 floats), so that the
-// adjoint reads its coefficients as they are used.
-constexpr int kGT = 16;
+// Gate-table entry: U, 8 floats, row-major complex.
+constexpr int kGT = 8;
 
 // Swap slots of a round: after its three register-bit gates, register bit i (i < swap_slots(n))
 // trades places with thread bit 4 + i (lane bit 4 or 5 of the wave, by a cross-lane swap of
@@ -219,7 +218,7 @@ struct alignas(16) QPlanDev {
   uint32_t zmask[kMaxOut];          // readout parity mask of output i (trailing entangler folded)
   int32_t off_rounds;               // QRound[n_rounds]
   int32_t off_xf;                   // QXchg[n_rounds]  forward exchange before round k (k>=1)
-  int32_t off_xb;                   // QXchg[n_rounds]  inverse exchange after round k (k>=1)
+  int32_t off_xb;                   // QXchg[n_rounds]  inverse exchange after round k (k>=1); qp_plan_image only
   int32_t off_fused;                // QFused[n_fused]
   int32_t off_csr_ptr;              // int32[n_params+1]
   int32_t off_csr_idx;              // int32[nnz]: fused*4 + component

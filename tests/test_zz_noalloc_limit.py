@@ -24,7 +24,7 @@ def test_documented_limit():
     al = lambda x: (x + 255) // 256 * 256
     n, F, grid = w.circuit.n, c.info(3), 4 * ctx.cu_count
     for P in (0, 1, 1000, 100003):      # the gate matrices, counts, angles and Jacobian, partials, sums
-        assert counted(P) == (al(64 * (F + 1)) + al(8) + al(4 * n * P) + al(12 * n * P) + al(16 * F * grid)
+        assert counted(P) == (al(32 * (F + 1)) + al(8) + al(4 * n * P) + al(12 * n * P) + al(16 * F * grid)
                               + al(4 * grid) + al(32 * F))
     S = w.circuit.n_params // (3 * n)   # rotation layers, each with its phases, tangents and scales
     assert tables >= (8 << n) * S and tables < (8 << n) * (S + 1) + 4096 + 32 * F + 100 * S
