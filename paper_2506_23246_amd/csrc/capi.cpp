@@ -280,7 +280,7 @@ SweepTabs qp::sweep_tabs(const qp_circuit* c, void* base) {
 
 SweepPlan qp::sweep_plan(const qp_circuit* c) {
   const QPlanDev* h = reinterpret_cast<const QPlanDev*>(c->hp.blob.data());
-  return SweepPlan{c->dplan, h->n, h->n_fused, h->n_sweeps, h->sweep_first, h->off_fused, h->off_sweeps};
+  return SweepPlan{c->dplan, h->n, h->n_params, h->n_fused, h->n_sweeps, h->sweep_first, h->off_fused, h->off_sweeps};
 }
 
 WsLayout qp::fused_layout(const qp_circuit* c, int64_t P, int grid_cap) {

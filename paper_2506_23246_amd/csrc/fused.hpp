@@ -24,7 +24,7 @@ struct SweepTabs {
 // What the table kernel needs of the plan's header, passed by value (one dependent load less).
 struct SweepPlan {
   const QPlanDev* plan;
-  int32_t n, n_fused, n_sweeps, sweep_first, off_fused, off_sweeps;
+  int32_t n, n_params, n_fused, n_sweeps, sweep_first, off_fused, off_sweeps;
 };
 
 struct FusedArgs {

@@ -19,49 +19,15 @@
 
 namespace qp {
 
-// Axis (n_x, n_y, n_z) of G_c for component ci of fused gate fu.
-__host__ __device__ inline void generator_axis(const QFused& fu, const float* __restrict__ params, int ci, double* nvec) {
-  if (fu.head) {
-    double v[8];
-    set_identity(v);
-    for (int c = ci + 1; c < fu.ncomp; ++c) {
-      double s, co;
-      sincos(0.5 * (double)params[fu.param[c]], &s, &co);
-      left_mul_rot<double>(fu.kind[c], co, s, v);
-    }
-    // a = (-i/2) P V^H, so P V^H = 2i a
-    double a[8] = {v[0], -v[1], v[4], -v[5], v[2], -v[3], v[6], -v[7]};
-    left_mul_mhalf_i_pauli<double>(fu.kind[ci], a);
-    double b[8];
-    for (int e = 0; e < 4; ++e) { b[2 * e] = -2.0 * a[2 * e + 1]; b[2 * e + 1] = 2.0 * a[2 * e]; }
-    // G' = V b: G'00 = V00 b00 + V01 b10, G'10 = V10 b00 + V11 b10
-    const double g00r = v[0] * b[0] - v[1] * b[1] + v[2] * b[4] - v[3] * b[5];
-    const double g10r = v[4] * b[0] - v[5] * b[1] + v[6] * b[4] - v[7] * b[5];
-    const double g10i = v[4] * b[1] + v[5] * b[0] + v[6] * b[5] + v[7] * b[4];
-    nvec[0] = g10r;
-    nvec[1] = g10i;
-    nvec[2] = g00r;
-    return;
-  }
-  double w[8];
-  set_identity(w);
-  for (int c = 0; c < ci; ++c) {
-    double s, co;
-    sincos(0.5 * (double)params[fu.param[c]], &s, &co);
-    left_mul_rot<double>(fu.kind[c], co, s, w);
-  }
-  double v[8];
-  for (int e = 0; e < 8; ++e) v[e] = w[e];
-  left_mul_mhalf_i_pauli<double>(fu.kind[ci], v);   // v = (-i/2) P W, so P W = 2i v
-  double pw[8];
-  for (int e = 0; e < 4; ++e) { pw[2 * e] = -2.0 * v[2 * e + 1]; pw[2 * e + 1] = 2.0 * v[2 * e]; }
-  // G00 = conj(W00) PW00 + conj(W10) PW10;  G10 = conj(W01) PW00 + conj(W11) PW10
-  const double g00r = w[0] * pw[0] + w[1] * pw[1] + w[4] * pw[4] + w[5] * pw[5];
-  const double g10r = w[2] * pw[0] + w[3] * pw[1] + w[6] * pw[4] + w[7] * pw[5];
-  const double g10i = w[2] * pw[1] - w[3] * pw[0] + w[6] * pw[5] - w[7] * pw[4];
-  nvec[0] = g10r;
-  nvec[1] = g10i;
-  nvec[2] = g00r;
+// Axis (n_x, n_y, n_z) of V P V^H, V = [[a, -b*], [b, a*]] by its first column.
+__device__ inline void pauli_axis(int kind, double2 a, double2 b, double* n) {
+  const double2 ab = make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+  const double ap = a.x * a.x - a.y * a.y, aq = -2.0 * a.x * a.y;   // (a*)^2
+  const double bp = b.x * b.x - b.y * b.y, bq = 2.0 * b.x * b.y;    // b^2
+  const bool x = kind == QP_RX, y = kind == QP_RY;
+  n[0] = x ? ap - bp : (y ? -(aq + bq) : 2.0 * (a.x * b.x + a.y * b.y));
+  n[1] = x ? aq - bq : (y ? ap + bp : 2.0 * (a.x * b.y - a.y * b.x));
+  n[2] = x ? -2.0 * ab.x : (y ? -2.0 * ab.y : a.x * a.x + a.y * a.y - b.x * b.x - b.y * b.y);
 }
 
 __device__ inline double param_grad_one(const QPlanDev* __restrict__ plan, const float* __restrict__ params,
@@ -72,14 +38,33 @@ __device__ inline double param_grad_one(const QPlanDev* __restrict__ plan, const
   const int* idx = reinterpret_cast<const int*>(pb + plan->off_csr_idx);
   double gsum = 0.0;
   for (int e = ptr[k]; e < ptr[k + 1]; ++e) {
+    // (one fetch of all that belongs to the gate, then one of its parameters: the kernel is a chain of fetches)
     const int fi = idx[e] >> 2, ci = idx[e] & 3;
-    double nv[3];
-    generator_axis(fused[fi], params, ci, nv);
-    // the cosines left out when the statistics were taken, and the sign of Y and Z behind an X mask
+    const QFused fu = fused[fi];
     const double* S = s64 + fi * kGS;
     const double* g = T.gpar + (long long)fi * kGP;
-    const double nx = g[0] * nv[0] - g[1] * nv[1], ny = g[1] * nv[0] + g[0] * nv[1];
-    gsum += nx * S[0] * g[2] + (g[3] < 0.0 ? -ny : ny) * S[1] * g[2] + nv[2] * S[2] * g[3];
+    const double Sx = S[0], Sy = S[1], Sz = S[2], gc = g[0], gs = g[1], gxy = g[2], gz = g[3];
+    // the components after c (statistic behind the gate) or before it: V P V^H or W^H P W, W^H of first column
+    // (a*, -b)
+    const int c0 = fu.head ? ci + 1 : 0, c1 = fu.head ? fu.ncomp : ci;
+    float th[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) th[c] = params[c < fu.ncomp ? fu.param[c] : fu.param[0]];
+    double2 a = make_double2(1.0, 0.0), b = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const int c = c0 + o;
+      if (c >= c1) break;
+      double sn, cs;
+      sincos(0.5 * (double)(c == 0 ? th[0] : (c == 1 ? th[1] : th[2])), &sn, &cs);
+      column_rot(c == 0 ? fu.kind[0] : (c == 1 ? fu.kind[1] : fu.kind[2]), cs, sn, a, b);
+    }
+    if (!fu.head) { a.y = -a.y; b.x = -b.x; b.y = -b.y; }
+    double nv[3];
+    pauli_axis(ci == 0 ? fu.kind[0] : (ci == 1 ? fu.kind[1] : fu.kind[2]), a, b, nv);
+    // the cosines left out when the statistics were taken, and the sign of Y and Z behind an X mask
+    const double nx = gc * nv[0] - gs * nv[1], ny = gs * nv[0] + gc * nv[1];
+    gsum += nx * Sx * gxy + (gz < 0.0 ? -ny : ny) * Sy * gxy + nv[2] * Sz * gz;
   }
   // CRZ(c, t) occurrences: dL/dtheta = (W_t - W_ct) / 2 from the layer's parity sums, which follow the
   // fused-gate statistics (see QPhaseStage)

@@ -60,4 +60,14 @@ __host__ __device__ inline void set_identity(T* u) {
   u[4] = T(0); u[5] = T(0); u[6] = T(1); u[7] = T(0);
 }
 
+// (u0, u1) <- (c - i s P) (u0, u1): the first column of a product behind one more rotation, c u + s w with the
+// partners w = -i P u chosen, not branched to.
+__host__ __device__ inline void column_rot(int kind, double c, double s, double2& u0, double2& u1) {
+  const bool x = kind == QP_RX, y = kind == QP_RY;
+  const double2 w0 = make_double2(x ? u1.y : (y ? -u1.x : u0.y), x ? -u1.x : (y ? -u1.y : -u0.x));
+  const double2 w1 = make_double2(x ? u0.y : (y ? u0.x : -u1.y), x ? -u0.x : (y ? u0.y : u1.x));
+  u0 = make_double2(c * u0.x + s * w0.x, c * u0.y + s * w0.y);
+  u1 = make_double2(c * u1.x + s * w1.x, c * u1.y + s * w1.y);
+}
+
 }  // namespace qp

@@ -1,5 +1,5 @@
 // Per-call tables of the sweep layers, formed in FP64 from the parameters and rounded once
-// (O(layers 2^n) work, independent of the point count): the tangents of the layers' rotations, the
+// (independent of the point count): the tangents of the layers' rotations, the
 // phase (times the rotations' cosines) of every basis index in front of each layer, the X masks, and
 // what the gradient kernel needs to read the statistics.  See QSweep.
 #pragma once
@@ -107,18 +107,18 @@ struct Zyz {
   double t, cosb;
   int flip;
 };
-__device__ inline int zyz_flip(const double* u) { return u[4] * u[4] + u[5] * u[5] > u[0] * u[0] + u[1] * u[1]; }
 __device__ inline double2 cmul(double2 x, double2 y) { return make_double2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x); }
-__device__ inline Zyz zyz_split(const double* u) {
+__device__ inline int zyz_flip(double2 u0, double2 u1) { return u1.x * u1.x + u1.y * u1.y > u0.x * u0.x + u0.y * u0.y; }
+__device__ inline Zyz zyz_split(double2 u0, double2 u1) {
   Zyz z;
-  const double n0 = u[0] * u[0] + u[1] * u[1], n1 = u[4] * u[4] + u[5] * u[5];
+  const double n0 = u0.x * u0.x + u0.y * u0.y, n1 = u1.x * u1.x + u1.y * u1.y;
   const double i0 = rsqrt(n0), i1 = rsqrt(n1), r0 = n0 > 0.0 ? n0 * i0 : 0.0, r1 = n1 > 0.0 ? n1 * i1 : 0.0;
-  const double2 p0 = r0 > 0.0 ? make_double2(u[0] * i0, u[1] * i0) : make_double2(1.0, 0.0);
-  const double2 p1 = r1 > 0.0 ? make_double2(u[4] * i1, u[5] * i1) : make_double2(1.0, 0.0);
+  const double2 p0 = r0 > 0.0 ? make_double2(u0.x * i0, u0.y * i0) : make_double2(1.0, 0.0);
+  const double2 p1 = r1 > 0.0 ? make_double2(u1.x * i1, u1.y * i1) : make_double2(1.0, 0.0);
   const double2 q = cmul(p0, p1);
   z.a = cmul(p1, make_double2(p0.x, -p0.y));
   z.c = make_double2(q.x, -q.y);
-  z.flip = zyz_flip(u);
+  z.flip = zyz_flip(u0, u1);
   z.t = z.flip ? -r0 * i1 : r1 * i0;
   z.cosb = z.flip ? r1 : r0;   // (U has unit determinant)
   return z;
@@ -127,11 +127,14 @@ __device__ inline Zyz zyz_split(const double* u) {
 constexpr int kTabThreads = 256;
 constexpr int kFlipLayers = 1024;   // layers whose flips the table kernel holds at a time
 
-// Block blk of a circuit's tables (kTabThreads threads; all of them call this).  What bounds it is
-// latency: dependent loads, barriers, and code run once from a cold instruction cache.  So everything
-// that comes from the plan is fetched before anything is formed, uniform data by scalar loads, and the
-// layer's rotations are written by another wave than the first entries (4 qubits, 2 layers: 6.8 -> 5.1 us;
-// the bare gate matrices take 2.8).
+// Block blk of a circuit's tables (kTabThreads threads; all of them call this).  What bounds it is the chain
+// of one wave's instructions, about 8 cycles each (a second pass over warm caches takes as long as the first).
+// So everything that comes from the plan is fetched unconditionally and before anything is formed, the
+// parameters beside it, choices are selected and not branched to, and gates, entries and the layer's rotations
+// are different waves' (4 qubits, 2 layers: 5.3 -> 4.2 us; the bare gate matrices take 2.9).
+// Every block forms the gates from its layer on, whose flips it needs: work grows with gates x layers, and
+// from kFlipLayers layers on once more with every kFlipLayers (3 qubits, 600 layers of one rotation each: 81 us
+// in front of a kernel of 937; 12 qubits, 700 layers of one gate: 507 us in front of 4165).
 __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict__ params, const SweepTabs& T, int blk,
                                     int fp32) {
   __shared__ uint32_t flips[kFlipLayers];
@@ -139,6 +142,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   __shared__ double s_cos[kMaxQubits], s_t[kMaxQubits];
   __shared__ int s_flip[kMaxQubits];
   __shared__ double2 s_trig[kTabThreads];
+  __shared__ float s_par[kTabThreads];
   __shared__ uint32_t s_x, s_xo;
   const int tid = threadIdx.x;
   const QPlanDev* gplan = A.plan;
@@ -147,12 +151,12 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   const QFused* fused = reinterpret_cast<const QFused*>(reinterpret_cast<const char*>(gplan) + A.off_fused);
   CP<QSweep> sweeps = reinterpret_cast<CP<QSweep>>(pb + A.off_sweeps);
   const int n = A.n, F = A.n_fused, S = A.n_sweeps, L0 = A.sweep_first;
-  const int cpl = (1 << n) > kTabThreads ? (1 << n) / kTabThreads : 1;
+  const int cs = n > 8 ? n - 8 : 0;   // 2^cs blocks of kTabThreads entries per layer
   if (blk == 0) {
     for (int f = tid; f <= F; f += kTabThreads) gate_entry(gplan, params, f, fp32, T.gtab);
     return;
   }
-  const int l = L0 + (blk - 1) / cpl, chunk = (blk - 1) % cpl;   // l = S: behind the last layer
+  const int l = L0 + ((blk - 1) >> cs), chunk = (blk - 1) & ((1 << cs) - 1);   // l = S: behind the last layer
   if (l > S) {
     for (int i = tid; i < plan->n_phase_coef; i += kTabThreads)
       phase_entry(gplan, params, i, reinterpret_cast<uint32_t*>(T.gtab + (size_t)(F + 1) * kGT));
@@ -161,55 +165,96 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   // a thread per rotation takes its sine, then one per gate multiplies them up
   constexpr int kGates = kTabThreads / 3;
   const int rc = tid % 3, ti = tid - (kTabThreads - 64);
-  QFused fu{};
-  int nc = 0, pi = 0;
-  if (F > 0) {   // a circuit without parameters has no gate to read and may have no parameter array
-    fu = fused[tid < F ? tid : 0];
-    nc = fused[tid / 3 < F ? tid / 3 : 0].ncomp;
-    pi = fused[tid / 3 < F ? tid / 3 : 0].param[rc];
-  }
+  // Everything is fetched unconditionally, from the plan's header where there is nothing (a circuit without
+  // parameters has no gate and may have no parameter array): a condition would be a branch around each fetch,
+  // or a wait for the one it depends on.
+  const QFused* fsrc = F > 0 ? fused : reinterpret_cast<const QFused*>(gplan);
+  const int fr0 = tid / 3 < F ? tid / 3 : 0;
+  QFused fu = fsrc[tid < F ? tid : 0];
+  int nc = fsrc[fr0].ncomp, pi = fsrc[fr0].param[rc];
   constexpr int kAhead = 4;
-  const uint32_t* grows = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(gplan) + A.off_sweeps +
-                                                            offsetof(QSweep, arow));
-  auto row_of = [&](int k) { return k >= 0 && k < S && tid < 16 ? grows[(size_t)k * (sizeof(QSweep) / 4) + tid] : 0u; };
+  const uint32_t* grows = S > 0 ? reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(gplan) + A.off_sweeps +
+                                                                    offsetof(QSweep, arow))
+                                : reinterpret_cast<const uint32_t*>(gplan);
+  auto row_of = [&](int k) {   // (lanes 16.. repeat the rows; a layer out of range gives some row)
+    k = k < S ? k : S - 1;
+    return grows[(size_t)(k > 0 ? k : 0) * (sizeof(QSweep) / 4) + (tid & 15)];
+  };
   uint32_t ahead[kAhead];
 #pragma unroll
   for (int i = 0; i < kAhead; ++i) ahead[i] = row_of(S - 1 - i);
   const uint32_t row_l = row_of(l);
   CP<QSweep> L = sweeps + (l < S ? l : 0);
   const bool rot = ti >= 0 && ti < kPos && l < S;
-  const int my_gate = rot ? reinterpret_cast<const QSweep*>(reinterpret_cast<const char*>(gplan) + A.off_sweeps)[l].gate[ti] : -1;
+  const int32_t* gl = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(gplan) +
+                                                       (rot ? A.off_sweeps + l * (int)sizeof(QSweep) : 0));
+  const int gate_at = gl[rot ? ti : 0], bit_at = gl[rot ? offsetof(QSweep, tin) / 4 + ti : 0];
+  // the parameters, fetched beside the plan that says which is whose, if there are no more than threads
+  const bool few = A.n_params <= kTabThreads;
+  const float par = (A.n_params > 0 ? params : reinterpret_cast<const float*>(gplan))[tid < A.n_params ? tid : 0];
   CP<int32_t> tin = reinterpret_cast<CP<int32_t>>(pb + (l < S ? A.off_sweeps + l * (int)sizeof(QSweep) + (int)offsetof(QSweep, tin)
                                                               : (int)offsetof(QPlanDev, ftpos)));
-  int tb[kMaxQubits];   // index bit of each position of the mapping
+  int tb[kMaxQubits];   // index bit of each position of the mapping (0 behind the last)
 #pragma unroll
-  for (int k = 0; k < kMaxQubits; ++k) tb[k] = k < n ? tin[k] : 0;
-  float th = F > 0 ? params[rc < nc ? pi : 0] : 0.f;
+  for (int k = 0; k < kMaxQubits; ++k) tb[k] = tin[k];
+  int nterms = 0, phase = -1;
+  uint32_t arow[kMaxQubits] = {};
+  if (l < S) {
+    nterms = L->nterms;
+    phase = L->phase;
+#pragma unroll
+    for (int b = 0; b < kMaxQubits; ++b) arow[b] = L->arow[b];
+  }
   // this thread's index in the layer's mapping, without the X mask, and where it was before the index map
   // (linear, so the mask's share is added later)
-  const int i = chunk * kTabThreads + tid;
+  // Up to 6 qubits the entries are one wave's, the third: the first has the gates and the masks.
+  const bool apart = n <= 6;
+  const int i = chunk * kTabThreads + (apart ? tid ^ 128 : tid);
   const uint32_t v = sweep_thread((uint32_t)i >> 3, n), r = (uint32_t)i & 7u;
   uint32_t ji = 0, joi = 0;
+  if (i < (1 << n)) {
 #pragma unroll
-  for (int k = 0; k < kMaxQubits; ++k)
-    if (k < n) ji ^= ((k < 3 ? r >> k : v >> (k - 3)) & 1u) << tb[k];
-  if (l < S)
+    for (int k = 0; k < kMaxQubits; ++k) ji ^= ((k < 3 ? r >> k : v >> (k - 3)) & 1u) << tb[k];
 #pragma unroll
-    for (int b = 0; b < kMaxQubits; ++b)
-      if (b < n) joi |= ((uint32_t)__popc(L->arow[b] & ji) & 1u) << b;
+    for (int b = 0; b < kMaxQubits; ++b) joi |= ((uint32_t)__popc(arow[b] & ji) & 1u) << b;
+  }
+  asm volatile("" : "+v"(ji), "+v"(joi));   // (formed here: the mapping and the rows need not be kept)
+  s_par[tid] = par;
   if (tid < kMaxQubits) {
     s_c[tid] = s_a[tid] = make_double2(1.0, 0.0);
     s_t[tid] = 0.0; s_cos[tid] = 1.0; s_flip[tid] = 0;
   }
   // Flips from layer l on, kFlipLayers layers at a time from the last one back; layer l's gates, and those
   // before it.
+  auto first_gate = [&](int k) {
+    int f = k < 0 ? 0 : F;
+    if (k >= 0)
+#pragma unroll
+      for (int p = 0; p < kPos; ++p) {
+        const int g = sweeps[k].gate[p];
+        if (g >= 0 && g < f) f = g;
+      }
+    return f;
+  };
+  __syncthreads();
+  float th = 0.f;
+  if (F > 0) {
+    const int at = rc < nc ? pi : 0;
+    th = s_par[few ? at : 0];
+    if (!few) th = params[at];
+  }
   uint32_t x = 0;      // the X mask, carried back from the readout through the index maps (first wave)
   auto pass = [&](int hi, auto first) {
     constexpr bool FIRST = decltype(first)::value;   // (its gates and rows are fetched already)
     const int lo = hi - kFlipLayers > l ? hi - kFlipLayers : l;
     for (int k = lo + tid; k < hi; k += kTabThreads) flips[k - lo] = 0;
     if (F == 0) __syncthreads();
-    for (int f0 = 0; f0 < F; f0 += kGates) {
+    int fa = 0, fb = F;   // the gates come layer by layer: from layer l - 1 on, and those of layers [lo, hi)
+    if (F > kGates) {
+      fa = first_gate(lo > l ? lo : l - 1) / kGates * kGates;
+      if (hi < S) fb = first_gate(hi);
+    }
+    for (int f0 = fa; f0 < fb; f0 += kGates) {
       const int f = f0 + tid, fr = f0 + tid / 3;
       if (f0 || !FIRST) {
         fu = fused[f < F ? f : 0];
@@ -229,33 +274,42 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
       }
       __syncthreads();
       if (tid < kGates && f < F && !fu.head && fu.layer >= l - 1) {
-        double u[8];
-        set_identity(u);
+        double2 u0 = make_double2(1.0, 0.0), u1 = make_double2(0.0, 0.0);   // first column: all the split needs
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-          if (k < fu.ncomp) left_mul_rot<double>(fu.kind[k], s_trig[3 * tid + k].x, s_trig[3 * tid + k].y, u);
-        const int b = n - 1 - fu.qubit, flip = zyz_flip(u);
+        for (int k = 0; k < 3; ++k) {
+          const double2 t = s_trig[3 * tid + k];
+          if (k < fu.ncomp) column_rot(fu.kind[k], t.x, t.y, u0, u1);
+        }
+        const int b = n - 1 - fu.qubit, flip = zyz_flip(u0, u1);
         if (fu.layer >= lo && fu.layer < hi && flip) atomicOr(&flips[fu.layer - lo], 1u << b);
         if (fu.layer <= l) {
-          const Zyz z = zyz_split(u);
+          const Zyz z = zyz_split(u0, u1);
           if (fu.layer == l) { s_c[b] = z.c; s_cos[b] = z.cosb; s_t[b] = z.t; }
           else { s_a[b] = z.a; s_flip[b] = flip; }
         }
       }
       __syncthreads();
     }
-    if (tid < 64) {   // (ballots of row parities)
-      auto step = [&](int k, uint32_t row) {
-        x ^= __builtin_amdgcn_readfirstlane(flips[k - lo]);
-        if (k > l) x = (uint32_t)__ballot((int)(__popc(x & row) & 1u));
-      };
-      if constexpr (FIRST) {
+    if (tid < 64) {   // (ballots of row parities; rows and flips four layers at a time, for they are cold)
+      auto steps = [&](int k0, const uint32_t (&rows)[kAhead]) {
+        uint32_t fl[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) fl[i] = flips[k0 - i >= lo ? k0 - i - lo : 0];
 #pragma unroll
         for (int i = 0; i < kAhead; ++i)
-          if (S - 1 - i >= lo) step(S - 1 - i, ahead[i]);
-      }
+          if (k0 - i >= lo) {
+            x ^= __builtin_amdgcn_readfirstlane(fl[i]);
+            if (k0 - i > l) x = (uint32_t)__ballot((int)(__popc(x & rows[i]) & 1u)) & 0xffffu;
+          }
+      };
+      if constexpr (FIRST) steps(S - 1, ahead);
 #pragma unroll 1
-      for (int k = FIRST ? S - 1 - kAhead : hi - 1; k >= lo; --k) step(k, row_of(k));
+      for (int k0 = FIRST ? S - 1 - kAhead : hi - 1; k0 >= lo; k0 -= kAhead) {
+        uint32_t rows[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) rows[i] = row_of(k0 - i);
+        steps(k0, rows);
+      }
     }
     return lo;
   };
@@ -264,7 +318,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
     hi = pass(hi, std::false_type{});
   }
   if (tid < 64) {
-    const uint32_t xo = l < S ? (uint32_t)__ballot((int)(__popc(x & row_l) & 1u)) : x;   // before the index map
+    const uint32_t xo = l < S ? (uint32_t)__ballot((int)(__popc(x & row_l) & 1u)) & 0xffffu : x;   // before the index map
     if (tid == 0) {
       s_x = x;
       s_xo = xo;
@@ -280,26 +334,29 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
     if (tid < kTC) T.tcoef[tid] = 0.f;
     if (tid == 0) { T.xmask[0] = s_xo; T.lscale[0] = 1.0; }
     for (int f = tid; f < F; f += kTabThreads) {
-      if (!fused[f].head) continue;
+      if (F > kGates) fu = fused[f];   // (else each thread still has its gate)
+      if (!fu.head) continue;
       double* g = T.gpar + (size_t)f * kGP;
       g[0] = 1.0; g[1] = 0.0; g[2] = 1.0;
-      g[3] = ((s_xo >> (n - 1 - fused[f].qubit)) & 1u) ? -1.0 : 1.0;
+      g[3] = ((s_xo >> (n - 1 - fu.qubit)) & 1u) ? -1.0 : 1.0;
     }
   }
   if (chunk == 0 && l < S && ti >= 0 && ti < kTC) {
     if (ti == 0) { T.xmask[l] = x; T.lscale[l] = mag * mag; }
     float t = 0.f;
+    const int my_gate = rot ? gate_at : -1;
     if (my_gate >= 0) {
       // S_x, S_y: the cosines of the gates pulled back when they are taken (wave positions first,
       // then the swap slots, then the rest); S_z: of all
-      const int from = ti >= 9 ? 9 : (ti >= 7 ? 7 : 0);
-      double sc = 1.0;
-      int b = 0;
-#pragma unroll
-      for (int p = 0; p < kMaxQubits; ++p) {
-        b = p == ti ? tb[p] : b;
-        if (p < n && p >= from) sc *= s_cos[tb[p]] * s_cos[tb[p]];
+      double s7 = 1.0, s9 = 1.0;
+#pragma unroll 1
+      for (int p = 7; p < n; ++p) {
+        const double c2 = s_cos[tin[p]] * s_cos[tin[p]];
+        s7 *= c2;
+        if (p >= 9) s9 *= c2;
       }
+      const double sc = ti >= 9 ? s9 : (ti >= 7 ? s7 : mag * mag);
+      const int b = bit_at;
       const bool neg = (x >> b) & 1u;   // X RY(b) X = RY(-b)
       t = (float)(neg ? -s_t[b] : s_t[b]);
       double* gp = T.gpar + (size_t)my_gate * kGP;
@@ -314,19 +371,26 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   // two products, so that their chains overlap
   double2 ph = make_double2(mag, 0.0), pa = make_double2(1.0, 0.0);
   int half = 0;     // half turns
-  for (int b0 = 0; b0 < n; b0 += 4)
+  const double2 one = make_double2(1.0, 0.0);
+  for (int b0 = 0; b0 < n; b0 += 4) {
+    double2 c[4], a[4];
+    int fl[4];
 #pragma unroll
-    for (int b = b0; b < b0 + 4; ++b) {
-      if ((j >> b) & 1u) ph = cmul(ph, s_c[b]);
-      if ((jo >> b) & 1u) pa = cmul(pa, s_a[b]);
-      else half += s_flip[b];   // RY(pi) = diag(-1, 1) X
+    for (int b = 0; b < 4; ++b) { c[b] = s_c[b0 + b]; a[b] = s_a[b0 + b]; fl[b] = s_flip[b0 + b]; }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const bool cb = (j >> (b0 + b)) & 1u, ab = (jo >> (b0 + b)) & 1u;
+      ph = cmul(ph, cb ? c[b] : one);
+      pa = cmul(pa, ab ? a[b] : one);
+      half += ab ? 0 : fl[b];   // RY(pi) = diag(-1, 1) X
     }
+  }
   ph = cmul(ph, pa);
   if (l < S) {
     CP<uint32_t> terms = reinterpret_cast<CP<uint32_t>>(pb + plan->off_terms) + 2 * L->term0;
-    for (int t = 0; t < L->nterms; ++t) half += __popc(terms[2 * t] & j) & __popc(terms[2 * t + 1] & j) & 1;
-    if (L->phase >= 0) {
-      CP<QPhaseStage> st = reinterpret_cast<CP<QPhaseStage>>(pb + plan->off_phase) + L->phase;
+    for (int t = 0; t < nterms; ++t) half += __popc(terms[2 * t] & j) & __popc(terms[2 * t + 1] & j) & 1;
+    if (phase >= 0) {
+      CP<QPhaseStage> st = reinterpret_cast<CP<QPhaseStage>>(pb + plan->off_phase) + phase;
       CP<QPhaseGate> pg = reinterpret_cast<CP<QPhaseGate>>(pb + plan->off_phase_gates) + st->gate0;
       double turn = 0.0;   // in units of pi
       for (int g = 0; g < st->ngates; ++g)
