@@ -151,7 +151,8 @@ void qp_circuit_destroy(qp_circuit* c);
 int64_t qp_circuit_info(const qp_circuit* c, int32_t what);
 
 /* Launch shape of the fused kernel for this circuit (what the autotuner sets): exchange_planes
- * 4 = software-pipelined exchanges over two plane pairs, 2 = one plane pair, unpipelined;
+ * 4 = software-pipelined exchanges over two plane pairs, 2 = one plane pair, unpipelined (from
+ * 10 qubits on; below, exchanges stay inside a wave, and input gradients always take 2);
  * wg_per_cu = persistent workgroups per CU, 1 at 12 qubits, 1..4 below (above 2 the grid runs
  * in two generations).  The choice changes speed, not results beyond rounding order.
  * QP_EINVAL for other values or a shape whose LDS does not fit a CU.  Circuit compilation

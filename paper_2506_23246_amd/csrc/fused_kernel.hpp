@@ -1973,10 +1973,13 @@ hipError_t launch_one(const FusedArgs& a, int grid, size_t dyn, hipStream_t st) 
 }
 
 // Entry point of one per-N unit.  exs: exchange planes (2 or 4) from 10 qubits on; below, an exchange
-// stays inside a wave and one kernel serves both.
+// stays inside a wave and one kernel serves both.  Input gradients take two planes (4 layers, 2^23 amplitudes,
+// adjoint: 10 qubits 1140 us with four planes, 997 with two; 11: 1230, 1053; 12: 1278, 1181; with the loss 1251 and
+// 1217, 1330 and 1227, 1506 and 1397; 32 points 126 and 119, 135 and 125, 170 and 166): with four planes their
+// kernels spill 160 to 330 registers.
 template <int N, int MODE, bool EG = false>
 hipError_t launch_mode(const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st) {
-  if constexpr (N >= 10) {
+  if constexpr (N >= 10 && !EG) {
     if (exs == 4) return launch_one<N, 4, MODE, EG>(a, grid, dyn, st);
   }
   return launch_one<N, 2, MODE, EG>(a, grid, dyn, st);
