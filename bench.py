@@ -75,7 +75,7 @@ def matrix_core_share(n_fused: int, n_folded: int = 0, n: int = 12) -> float:
 KERNEL_SOURCES = {
     "k_fused": ["fused_kernel.hpp", "fused.hip", "fused.hpp", "fused_n*.hip", "qp_internal.hpp", "grads_dev.hpp",
                 "rot_dev.hpp", "const_dev.hpp", "sweep_tables_dev.hpp", "plan.cpp", "plan.hpp"],
-    "k_batch": ["batch.hip", "const_dev.hpp", "sweep_tables_dev.hpp", "batch_kernel.hpp", "batch.hpp", "batch_api.cpp", "fused_kernel.hpp",
+    "k_batch": ["batch.hip", "batch_thin.hip", "const_dev.hpp", "sweep_tables_dev.hpp", "batch_kernel.hpp", "batch.hpp", "batch_api.cpp", "fused_kernel.hpp",
                 "fused.hpp", "qp_internal.hpp", "grads_dev.hpp", "rot_dev.hpp", "plan.cpp", "plan.hpp"],
 }
 

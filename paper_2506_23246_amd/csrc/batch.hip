@@ -79,46 +79,14 @@ size_t batch_lds_bytes(int n, int max_cols) {   // static exchange planes + dyna
   return (size_t)kBEXS * T * 8 * sizeof(float2) + batch_dyn_lds_bytes(T, max_cols);
 }
 
-hipError_t launch_batch_seg(int seg, int grid, size_t dyn, hipStream_t s, const BatchCirc* circs,
-                            const BatchItem* items, int nitems, int* counter, float* mpart, float* lpart) {
-  switch (seg) {
-    case kSegLo:
-      hipLaunchKernelGGL((k_batch<3, kBatchSplit, 256>), dim3(grid), dim3(256), dyn, s, circs, items, nitems,
-                         counter, mpart, lpart);
-      break;
-    case kSegHi:
-      hipLaunchKernelGGL((k_batch<kBatchSplit + 1, 11, 256>), dim3(grid), dim3(256), dyn, s, circs, items,
-                         nitems, counter, mpart, lpart);
-      break;
-    case kSegBig:
-      hipLaunchKernelGGL((k_batch<kBatchBig, kBatchBig, 512>), dim3(grid), dim3(512), dyn, s, circs, items,
-                         nitems, counter, mpart, lpart);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t batch_prepare(int max_cols, int max_cols_big) {
-  const int lds = (int)batch_dyn_lds_bytes(256, max_cols), lds_big = (int)batch_dyn_lds_bytes(512, max_cols_big);
-  hipError_t e = hipSuccess;
-  if (max_cols > 0) {
-    e = hipFuncSetAttribute((const void*)k_batch<3, kBatchSplit, 256>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_batch<kBatchSplit + 1, 11, 256>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  }
-  if (e == hipSuccess && max_cols_big > 0)
-    e = hipFuncSetAttribute((const void*)k_batch<kBatchBig, kBatchBig, 512>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_big);
-  return e;
+hipError_t batch_prepare(int max_cols, int max_cols_big, bool thin) {
+  return thin ? prepare_batch_thin(max_cols, max_cols_big) : prepare_batch_classes<false>(max_cols, max_cols_big);
 }
 
 hipError_t launch_batch(const BatchCirc* circs, int ncirc, const BatchItem* items, const int* nitems_seg,
                         const BatchGate* gates, int ngates, const BatchCol* cols, int ncols, const BatchGate* pars,
                         int npars, int* counter, float* mpart, float* lpart, int grid, int grid_lo, int grid_hi,
-                        int grid_big, int max_cols, int max_cols_big, int count_needed, hipStream_t st,
+                        int grid_big, int max_cols, int max_cols_big, bool thin, int count_needed, hipStream_t st,
                         hipStream_t aux, hipEvent_t ev_fork, hipEvent_t ev_join, hipEvent_t ev0, hipEvent_t ev1) {
   hipError_t e = hipSuccess;
   auto keep = [&](hipError_t x) { if (e == hipSuccess) e = x; };
@@ -135,7 +103,8 @@ hipError_t launch_batch(const BatchCirc* circs, int ncirc, const BatchItem* item
   auto seg = [&](int sg, hipStream_t s, int g) -> hipError_t {
     if (nitems_seg[sg] == 0 || g <= 0) return hipSuccess;
     const size_t dyn = sg == kSegBig ? batch_dyn_lds_bytes(512, max_cols_big) : batch_dyn_lds_bytes(256, max_cols);
-    return launch_batch_seg(sg, g, dyn, s, circs, seg_items[sg], nitems_seg[sg], counter + sg, mpart, lpart);
+    return (thin ? launch_batch_thin : launch_batch_class<false>)(sg, g, dyn, s, circs, seg_items[sg], nitems_seg[sg],
+                                                                  counter + sg, mpart, lpart);
   };
   if (two) {
     // the low segment on st, the others one after the other on aux, at the same time

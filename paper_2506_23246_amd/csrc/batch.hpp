@@ -54,9 +54,9 @@ inline int batch_segment(int n) { return n >= kBatchBig ? kSegBig : (n > kBatchS
 hipError_t launch_batch(const BatchCirc* circs, int ncirc, const BatchItem* items, const int* nitems_seg,
                         const BatchGate* gates, int ngates, const BatchCol* cols, int ncols, const BatchGate* pars,
                         int npars, int* counter, float* mpart, float* lpart, int grid, int grid_lo, int grid_hi,
-                        int grid_big, int max_cols, int max_cols_big, int count_needed, hipStream_t st, hipStream_t aux,
+                        int grid_big, int max_cols, int max_cols_big, bool thin, int count_needed, hipStream_t st, hipStream_t aux,
                         hipEvent_t ev_fork, hipEvent_t ev_join, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t batch_prepare(int max_cols, int max_cols_big);   // 0: no circuit of that block size
+hipError_t batch_prepare(int max_cols, int max_cols_big, bool thin);   // 0: no circuit of that block size
 size_t batch_lds_bytes(int n, int max_cols);
 
 }  // namespace qp
@@ -80,6 +80,7 @@ struct qp_batch {
   int grid_lo = 0, grid_hi = 0;     // grids of the low and high classes when they run at once
   int grid_big = 0;                 // grid of the 12-qubit class
   int max_cols = 0, max_cols_big = 0;   // largest F * 8 + n_mom below 12 qubits and at 12
+  bool thin = false;                   // a circuit is thin (HostPlan::thin)
   int items_crz = 0;                   // work items of circuits with CRZ phase stages
   int nitems_seg[qp::kNumSegs] = {};   // work items per segment (listed in segment order)
   double work_lo = 0.0, work_rest = 0.0;   // estimated work of the low segments and of the others

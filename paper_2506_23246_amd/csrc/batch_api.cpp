@@ -55,6 +55,7 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
     int& mc = c->hp.n >= kBatchBig ? b->max_cols_big : b->max_cols;
     mc = std::max(mc, (int)c->hp.fused.size() * kGS + n_moments(c));
     if (c->hp.enc_kind == QP_ENC_RFF) b->rff_circs.push_back(i);
+    b->thin = b->thin || c->hp.thin;
   }
   if ((b->max_cols > 0 && batch_lds_bytes(3, b->max_cols) > 160 * 1024) ||
       (b->max_cols_big > 0 && batch_lds_bytes(kBatchBig, b->max_cols_big) > 160 * 1024))
@@ -167,7 +168,7 @@ extern "C" qp_status qp_batch_compile(qp_ctx* ctx, int32_t count, const qp_circu
   if (e == hipSuccess) e = hipMemcpy(b->dcols, b->cols.data(), sizeof(BatchCol) * b->cols.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess && !b->gates.empty()) e = hipMemcpy(b->dgates, b->gates.data(), sizeof(BatchGate) * b->gates.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess && !b->pars.empty()) e = hipMemcpy(b->dpars, b->pars.data(), sizeof(BatchGate) * b->pars.size(), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = batch_prepare(b->max_cols, b->max_cols_big);
+  if (e == hipSuccess) e = batch_prepare(b->max_cols, b->max_cols_big, b->thin);
   // the second stream keeps the default priority (no other priority is used anywhere)
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->aux, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
@@ -307,7 +308,7 @@ static hipError_t batch_launch(qp_ctx* ctx, qp_batch* b, const qp_maxwell_desc* 
   }
   return launch_batch(b->dcirc, (int)b->circs.size(), b->ditems, b->nitems_seg, b->dgates, (int)b->gates.size(), b->dcols, (int)b->cols.size(), b->dpars, (int)b->pars.size(),
                       reinterpret_cast<int*>(w + L.counter), reinterpret_cast<float*>(w + L.mpart),
-                      reinterpret_cast<float*>(w + L.lpart), grid, g_lo, g_hi, b->grid_big, b->max_cols, b->max_cols_big,
+                      reinterpret_cast<float*>(w + L.lpart), grid, g_lo, g_hi, b->grid_big, b->max_cols, b->max_cols_big, b->thin,
                       ld->kind == QP_LOSS_DIEL_SPLIT ? 1 : 0, ctx->stream, b->aux, b->ev_fork, b->ev_join,
                       ctx->timing ? ctx->ev0 : nullptr, ctx->timing ? ctx->ev1 : nullptr);
 }

@@ -18,12 +18,12 @@ inline size_t batch_dyn_lds_bytes(int T, int max_cols) {
 }
 
 // The tiles of one work item.
-template <int N, int NLO, int NHI, int T>
+template <int N, int NLO, int NHI, int T, bool THIN>
 __device__ __forceinline__ void batch_case(const BatchCirc& C, const BatchItem& it, float2* buf, float* slots,
                                            float* mslots, float* red, float& lacc) {
   if constexpr (NLO <= N && N <= NHI) {
     for (int t = it.tile0; t < it.tile0 + it.ntile; ++t)
-      fused_tile<N, T, kBEXS, kModeMaxwell>(C.a, t, buf, slots, mslots, red, lacc);
+      fused_tile<N, T, kBEXS, kModeMaxwell, false, THIN && (N >= kThinQubits)>(C.a, t, buf, slots, mslots, red, lacc);
   }
 }
 
@@ -31,7 +31,7 @@ __device__ __forceinline__ void batch_case(const BatchCirc& C, const BatchItem& 
 // gets its own register allocation (all counts 3..11 in one function exceeded the 256-VGPR cap
 // and spilled 128 bytes a lane, whose scratch traffic doubled the kernel's HBM bytes; 3..8 and
 // 9..11 each fit, and 12 qubits need 512 threads: a tile is one point on 512 threads).
-template <int NLO, int NHI, int T>
+template <int NLO, int NHI, int T, bool THIN>
 __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ circs, const BatchItem* __restrict__ items,
                                              int nitems, int* __restrict__ counter, float* __restrict__ mpart,
                                              float* __restrict__ lpart) {
@@ -58,16 +58,16 @@ __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ ci
     __syncthreads();
     float lacc = 0.f;
     switch (C.n) {
-      case 3: batch_case<3, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 4: batch_case<4, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 5: batch_case<5, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 6: batch_case<6, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 7: batch_case<7, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 8: batch_case<8, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 9: batch_case<9, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 10: batch_case<10, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 11: batch_case<11, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
-      case 12: batch_case<12, NLO, NHI, T>(C, it, buf, slots, mslots, red, lacc); break;
+      case 3: batch_case<3, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 4: batch_case<4, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 5: batch_case<5, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 6: batch_case<6, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 7: batch_case<7, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 8: batch_case<8, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 9: batch_case<9, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 10: batch_case<10, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 11: batch_case<11, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
+      case 12: batch_case<12, NLO, NHI, T, THIN>(C, it, buf, slots, mslots, red, lacc); break;
       default: break;
     }
     __syncthreads();
@@ -95,7 +95,45 @@ __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ ci
   }
 }
 
-// Launches the class kernel of segment `seg` (see BatchSeg) on `grid` workgroups.
-hipError_t launch_batch_seg(int seg, int grid, size_t dyn, hipStream_t s, const BatchCirc* circs,
-                            const BatchItem* items, int nitems, int* counter, float* mpart, float* lpart);
+// Launches the class kernel of segment `seg` (see BatchSegment) on `grid` workgroups, and its dynamic LDS limit.
+template <bool THIN>
+hipError_t launch_batch_class(int seg, int grid, size_t dyn, hipStream_t s, const BatchCirc* circs, const BatchItem* items,
+                              int nitems, int* counter, float* mpart, float* lpart) {
+  switch (seg) {
+    case kSegLo:
+      hipLaunchKernelGGL((k_batch<3, kBatchSplit, 256, THIN>), dim3(grid), dim3(256), dyn, s, circs, items, nitems,
+                         counter, mpart, lpart);
+      break;
+    case kSegHi:
+      hipLaunchKernelGGL((k_batch<kBatchSplit + 1, 11, 256, THIN>), dim3(grid), dim3(256), dyn, s, circs, items,
+                         nitems, counter, mpart, lpart);
+      break;
+    case kSegBig:
+      hipLaunchKernelGGL((k_batch<kBatchBig, kBatchBig, 512, THIN>), dim3(grid), dim3(512), dyn, s, circs, items,
+                         nitems, counter, mpart, lpart);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+template <bool THIN>
+hipError_t prepare_batch_classes(int max_cols, int max_cols_big) {
+  const int lds = (int)batch_dyn_lds_bytes(256, max_cols), lds_big = (int)batch_dyn_lds_bytes(512, max_cols_big);
+  hipError_t e = hipSuccess;
+  if (max_cols > 0) {
+    e = hipFuncSetAttribute((const void*)k_batch<3, kBatchSplit, 256, THIN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_batch<kBatchSplit + 1, 11, 256, THIN>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  }
+  if (e == hipSuccess && max_cols_big > 0)
+    e = hipFuncSetAttribute((const void*)k_batch<kBatchBig, kBatchBig, 512, THIN>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_big);
+  return e;
+}
+// A batch with a thin circuit runs the kernels with thin layers (in a unit of their own, so that they compile
+// in parallel): with its branches the 32-circuit, 4..10-qubit batch of full layers takes 16.3 ms, without 15.8.
+hipError_t launch_batch_thin(int seg, int grid, size_t dyn, hipStream_t s, const BatchCirc* circs, const BatchItem* items,
+                             int nitems, int* counter, float* mpart, float* lpart);
+hipError_t prepare_batch_thin(int max_cols, int max_cols_big);
 }  // namespace qp

@@ -470,6 +470,7 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   a.P = P;
   a.ntiles = (int)((P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
   a.n_gates = F;
+  a.thin = c->hp.thin;
   a.n_fused = fwd ? 0 : F;
   a.out = out;
   a.tan = tan;

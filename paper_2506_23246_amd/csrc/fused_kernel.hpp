@@ -332,16 +332,21 @@ __device__ __forceinline__ Phase load_phase(const float4* __restrict__ tab) {   
   return P;
 }
 
-// Rotations of statevector S: the positions reached in place, then the swap slots.
+// Rotations of statevector S: the positions reached in place, then the swap slots.  has: the layer's flags (in
+// the kernels of circuits that are not thin all positions, known to the compiler).
 template <int N, int S>
-__device__ __forceinline__ void rot_base(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
+__device__ __forceinline__ void rot_base(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, int has) {
   rot_reg<0, S>(sr, si, K.t[0]);
   rot_reg<1, S>(sr, si, K.t[1]);
   rot_reg<2, S>(sr, si, K.t[2]);
-  if constexpr (N > 3) rot_lane<0, S>(sr, si, K.t[3]);
-  if constexpr (N > 4) rot_lane<1, S>(sr, si, K.t[4]);
-  if constexpr (N > 5) rot_lane<2, S>(sr, si, K.t[5]);
-  if constexpr (N > 6) rot_lane<3, S>(sr, si, K.t[6]);
+  if (N > 3 && (has & kSweepLane0)) {
+    if constexpr (N > 3) rot_lane<0, S>(sr, si, K.t[3]);
+  }
+  if (N > 4 && (has & kSweepLanes)) {
+    if constexpr (N > 4) rot_lane<1, S>(sr, si, K.t[4]);
+    if constexpr (N > 5) rot_lane<2, S>(sr, si, K.t[5]);
+    if constexpr (N > 6) rot_lane<3, S>(sr, si, K.t[6]);
+  }
 }
 template <int N, int S>
 __device__ __forceinline__ void swap_all(float (&sr)[8][8], float (&si)[8][8]) {
@@ -362,19 +367,13 @@ __device__ __forceinline__ void rot_wave(float (&sr)[8][8], float (&si)[8][8], c
 // Forward: phase and rotations in place, then the swap slots (the state ends in the layer's mapping
 // before the wave exchange).
 template <int N, int S>
-__device__ __forceinline__ void fwd_base(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P) {
+__device__ __forceinline__ void layer_fwd(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P, int has) {
   mul_phase<S, false>(sr, si, P.c, P.s);
-  rot_base<N, S>(sr, si, K);
-}
-template <int N, int S>
-__device__ __forceinline__ void fwd_slots(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K) {
-  swap_all<N, S>(sr, si);
-  rot_slots<N, S>(sr, si, K);
-}
-template <int N, int S>
-__device__ __forceinline__ void layer_fwd(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P) {
-  fwd_base<N, S>(sr, si, K, P);
-  fwd_slots<N, S>(sr, si, K);
+  rot_base<N, S>(sr, si, K, has);
+  if (N > 7 && (has & kSweepSlots)) {
+    swap_all<N, S>(sr, si);
+    rot_slots<N, S>(sr, si, K);
+  }
   sched_cut();
 }
 
@@ -419,28 +418,32 @@ __device__ __forceinline__ void wave_stat(const float (&sr)[8][8], const float (
 // commute, so each statistic may be taken with any of the others pulled back or not; only the cosines
 // left out so far scale it, which the gradient kernel puts back (gpar).
 template <int N, int C, bool PULL>
-__device__ __forceinline__ void adj_rot(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, Stats<N>& Q) {
-  if constexpr (N > 7) {
+__device__ __forceinline__ void adj_rot(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, Stats<N>& Q, int has) {
+  if (N > 7 && (has & kSweepSlots)) {
     if (PULL) { rot_slots<N, C>(sr, si, K); rot_slots<N, 4 + C>(sr, si, K); }
-    stat_reg<0, C>(sr, si, Q.x[7], Q.y[7]);
+    if constexpr (N > 7) stat_reg<0, C>(sr, si, Q.x[7], Q.y[7]);
     if constexpr (N > 8) stat_reg<1, C>(sr, si, Q.x[8], Q.y[8]);
-    pin_stats<N, 7, N < 9 ? N : 9>(Q, false);
+    if constexpr (N > 7) pin_stats<N, 7, N < 9 ? N : 9>(Q, false);
     swap_all<N, C>(sr, si); swap_all<N, 4 + C>(sr, si);
   }
   sched_cut();
-  if (PULL) { rot_base<N, C>(sr, si, K); rot_base<N, 4 + C>(sr, si, K); }
+  if (PULL) { rot_base<N, C>(sr, si, K, has); rot_base<N, 4 + C>(sr, si, K, has); }
   sched_cut();
 }
 template <int N, int C, bool PULL>
-__device__ __forceinline__ void adj_stat(float (&sr)[8][8], float (&si)[8][8], const Phase& P, Stats<N>& Q) {
+__device__ __forceinline__ void adj_stat(float (&sr)[8][8], float (&si)[8][8], const Phase& P, Stats<N>& Q, int has) {
   stat_reg<0, C>(sr, si, Q.x[0], Q.y[0]);
   stat_reg<1, C>(sr, si, Q.x[1], Q.y[1]);
   stat_reg<2, C>(sr, si, Q.x[2], Q.y[2]);
   sched_cut();
-  if constexpr (N > 3) stat_lane<0, C>(sr, si, Q.x[3], Q.y[3]);
-  if constexpr (N > 4) stat_lane<1, C>(sr, si, Q.x[4], Q.y[4]);
-  if constexpr (N > 5) stat_lane<2, C>(sr, si, Q.x[5], Q.y[5]);
-  if constexpr (N > 6) stat_lane<3, C>(sr, si, Q.x[6], Q.y[6]);
+  if (N > 3 && (has & kSweepLane0)) {
+    if constexpr (N > 3) stat_lane<0, C>(sr, si, Q.x[3], Q.y[3]);
+  }
+  if (N > 4 && (has & kSweepLanes)) {
+    if constexpr (N > 4) stat_lane<1, C>(sr, si, Q.x[4], Q.y[4]);
+    if constexpr (N > 5) stat_lane<2, C>(sr, si, Q.x[5], Q.y[5]);
+    if constexpr (N > 6) stat_lane<3, C>(sr, si, Q.x[6], Q.y[6]);
+  }
   stat_diag<C>(sr, si, Q.w);
   pin_stats<N, 0, N < 7 ? N : 7>(Q, true);
   sched_cut();
@@ -448,18 +451,20 @@ __device__ __forceinline__ void adj_stat(float (&sr)[8][8], float (&si)[8][8], c
   sched_cut();
 }
 template <int N, int C, bool PULL>
-__device__ __forceinline__ void layer_adj(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P, Stats<N>& Q) {
-  adj_rot<N, C, PULL>(sr, si, K, Q);
-  adj_stat<N, C, PULL>(sr, si, P, Q);
+__device__ __forceinline__ void layer_adj(float (&sr)[8][8], float (&si)[8][8], const Coef<N>& K, const Phase& P, Stats<N>& Q,
+                                          int has) {
+  adj_rot<N, C, PULL>(sr, si, K, Q, has);
+  adj_stat<N, C, PULL>(sr, si, P, Q, has);
 }
 
 // Adds the S_x and S_y of positions [P0, P1) to the wave's slots (two gates per reduction).
-template <int N, int P0, int P1>
+template <int N, int P0, int P1, bool THIN>
 __device__ __forceinline__ void flush_xy(CP<QSweep> L, const Stats<N>& Q, uint32_t v, float* __restrict__ slots, int F,
                                          int wave, int lane) {
 #pragma unroll
   for (int p = P0; p < P1; p += 2) {
     const int q = p + 1 < P1 ? p + 1 : p;
+    if (THIN && L->gate[p] < 0 && L->gate[q] < 0) continue;
     auto ys = [&](int k) { return k >= 3 && k < 7 && !((v >> (k - 3)) & 1u) ? -Q.y[k] : Q.y[k]; };
     const float v4[4] = {Q.x[p], ys(p), Q.x[q], ys(q)};
     const float s = wave_reduce_scatter4(v4);
@@ -1246,7 +1251,7 @@ __device__ __forceinline__ void packed_state(float (&sr)[8][8], float (&si)[8][8
 // sums per gate: 12 qubits x 8 layers, 262144 points, 284 -> 229 ms (layers in the adjoint alone; 194 ms
 // both ways, not run: see the forward by rounds); forward and backward of 7 qubits x 4 layers, 64000
 // points, layers both ways, 1424 -> 833 us.
-template <int N, int T, int EXS, int MODE, bool EG = false>
+template <int N, int T, int EXS, int MODE, bool EG = false, bool THIN = false>
 __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2* __restrict__ buf,
                                            float* __restrict__ slots, float* __restrict__ mslots,
                                            float* __restrict__ red, float& lacc) {
@@ -1282,6 +1287,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
   const uint32_t rvb = (uint32_t)(wave * 4096 + lane * 8);
   const float4* __restrict__ ptab = reinterpret_cast<const float4*>(a.ptab) + u * 4;   // this thread's entries, per layer
   auto phase_of = [&](int l) { return load_phase(ptab + (size_t)(l - L0) * (DIM / 2)); };
+  auto positions = [&](CP<QSweep> L) { return THIN ? L->flags : L->flags | kSweepAll; };
   auto lane_of = [&](int l) { return slanes[(size_t)l * TP + u]; };
   // loss weights: 1/P for the mean over all points, 1/N_vac and 1/N_diel for the split loss
   float w_all = 1.f, w_vac = 1.f, w_diel = 1.f;
@@ -1453,10 +1459,11 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
           const Addr A = xchg_addr(L->woff, L->roff, w.x ^ pb8, w.y ^ pb8);
           exchange_wave<T, 0, 4>(sr, si, buf, A);
         }
-        layer_fwd<N, 0>(sr, si, K, P);
-        layer_fwd<N, 1>(sr, si, K, P);
-        layer_fwd<N, 2>(sr, si, K, P);
-        layer_fwd<N, 3>(sr, si, K, P);
+        const int has = positions(L);
+        layer_fwd<N, 0>(sr, si, K, P, has);
+        layer_fwd<N, 1>(sr, si, K, P, has);
+        layer_fwd<N, 2>(sr, si, K, P, has);
+        layer_fwd<N, 3>(sr, si, K, P, has);
       }
     } else if constexpr (EXS == 4) {
       // Statevectors {0, 1} go through planes 0 and 1, {2, 3} through planes 2 and 3: between two
@@ -1473,7 +1480,8 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
       }
       for (int l = L0; l < L1; ++l) {
         CP<QSweep> L = sweeps + l;
-        const bool moves = L->flags & kSweepXchg;
+        const int has = positions(L);
+        const bool moves = has & kSweepXchg, wave_bits = has & kSweepWave;
         const Phase P = phase_of(l);
         const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, false);
         if (moves) {
@@ -1481,33 +1489,38 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
           xread<T, 0, 0>(sr, si, buf, A.r); xread<T, 1, 1>(sr, si, buf, A.r);
           xwrite<T, 2, 2>(sr, si, buf, A.w); xwrite<T, 3, 3>(sr, si, buf, A.w);
         }
-        layer_fwd<N, 0>(sr, si, K, P);
-        layer_fwd<N, 1>(sr, si, K, P);
+        layer_fwd<N, 0>(sr, si, K, P, has);
+        layer_fwd<N, 1>(sr, si, K, P, has);
         if (moves) {
           __syncthreads();
           xread<T, 2, 2>(sr, si, buf, A.r); xread<T, 3, 3>(sr, si, buf, A.r);
         }
-        wwrite<N, T, 0, 0>(sr, si, buf, wvb); wwrite<N, T, 1, 1>(sr, si, buf, wvb);
-        layer_fwd<N, 2>(sr, si, K, P);
-        layer_fwd<N, 3>(sr, si, K, P);
-        __syncthreads();
-        wread<N, T, 0, 0>(sr, si, buf, rvb); wread<N, T, 1, 1>(sr, si, buf, rvb);
-        wwrite<N, T, 2, 2>(sr, si, buf, wvb); wwrite<N, T, 3, 3>(sr, si, buf, wvb);
-        rot_wave<N, 0>(sr, si, K); rot_wave<N, 1>(sr, si, K);
-        __syncthreads();
-        wread<N, T, 2, 2>(sr, si, buf, rvb); wread<N, T, 3, 3>(sr, si, buf, rvb);
+        if (wave_bits) {
+          wwrite<N, T, 0, 0>(sr, si, buf, wvb); wwrite<N, T, 1, 1>(sr, si, buf, wvb);
+        }
+        layer_fwd<N, 2>(sr, si, K, P, has);
+        layer_fwd<N, 3>(sr, si, K, P, has);
+        if (wave_bits) {
+          __syncthreads();
+          wread<N, T, 0, 0>(sr, si, buf, rvb); wread<N, T, 1, 1>(sr, si, buf, rvb);
+          wwrite<N, T, 2, 2>(sr, si, buf, wvb); wwrite<N, T, 3, 3>(sr, si, buf, wvb);
+          rot_wave<N, 0>(sr, si, K); rot_wave<N, 1>(sr, si, K);
+          __syncthreads();
+          wread<N, T, 2, 2>(sr, si, buf, rvb); wread<N, T, 3, 3>(sr, si, buf, rvb);
+        }
         if (l + 1 < L1 && (sweeps[l + 1].flags & kSweepXchg)) {
           addr(l + 1);
           xwrite<T, 0, 0>(sr, si, buf, A.w); xwrite<T, 1, 1>(sr, si, buf, A.w);
         }
-        rot_wave<N, 2>(sr, si, K); rot_wave<N, 3>(sr, si, K);
+        if (wave_bits) { rot_wave<N, 2>(sr, si, K); rot_wave<N, 3>(sr, si, K); }
       }
     } else {
       for (int l = L0; l < L1; ++l) {
         CP<QSweep> L = sweeps + l;
         const Phase P = phase_of(l);
         const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, false);
-        const bool moves = L->flags & kSweepXchg;
+        const int has = positions(L);
+        const bool moves = has & kSweepXchg;
         const uint4 w = lane_of(l);
         const Addr A = xchg_addr(L->woff, L->roff, w.x ^ pb8, w.y ^ pb8);
         auto pair = [&](auto c) {
@@ -1518,13 +1531,15 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
             xread<T, S, 0>(sr, si, buf, A.r); xread<T, S + 1, 1>(sr, si, buf, A.r);
             __syncthreads();
           }
-          layer_fwd<N, S>(sr, si, K, P);
-          layer_fwd<N, S + 1>(sr, si, K, P);
-          wwrite<N, T, S, 0>(sr, si, buf, wvb); wwrite<N, T, S + 1, 1>(sr, si, buf, wvb);
-          __syncthreads();
-          wread<N, T, S, 0>(sr, si, buf, rvb); wread<N, T, S + 1, 1>(sr, si, buf, rvb);
-          __syncthreads();
-          rot_wave<N, S>(sr, si, K); rot_wave<N, S + 1>(sr, si, K);
+          layer_fwd<N, S>(sr, si, K, P, has);
+          layer_fwd<N, S + 1>(sr, si, K, P, has);
+          if (has & kSweepWave) {
+            wwrite<N, T, S, 0>(sr, si, buf, wvb); wwrite<N, T, S + 1, 1>(sr, si, buf, wvb);
+            __syncthreads();
+            wread<N, T, S, 0>(sr, si, buf, rvb); wread<N, T, S + 1, 1>(sr, si, buf, rvb);
+            __syncthreads();
+            rot_wave<N, S>(sr, si, K); rot_wave<N, S + 1>(sr, si, K);
+          }
         };
         pair(IntC<0>{});
         pair(IntC<2>{});
@@ -1757,11 +1772,12 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
         if (PULL) P = phase_of(l);
         const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, true);
         clear(Q);
-        layer_adj<N, 0, PULL>(sr, si, K, P, Q);
-        layer_adj<N, 1, PULL>(sr, si, K, P, Q);
-        layer_adj<N, 2, PULL>(sr, si, K, P, Q);
-        layer_adj<N, 3, PULL>(sr, si, K, P, Q);
-        flush_xy<N, 0, N>(L, Q, v, slots, F, wave, lane);
+        const int has = positions(L);
+        layer_adj<N, 0, PULL>(sr, si, K, P, Q, has);
+        layer_adj<N, 1, PULL>(sr, si, K, P, Q, has);
+        layer_adj<N, 2, PULL>(sr, si, K, P, Q, has);
+        layer_adj<N, 3, PULL>(sr, si, K, P, Q, has);
+        flush_xy<N, 0, N, THIN>(L, Q, v, slots, F, wave, lane);
         flush_z<N>(L, Q.w, v, slots, mom_of(L), F, wave, lane);
         if (PULL && (L->flags & kSweepXchg) && (l > 0 || EG)) {   // (nothing follows the first layer else)
           const uint4 w = lane_of(l);
@@ -1797,16 +1813,18 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
       auto enter = [&](int l, auto pull) {
         constexpr bool PULL = decltype(pull)::value != 0;
         const Coef<N> K = load_coef<N, 9, N>(tcoef + l * kTC, v, true);
+        const bool wave_bits = positions(sweeps + l) & kSweepWave;
         clear<N, 9, N>(Q);
         auto step = [&](auto c) {
           constexpr int C = decltype(c)::value;
           if (moves) xstep(c);
+          if (!wave_bits) return;
           if (PULL) wave_rot<N, C>(sr, si, K);
           wave_stat<N, C>(sr, si, Q);
           if constexpr (C == 3) wpair(IntC<0>{});
         };
         step(IntC<0>{}); step(IntC<1>{}); step(IntC<2>{}); step(IntC<3>{});
-        flush_xy<N, 9, N>(sweeps + l, Q, v, slots, F, wave, lane);
+        flush_xy<N, 9, N, THIN>(sweeps + l, Q, v, slots, F, wave, lane);
       };
       auto rest = [&](int l, auto pull) {
         constexpr bool PULL = decltype(pull)::value != 0;
@@ -1814,16 +1832,19 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
         Phase P{};
         if (PULL) P = phase_of(l);
         const Coef<N> K = load_coef<N, 0, 9>(tcoef + l * kTC, v, true);
+        const int has = positions(L);
         clear<N, 0, 9>(Q);
         auto step = [&](auto c) {
           constexpr int C = decltype(c)::value, PL = 2 * (C & 1);
-          __syncthreads();
-          wread<N, T, C, PL>(sr, si, buf, rvb); wread<N, T, 4 + C, PL + 1>(sr, si, buf, rvb);
-          if constexpr (C < 3) wpair(IntC<C + 1>{});
-          layer_adj<N, C, PULL>(sr, si, K, P, Q);
+          if (has & kSweepWave) {
+            __syncthreads();
+            wread<N, T, C, PL>(sr, si, buf, rvb); wread<N, T, 4 + C, PL + 1>(sr, si, buf, rvb);
+            if constexpr (C < 3) wpair(IntC<C + 1>{});
+          }
+          layer_adj<N, C, PULL>(sr, si, K, P, Q, has);
         };
         step(IntC<0>{}); step(IntC<1>{}); step(IntC<2>{}); step(IntC<3>{});
-        flush_xy<N, 0, 9>(L, Q, v, slots, F, wave, lane);
+        flush_xy<N, 0, 9, THIN>(L, Q, v, slots, F, wave, lane);
         flush_z<N>(L, Q.w, v, slots, mom_of(L), F, wave, lane);
         moves = PULL && (L->flags & kSweepXchg) && (l > 0 || EG);
         if (moves) {
@@ -1850,19 +1871,22 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
         Phase P{};
         if (PULL) P = phase_of(l);
         const Coef<N> K = load_coef<N>(tcoef + l * kTC, v, true);
-        const bool moves = PULL && (L->flags & kSweepXchg) && (l > 0 || EG);
+        const int has = positions(L);
+        const bool moves = PULL && (has & kSweepXchg) && (l > 0 || EG);
         const uint4 w = lane_of(l);
         const Addr A = xchg_addr(L->bwoff, L->broff, w.z ^ pb8, w.w ^ pb8);
         clear(Q);
         auto pair = [&](auto c) {
           constexpr int C = decltype(c)::value;
-          if (PULL) wave_rot<N, C>(sr, si, K);
-          wave_stat<N, C>(sr, si, Q);
-          wwrite<N, T, C, 0>(sr, si, buf, wvb); wwrite<N, T, 4 + C, 1>(sr, si, buf, wvb);
-          __syncthreads();
-          wread<N, T, C, 0>(sr, si, buf, rvb); wread<N, T, 4 + C, 1>(sr, si, buf, rvb);
-          __syncthreads();
-          layer_adj<N, C, PULL>(sr, si, K, P, Q);
+          if (has & kSweepWave) {
+            if (PULL) wave_rot<N, C>(sr, si, K);
+            wave_stat<N, C>(sr, si, Q);
+            wwrite<N, T, C, 0>(sr, si, buf, wvb); wwrite<N, T, 4 + C, 1>(sr, si, buf, wvb);
+            __syncthreads();
+            wread<N, T, C, 0>(sr, si, buf, rvb); wread<N, T, 4 + C, 1>(sr, si, buf, rvb);
+            __syncthreads();
+          }
+          layer_adj<N, C, PULL>(sr, si, K, P, Q, has);
           if (moves) {
             xwrite<T, C, 0>(sr, si, buf, A.w); xwrite<T, 4 + C, 1>(sr, si, buf, A.w);
             __syncthreads();
@@ -1871,7 +1895,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
           }
         };
         pair(IntC<0>{}); pair(IntC<1>{}); pair(IntC<2>{}); pair(IntC<3>{});
-        flush_xy<N, 0, N>(L, Q, v, slots, F, wave, lane);
+        flush_xy<N, 0, N, THIN>(L, Q, v, slots, F, wave, lane);
         flush_z<N>(L, Q.w, v, slots, mom_of(L), F, wave, lane);
       };
       for (int l = L1 - 1; l >= L0; --l) layer(l, IntC<1>{});
@@ -1890,7 +1914,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
 }
 
 // ---- the fused kernel: a persistent grid walks the tiles ------------------------------------
-template <int N, int T, int EXS, int MODE, bool EG = false>
+template <int N, int T, int EXS, int MODE, bool EG = false, bool THIN = false>
 __global__ __launch_bounds__(T, mode_fwd_only(MODE) ? fwd_waves(N, EXS) : 2) void k_fused(FusedArgs a) {
   constexpr int WAVES = T / 64;
   constexpr int PLANE = T * 8;
@@ -1923,7 +1947,7 @@ __global__ __launch_bounds__(T, mode_fwd_only(MODE) ? fwd_waves(N, EXS) : 2) voi
     t_step = gridDim.x / kXcd;
   }
   for (int tile = t_begin; tile < t_end; tile += t_step)
-    fused_tile<N, T, EXS, MODE, EG>(a, tile, buf, slots, mslots, red, lacc);
+    fused_tile<N, T, EXS, MODE, EG, THIN>(a, tile, buf, slots, mslots, red, lacc);
   if (mode_fwd_only(MODE)) return;
   // ---------------- per-workgroup partials (fixed order) -----------------------------------
   __syncthreads();
@@ -1953,10 +1977,10 @@ __global__ __launch_bounds__(T, mode_fwd_only(MODE) ? fwd_waves(N, EXS) : 2) voi
 }
 
 
-template <int N, int EXS, int MODE, bool EG = false>
+template <int N, int EXS, int MODE, bool EG, bool THIN>
 hipError_t launch_one(const FusedArgs& a, int grid, size_t dyn, hipStream_t st) {
   constexpr int T = fused_wg_threads(N);
-  auto kern = k_fused<N, T, EXS, MODE, EG>;
+  auto kern = k_fused<N, T, EXS, MODE, EG, THIN>;
   // the attribute is set once per device (and raised when a larger size comes)
   static size_t attr_bytes[kMaxDevices] = {};
   int dev = 0;
@@ -1973,16 +1997,26 @@ hipError_t launch_one(const FusedArgs& a, int grid, size_t dyn, hipStream_t st) 
 }
 
 // Entry point of one per-N unit.  exs: exchange planes (2 or 4) from 10 qubits on; below, an exchange
-// stays inside a wave and one kernel serves both.  Input gradients take two planes (4 layers, 2^23 amplitudes,
-// adjoint: 10 qubits 1140 us with four planes, 997 with two; 11: 1230, 1053; 12: 1278, 1181; with the loss 1251 and
-// 1217, 1330 and 1227, 1506 and 1397; 32 points 126 and 119, 135 and 125, 170 and 166): with four planes their
-// kernels spill 160 to 330 registers.
+// stays inside a wave and one kernel serves both.  Thin circuits have kernels of their own, with branches around
+// what a layer leaves out (24 layers, adjoint: 3 of 9 qubits rotated 806 -> 412 us, 3 of 11 1007 -> 454, 4 of 12 1111 -> 599);
+// in one kernel with the rest, the branches cost full layers 1 to 6 % from 7 qubits on.
+// Input gradients take two planes (4 layers, 2^23 amplitudes, adjoint: 10 qubits 1140 us with four planes, 997 with
+// two; 11: 1230, 1053; 12: 1278, 1181; with the loss 1251 and 1217, 1330 and 1227, 1506 and 1397; 32 points 126 and
+// 119, 135 and 125, 170 and 166): with four planes their kernels spill 160 to 330 registers.
+template <int N, int EXS, int MODE, bool EG>
+hipError_t launch_kind(const FusedArgs& a, int grid, size_t dyn, hipStream_t st) {
+  constexpr bool kThin = N >= kThinQubits && MODE != kModeFieldsPk;   // (kModeFieldsPk runs no layers)
+  if constexpr (kThin) {
+    if (a.thin) return launch_one<N, EXS, MODE, EG, true>(a, grid, dyn, st);
+  }
+  return launch_one<N, EXS, MODE, EG, false>(a, grid, dyn, st);
+}
 template <int N, int MODE, bool EG = false>
 hipError_t launch_mode(const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st) {
   if constexpr (N >= 10 && !EG) {
-    if (exs == 4) return launch_one<N, 4, MODE, EG>(a, grid, dyn, st);
+    if (exs == 4) return launch_kind<N, 4, MODE, EG>(a, grid, dyn, st);
   }
-  return launch_one<N, 2, MODE, EG>(a, grid, dyn, st);
+  return launch_kind<N, 2, MODE, EG>(a, grid, dyn, st);
 }
 template <int N>
 hipError_t launch_fused_n(int mode, const FusedArgs& a, int grid, int exs, size_t dyn, hipStream_t st) {

@@ -502,6 +502,7 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
     hp->terms.clear();
     hp->tlanes.clear();
     hp->sweep_first = 0;
+    hp->thin = false;
     for (int i = 0; i < hp->m; ++i) hp->zmask[i] = 1u << (n - 1 - hp->out_qubits[i]);
     goto image;
   }
@@ -732,6 +733,18 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
   int32_t cur[16];                 // mapping of the state as it stands
   for (int k = 0; k < 16; ++k) cur[k] = k < n ? k : 0;
   for (int k = 0; k < 16; ++k) hp->etpos[k] = hp->gtpos[k] = cur[k];
+  // Thin circuits: layers leave positions out, if that comes to four layers' worth and an eighth of all.  What a
+  // layer takes: the register bits in any case, the first lane bit, the other three, the slots, the wave bits.
+  int left_out = 0, layers = 0;
+  for (size_t si = 1; si < stages.size(); ++si) {
+    if (!stages[si].rot) continue;
+    const int k = (int)stages[si].fused_of_qubit.size();
+    ++layers;
+    const int in_use = k <= 4 ? std::max(k, 3) : std::min(n, k <= 7 ? 7 : (k <= 9 ? 9 : n));
+    left_out += n - in_use + (in_use <= 7 ? std::min(n, 9) - std::min(n, 7) : 0);   // (a slot costs two lane positions)
+  }
+  const bool thin = n >= kThinQubits && left_out >= 4 * n && 8 * left_out >= n * layers;
+  hp->thin = thin;
   const Stage* ent = nullptr;      // entanglers since the last rotation stage
   int nph = 0;                     // CRZ runs so far (numbered as hp->phases)
   for (size_t si = 0; si < stages.size(); ++si) {
@@ -760,15 +773,28 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
       for (int g = 0; g < ps.ngates; ++g) hp->phase_gates[ps.gate0 + g].layer = (int)hp->sweeps.size();
     }
     // input mapping: after an exchange a free choice (the qubits with gates first), else the state's
-    // mapping as it stands
-    int32_t tin[16];
-    for (int k = 0; k < 16; ++k) tin[k] = cur[k];
-    if (moves || head) {
-      int c = 0;
-      for (int pass = 0; pass < 2; ++pass)
-        for (int p = 0; p < n; ++p)
-          if ((s.fused_of_qubit.count(n - 1 - p) != 0) == (pass == 0)) tin[c++] = p;
-    }
+    // mapping as it stands, unless an exchange spares the layer three positions,
+    // or from 10 qubits on, where waves exchange in any case, the slots
+    int32_t tin[16], first[16];
+    int c = 0;
+    for (int pass = 0; pass < 2; ++pass)
+      for (int p = 0; p < n; ++p)
+        if ((s.fused_of_qubit.count(n - 1 - p) != 0) == (pass == 0)) first[c++] = p;
+    auto positions = [&](const int32_t* t) {
+      int g = 0;
+      for (int k = 0; k < n; ++k)
+        if (s.fused_of_qubit.count(n - 1 - t[k])) g |= kSweepPos << k;
+      return g;
+    };
+    auto takes = [&](int g) {   // besides the register bits
+      return ((g & kSweepWave) ? n - 9 : 0) + ((g & kSweepSlots) ? (n >= 10 ? 3 : std::min(n, 9) - 7) : 0) +
+             ((g & kSweepLanes) ? std::min(n, 7) - 4 : 0) + ((g & kSweepLane0) ? 1 : 0);
+    };
+    // (CZ rings, outputs alone and adjoint, us: 10 qubits, 7 gates, 89 and 787 without, 89 and 708 with, 5 gates 831
+    // and 703; but 9 qubits, 6 gates, the two slots, 65 -> 73, 8 qubits 59 -> 72, 11 and 12 qubits, 8 gates, 3 % and 7 %)
+    moves = moves || (thin && !head && takes(positions(first)) + 3 <= takes(positions(cur)));
+    for (int k = 0; k < 16; ++k) tin[k] = k < n && (moves || head) ? first[k] : cur[k];
+    const int has = thin && !head ? positions(tin) : kSweepAll;   // (input gradients take all sums of the head)
     for (int k = 0; k < kPos; ++k) L.gate[k] = -1;
     for (int k = 0; k < n; ++k) {
       auto it = s.fused_of_qubit.find(n - 1 - tin[k]);
@@ -780,9 +806,11 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
     }
     int32_t tout[16];
     for (int k = 0; k < 16; ++k) tout[k] = tin[k];
-    for (int i = 0; i < nsl; ++i) std::swap(tout[i], tout[7 + i]);
-    for (int i = 0; i < nw; ++i) std::swap(tout[i], tout[9 + i]);
-    L.flags = moves && !head ? kSweepXchg : 0;
+    if (has & kSweepSlots)
+      for (int i = 0; i < nsl; ++i) std::swap(tout[i], tout[7 + i]);
+    if (has & kSweepWave)
+      for (int i = 0; i < nw; ++i) std::swap(tout[i], tout[9 + i]);
+    L.flags = has | (moves && !head ? kSweepXchg : 0);
     const size_t l0 = hp->slanes.size();
     hp->slanes.resize(l0 + TP, QSweepLane{});
     if (L.flags & kSweepXchg) {
@@ -894,6 +922,7 @@ image:
   h.off_pcsr_idx = (int)off; off = align16(off + sizeof(int32_t) * std::max<size_t>(1, hp->pcsr_idx.size()));
   h.n_sweeps = hp->fused_ok ? (int)hp->sweeps.size() : 0;
   h.sweep_first = hp->sweep_first;
+  h.thin = hp->thin ? 1 : 0;
   h.off_sweeps = (int)off; off = align16(off + sizeof(QSweep) * hp->sweeps.size());
   h.off_slanes = (int)off; off = align16(off + sizeof(QSweepLane) * hp->slanes.size());
   h.off_terms = (int)off; off = align16(off + sizeof(uint32_t) * std::max<size_t>(2, hp->terms.size()));

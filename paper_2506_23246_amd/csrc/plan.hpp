@@ -40,6 +40,7 @@ struct HostPlan {
   QTurn turn = {};
   std::vector<uint32_t> tlanes;
   int sweep_first = 0;
+  bool thin = false;                   // layers leave positions out
   int32_t hgate[16], etpos[16], ftpos[16], gtpos[16];
   // dense-block plan (MFMA path)
   bool dense_ok = false;

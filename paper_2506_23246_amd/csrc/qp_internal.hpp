@@ -126,7 +126,7 @@ static_assert(sizeof(QFused) == 48, "QFused layout");
 constexpr int kPos = 12;
 struct alignas(16) QSweep {
   int32_t gate[kPos];       // fused gate at each position (-1: none)
-  int32_t flags;            // kSweepXchg: an index-map exchange comes first
+  int32_t flags;            // kSweepXchg: an index-map exchange comes first; kSweepPos ..: positions of gates
   int32_t phase;            // CRZ phase stage in front of the layer, or -1
   int32_t term0, nterms;    // CZ terms in front of the layer: masks [term0, term0 + nterms) of the term list
   int32_t tin[16], tout[16];
@@ -136,6 +136,12 @@ struct alignas(16) QSweep {
 };
 static_assert(sizeof(QSweep) == 384, "QSweep layout");
 constexpr int kSweepXchg = 1;
+// Thin circuits (QPlanDev::thin): positions a layer has gates at.  The others are neither rotated nor summed,
+// and slots or wave bits with no gate at all are not swapped.  Any other circuit has all of them set.
+constexpr int kThinQubits = 5;   // fewest qubits of a thin circuit
+constexpr int kSweepPos = 256;   // position 0; 1 .. follow
+constexpr int kSweepLane0 = kSweepPos << 3, kSweepLanes = 7 * (kSweepPos << 4), kSweepSlots = 3 * (kSweepPos << 7),
+              kSweepWave = 7 * (kSweepPos << 9), kSweepAll = 0xfff * kSweepPos;
 // Per thread of a point and layer: LDS byte bases of the forward and reverse exchange.
 struct alignas(16) QSweepLane {
   uint32_t fwb, frb, bwb, brb;
@@ -261,6 +267,7 @@ struct alignas(16) QPlanDev {
   int32_t gtpos[16];                // mapping at the end of the adjoint
   int32_t off_turn;                 // QTurn
   int32_t off_tlanes;               // uint32[2^(n-3)][2]
+  int32_t thin;                     // 1: layers leave positions out (kernels of their own)
 };
 
 }  // namespace qp
