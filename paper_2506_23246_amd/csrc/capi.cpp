@@ -429,11 +429,9 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   int* counts = reinterpret_cast<int*>(w + L.counts);
   const int NM = n_moments(c);
   const SweepTabs tabs = sweep_tabs(c, w + L.tabs);
-  const bool few = mode == kModeFwdPk && few_by_rounds(n, (int)c->hp.sweeps.size(), P, NM);
-  if (few) mode = kModeFieldsPk;
   hipError_t e = hipSuccess;
   if (!tabs_formed)
-    e = launch_sweep_tables(sweep_plan(c), NM > 0, params, tabs, (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st, few);
+    e = launch_sweep_tables(sweep_plan(c), NM > 0, params, tabs, (flags & QP_FLAG_GATES_FP32) ? 1 : 0, st);
   if (e != hipSuccess) return hipcheck(ctx, e, "gate table");
   const float* ang = angles;
   const float* jc = jac;

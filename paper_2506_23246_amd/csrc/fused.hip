@@ -187,9 +187,8 @@ hipError_t launch_fused(int n, int mode, const FusedArgs& a, int grid, int exs, 
 }
 
 hipError_t launch_sweep_tables(const SweepPlan& plan, bool phases, const float* params, const SweepTabs& t, int fp32,
-                               hipStream_t st, bool gates_only) {
-  const int blocks = gates_only ? 1 : sweep_table_blocks(plan.n, plan.n_sweeps - plan.sweep_first, phases);
-  hipLaunchKernelGGL(k_sweep_tables, dim3(blocks), dim3(kTabThreads), 0, st, plan, params, t, fp32);
+                               hipStream_t st) {
+  hipLaunchKernelGGL(k_sweep_tables, dim3(sweep_table_blocks(plan.n, plan.n_sweeps - plan.sweep_first, phases)), dim3(kTabThreads), 0, st, plan, params, t, fp32);
   return hipGetLastError();
 }
 

@@ -75,9 +75,8 @@ hipError_t launch_fused(int n, int mode, const FusedArgs& a, int grid, int exs, 
 QP_HD inline int sweep_table_blocks(int n, int layers, bool phases) {
   return 1 + (layers + 1) * ((1 << n) > 256 ? (1 << n) / 256 : 1) + (phases ? 1 : 0);
 }
-// gates_only: the gate matrices alone (calls that run no layer).
 hipError_t launch_sweep_tables(const SweepPlan& plan, bool phases, const float* params, const SweepTabs& t, int fp32,
-                               hipStream_t st, bool gates_only = false);
+                               hipStream_t st);
 hipError_t launch_rff(const QPlanDev* plan, const float* points, long long P, float* angles, float* jac, hipStream_t st);
 hipError_t launch_count(const float* points, long long P, float x_if, int* counts, hipStream_t st);
 hipError_t launch_reduce(const float* mpart, int nblk, int ncol, const float* lpart, double* m64, double* loss, hipStream_t st);

@@ -205,13 +205,6 @@ QP_HD inline constexpr int fwd_waves(int n, int exs) { return n < 10 ? 4 : (n < 
 // Modes whose results enter an FP64 loss: their forward runs the rounds.
 QP_HD inline constexpr bool mode_rounds(int mode) { return mode == kModeMaxwell || mode == kModeTotal || mode == kModeFieldsPk; }
 
-// Outputs alone of a shallow 3-qubit circuit: by the rounds, which need the gate matrices alone (2.9 us against
-// 4.2 for all tables; the kernels are level).  2 layers, 64 / 262144 points: 14.9 / 17.8 us by layers, 13.8 /
-// 17.3 by rounds; 6 layers: 20.7 / 24.0 and 21.2 / 25.4; 1 layer, 2^20 points: 23.7 and 24.8.
-QP_HD inline constexpr bool few_by_rounds(int n, int layers, int64_t P, int n_mom) {
-  return n == 3 && layers <= 3 && n_mom == 0 && P <= 262144;
-}
-
 // Dense 2^5 blocks (MFMA path): a contiguous run of gates acting on at most five qubits.
 constexpr int kDenseK = 5;
 struct alignas(16) QDenseGate {
