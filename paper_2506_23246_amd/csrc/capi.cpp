@@ -451,7 +451,7 @@ qp_status qp::run_fused(qp_ctx* ctx, const qp_circuit* c, int mode, const float*
   int grid = fused_grid(ctx, c, P_slots);
   if (fwd && !c->launch_set && n < 12) {   // as many workgroups as the registers hold (4 waves each)
     exs = 2;
-    grid = (int)std::min<int64_t>((int64_t)ctx->cu_count * fwd_waves(n, exs), (P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
+    grid = (int)std::min<int64_t>((int64_t)ctx->cu_count * fwd_waves(n, exs, mode), (P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));
   }
   if (grid_override > 0)
     grid = (int)std::min<int64_t>(grid_override, (P_slots + fused_points_per_tile(n) - 1) / fused_points_per_tile(n));

@@ -1915,7 +1915,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int tile, float2*
 
 // ---- the fused kernel: a persistent grid walks the tiles ------------------------------------
 template <int N, int T, int EXS, int MODE, bool EG = false, bool THIN = false>
-__global__ __launch_bounds__(T, mode_fwd_only(MODE) ? fwd_waves(N, EXS) : 2) void k_fused(FusedArgs a) {
+__global__ __launch_bounds__(T, mode_fwd_only(MODE) ? fwd_waves(N, EXS, MODE) : 2) void k_fused(FusedArgs a) {
   constexpr int WAVES = T / 64;
   constexpr int PLANE = T * 8;
   // Exchange planes in static LDS (their address is a link-time constant, so every access is

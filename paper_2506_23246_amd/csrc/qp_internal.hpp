@@ -160,7 +160,7 @@ QP_HD inline constexpr uint32_t sweep_thread(uint32_t u, int n) { return n >= 6 
 // Lane XOR that flips thread bit k.
 QP_HD inline constexpr uint32_t sweep_xor(int k) { return k == 2 ? 7u : 1u << k; }
 // Exchange planes a fused kernel allocates: up to 9 qubits an exchange stays inside a wave and one
-// plane serves all statevectors (two: the rounds' exchange and the input gradients); else exs.
+// plane serves all statevectors (two: the rounds' exchange, which hands two over at a time); else exs.
 QP_HD inline constexpr int sweep_planes(int n, int exs, bool two) { return n >= 10 ? exs : (two ? 2 : 1); }
 constexpr int kTC = 16;            // floats per layer of the coefficient table (kPos used)
 constexpr int kGP = 4;             // doubles per gate: cos c, sin c, scale of S_x and S_y, scale of S_z (sign: X mask)
@@ -197,11 +197,19 @@ QP_HD inline constexpr int phase_terms(int n) { return n + n * (n - 1) / 2; }
 enum Mode : int { kModeFwd = 0, kModeMaxwell = 1, kModeVjp = 2, kModeFwdPk = 3, kModeVjpPk = 4, kModeTotal = 5, kModeFieldsPk = 6 };
 QP_HD inline constexpr bool mode_packed(int mode) { return mode == kModeFwdPk || mode == kModeVjpPk || mode == kModeFieldsPk; }
 QP_HD inline constexpr bool mode_fwd_only(int mode) { return mode == kModeFwd || mode == kModeFwdPk || mode == kModeFieldsPk; }
-// Waves per SIMD of the forward-only kernels: half the statevectors of an adjoint, so more waves fit.
-// 7 qubits, 64000 points, forward: 155 us at 2 waves, 112 at 4; 10 qubits, 20000 points, outputs only: 175 us
-// at 2 waves (4 exchange planes), 150 at 3.  At 12 qubits a workgroup is 2 waves per SIMD, and two of them
-// leave 128 registers, where the kernel spills 200.
-QP_HD inline constexpr int fwd_waves(int n, int exs) { return n < 10 ? 4 : (n < 12 && exs == 2 ? 3 : 2); }
+// Waves per SIMD of the forward-only kernels: half the statevectors of an adjoint, so more waves fit.  2^24
+// amplitudes, 4 layers, us at 2, 3 and 4 waves: states of 3 qubits 164, 134, 126; 4: 182, 151, 146; 5: 209, 174, 167;
+// 6: 227, 187, 180; 7: 264, 209, 199; 8: 288, 238, 229; 9: 321, 283, 269.  Outputs alone (at 128 registers they
+// spill 11 to 37, at 168 none): 3 qubits 71, 64, 63; 4: 64, 54, 53; 5: 64, 53, 62; 6: 66, 54, 58; 7: 73, 59, 60; 8:
+// 78, 64, 65; 9: 89, 72, 76.  By rounds, within a total loss of 2^23 amplitudes: 3 qubits 249, 236, 240; 4: 250,
+// 238, 254; 5: 246, 238, 266; 6: 254, 247, 267; 7: 298, 283, 302; 8: 306, 293, 301; 9: 343, 327, 342.  10 and 11
+// qubits, states: 395 and 409 at 2 waves with 4 exchange planes, 419 and 429 with 2, 348 and 357 at 3 waves; outputs
+// alone 103 and 108, 112 and 114, 88 and 90.  At 12 qubits a workgroup is 2 waves per SIMD, and two of them leave
+// 128 registers, where the kernel spills 200.
+QP_HD inline constexpr int fwd_waves(int n, int exs, int mode) {
+  if (n >= 10) return n < 12 && exs == 2 ? 3 : 2;
+  return mode == kModeFieldsPk || (mode == kModeFwdPk && n >= 5) ? 3 : 4;
+}
 // Modes whose results enter an FP64 loss: their forward runs the rounds.
 QP_HD inline constexpr bool mode_rounds(int mode) { return mode == kModeMaxwell || mode == kModeTotal || mode == kModeFieldsPk; }
 
