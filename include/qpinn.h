@@ -301,8 +301,8 @@ qp_status qp_maxwell_fused_noalloc(qp_ctx* ctx, const qp_circuit* c, const float
  * qp_batch_compile plans `count` circuits with their point counts P[count] (host), orders the
  * (circuit, point-tile) work items longest first and uploads the work list.  qp_batch_run
  * evaluates the fused Maxwell step for every circuit with persistent kernels, one per qubit-count
- * class (3..8, 9..11, 12 qubits; circuits with CRZ phase stages in their own class kernels),
- * followed by one reduction kernel; with QP_FLAG_TUNE the grid size is chosen by timing.  Every
+ * class (3..8, 9..11, 12 qubits; in variants of their own where a circuit's layers rotate few
+ * qubits), followed by one reduction kernel; with QP_FLAG_TUNE the grid size is chosen by timing.  Every
  * circuit the fused path accepts may be batched, with cycled or RFF encodings, except
  * angle-given encodings (qp_batch_io carries no per-point angles: QP_EUNSUPPORTED) and circuits
  * with fewer than 3 outputs (QP_ESHAPE).  io is a host array [count] of per-circuit device

@@ -17,7 +17,7 @@ struct BatchCirc {          // per circuit, device side
   const float* params;
   double* loss;
   float* d_params;
-  double* m64;              // [F][8] gate statistics, then the phase-stage moments [a.n_mom]
+  double* m64;              // [F][kGS] gate statistics, then the phase-stage moments [a.n_mom]
   long long mpart_off;      // float offset of this circuit's item partials
   int n, F, K, nitems, item_lp0;   // item_lp0: offset into the loss partials
 };
@@ -49,7 +49,7 @@ inline int batch_segment(int n) { return n >= kBatchBig ? kSegBig : (n > kBatchS
 // second stream (aux, with the events that fork it from st and join it back), the low segment
 // runs on st on grid_lo workgroups while the others run on aux (the high segment on grid_hi, the 12-qubit
 // segment on grid_big) at the same time; otherwise every segment runs on st, on `grid`
-// workgroups (grid_big for 12 qubits).  max_cols, max_cols_big: the largest F * 8 + n_mom of
+// workgroups (grid_big for 12 qubits).  max_cols, max_cols_big: the largest F * kGS + n_mom of
 // the circuits below 12 qubits and of those with 12 (the dynamic LDS of the two block sizes).
 hipError_t launch_batch(const BatchCirc* circs, int ncirc, const BatchItem* items, const int* nitems_seg,
                         const BatchGate* gates, int ngates, const BatchCol* cols, int ncols, const BatchGate* pars,
@@ -79,7 +79,7 @@ struct qp_batch {
   int grid = 0;                     // persistent grid of a batch with one class
   int grid_lo = 0, grid_hi = 0;     // grids of the low and high classes when they run at once
   int grid_big = 0;                 // grid of the 12-qubit class
-  int max_cols = 0, max_cols_big = 0;   // largest F * 8 + n_mom below 12 qubits and at 12
+  int max_cols = 0, max_cols_big = 0;   // largest F * kGS + n_mom below 12 qubits and at 12
   bool thin = false;                   // a circuit is thin (HostPlan::thin)
   int items_crz = 0;                   // work items of circuits with CRZ phase stages
   int nitems_seg[qp::kNumSegs] = {};   // work items per segment (listed in segment order)

@@ -28,9 +28,10 @@ __device__ __forceinline__ void batch_case(const BatchCirc& C, const BatchItem& 
 }
 
 // One kernel per class of qubit counts [NLO, NHI] on T-thread workgroups: each class's tile code
-// gets its own register allocation (all counts 3..11 in one function exceeded the 256-VGPR cap
-// and spilled 128 bytes a lane, whose scratch traffic doubled the kernel's HBM bytes; 3..8 and
-// 9..11 each fit, and 12 qubits need 512 threads: a tile is one point on 512 threads).
+// gets its own register allocation, at the 256-VGPR cap all the same: 3..8, 9..11 and 12 qubits spill 201, 145
+// and 83 VGPRs (396, 372 and 260 bytes a lane; 312 MB of HBM traffic a launch of the 32-circuit, 4..10-qubit batch
+// for 38 MB of inputs and results), where a kernel of one count spills 2 to 4 up to 9 qubits: the tile bodies are
+// inlined into one function.  12 qubits need 512 threads: a tile is one point on 512 threads.
 template <int NLO, int NHI, int T, bool THIN>
 __global__ __launch_bounds__(T, 2) void k_batch(const BatchCirc* __restrict__ circs, const BatchItem* __restrict__ items,
                                              int nitems, int* __restrict__ counter, float* __restrict__ mpart,

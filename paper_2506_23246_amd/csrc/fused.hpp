@@ -48,7 +48,7 @@ struct FusedArgs {
   int loss_sum;           // 1: plain sums (weights 1) instead of means
   float eps_r, x_if;
   const int* counts;      // [2]: points with x < x_if, points with x >= x_if
-  float* mpart;           // [grid][F][8]
+  float* mpart;           // [grid][F][kGS]
   float* lpart;           // [grid]
   float* d_angles;        // [P][n] dL/d angles (angle-given encoding) or null
   float* d_jac;           // [P][n][3] dL/d Jacobian or null
