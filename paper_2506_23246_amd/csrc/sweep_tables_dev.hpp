@@ -31,6 +31,7 @@ __device__ inline void fused_product(const QFused& fu, const float* __restrict__
 // Half angles in FP64.  sincospi of theta / (2 pi) needs no long argument reduction, but the rounding of that
 // product grows with theta: up to 2^20 it is below 2^-33 turns, 2^-9 of an FP32 rounding; beyond, sincos's
 // exact reduction.  (The rounds' matrices come from sincos: adjoint and forward have to be of one circuit.)
+constexpr int kTabThreads = 256;   // of a block of the table kernel
 constexpr double kInv2Pi = 0.15915494309189533577;
 __device__ __forceinline__ bool long_angle(float theta) { return !(fabsf(theta) <= 1048576.f); }
 __device__ __forceinline__ void half_angle(float theta, double* s, double* c) {
@@ -70,35 +71,6 @@ __device__ inline void gate_entry(const QPlanDev* __restrict__ plan, const float
   }
 }
 
-// Phase-stage coefficient i of the rounds in 32-bit fractions of a turn: alpha_q = -(1/2) sum_t
-// theta_qt, beta_qq' = theta_qq' + theta_q'q (see QPhaseStage), formed in FP64.
-__device__ inline void phase_entry(const QPlanDev* __restrict__ plan, const float* __restrict__ params, int i,
-                                   uint32_t* __restrict__ coef) {
-  const int n = plan->n, nt = phase_terms(n);
-  const char* pb = reinterpret_cast<const char*>(plan);
-  const QPhaseStage& st = reinterpret_cast<const QPhaseStage*>(pb + plan->off_phase)[i / nt];
-  const QPhaseGate* gates = reinterpret_cast<const QPhaseGate*>(pb + plan->off_phase_gates) + st.gate0;
-  const int e = i % nt;
-  int qa = e, qb = -1;   // alpha_qa, or beta of the pair (qa, qb)
-  if (e >= n) {
-    int r = e - n;
-    qa = 0;
-    while (r >= n - 1 - qa) { r -= n - 1 - qa; ++qa; }
-    qb = qa + 1 + r;
-  }
-  double turns = 0.0;
-  for (int g = 0; g < st.ngates; ++g) {
-    const double th = turns_of(params[gates[g].param]);
-    if (qb < 0) {
-      if (gates[g].c == qa) turns -= 0.5 * th;
-    } else if ((gates[g].c == qa && gates[g].t == qb) || (gates[g].c == qb && gates[g].t == qa)) {
-      turns += th;
-    }
-  }
-  const double frac = turns - floor(turns);                 // [0, 1)
-  coef[st.coef_off + e] = (uint32_t)(unsigned long long)(frac * 4294967296.0);
-}
-
 // U = e^{i g} RZ(a) RY(b) RZ(c): u00 = e^{-i(a+c)/2} cos(b/2), u10 = e^{i(a-c)/2} sin(b/2).  The phases of
 // u00 and u10 give e^{ia} and e^{ic}; RZ(a) is diag(1, e^{ia}) up to a global phase, which no result
 // depends on.  flip: RY(b) = RY(pi) RY(b - pi) where |tan(b/2)| > 1; t is the tangent that is left.
@@ -124,8 +96,62 @@ __device__ inline Zyz zyz_split(double2 u0, double2 u1) {
   return z;
 }
 
-constexpr int kTabThreads = 256;
 constexpr int kFlipLayers = 1024;   // layers whose flips the table kernel holds at a time
+
+// CRZ angles of up to kTabThreads gates at a time, formed once by a block's threads and read by all: a thread that
+// formed them itself went through the stage's gates one fetch and one conversion after the other (4 layers of all pairs, 7
+// qubits, 42 CRZ a layer: 15.8 -> 9.2 us; 11 qubits, 110 a layer: 38.2 -> 28.2).
+struct PhaseChunk {
+  double turns[kTabThreads];
+  uint32_t ct[kTabThreads];   // control << 8 | target
+};
+__device__ inline void load_phase_gates(PhaseChunk& s, const QPhaseGate* gates, const float* __restrict__ params, int count) {
+  __syncthreads();   // (the chunk before is read)
+  if ((int)threadIdx.x < count) {
+    const QPhaseGate g = gates[threadIdx.x];
+    s.turns[threadIdx.x] = turns_of(params[g.param]);
+    s.ct[threadIdx.x] = (uint32_t)g.c << 8 | (uint32_t)g.t;
+  }
+  __syncthreads();
+}
+
+// Phase-stage coefficients of the rounds in 32-bit fractions of a turn: alpha_q = -(1/2) sum_t
+// theta_qt, beta_qq' = theta_qq' + theta_q'q (see QPhaseStage), formed in FP64 (all threads of a block).
+__device__ inline void phase_entries(const QPlanDev* __restrict__ plan, const float* __restrict__ params, PhaseChunk& s,
+                                     uint32_t* __restrict__ coef) {
+  const int n = plan->n, nt = phase_terms(n), count = plan->n_phase_coef;
+  const char* pb = reinterpret_cast<const char*>(plan);
+  const QPhaseStage* stages = reinterpret_cast<const QPhaseStage*>(pb + plan->off_phase);
+  const QPhaseGate* gates = reinterpret_cast<const QPhaseGate*>(pb + plan->off_phase_gates);
+  for (int i0 = 0; i0 < count; i0 += kTabThreads) {
+    const int i = i0 + (int)threadIdx.x < count ? i0 + (int)threadIdx.x : count - 1, last = min(i0 + kTabThreads, count) - 1;
+    const QPhaseStage st = stages[i / nt], end = stages[last / nt];
+    const int from = stages[i0 / nt].gate0, to = end.gate0 + end.ngates;   // gates of these entries
+    const int e = i % nt;
+    int qa = e, qb = -1;   // alpha_qa, or beta of the pair (qa, qb)
+    if (e >= n) {
+      int r = e - n;
+      qa = 0;
+      while (r >= n - 1 - qa) { r -= n - 1 - qa; ++qa; }
+      qb = qa + 1 + r;
+    }
+    double turns = 0.0;
+    for (int g0 = from; g0 < to; g0 += kTabThreads) {
+      load_phase_gates(s, gates + g0, params, min(to - g0, kTabThreads));
+      for (int g = max(st.gate0, g0); g < min(st.gate0 + st.ngates, g0 + kTabThreads); ++g) {
+        const double th = s.turns[g - g0];
+        const int c = (int)(s.ct[g - g0] >> 8), t = (int)(s.ct[g - g0] & 255u);
+        if (qb < 0) {
+          if (c == qa) turns -= 0.5 * th;
+        } else if ((c == qa && t == qb) || (c == qb && t == qa)) {
+          turns += th;
+        }
+      }
+    }
+    const double frac = turns - floor(turns);                 // [0, 1)
+    if (i0 + (int)threadIdx.x < count) coef[st.coef_off + e] = (uint32_t)(unsigned long long)(frac * 4294967296.0);
+  }
+}
 
 // Block blk of a circuit's tables (kTabThreads threads; all of them call this).  What bounds it is the chain
 // of one wave's instructions, about 8 cycles each (a second pass over warm caches takes as long as the first).
@@ -144,6 +170,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   __shared__ double2 s_trig[kTabThreads];
   __shared__ float s_par[kTabThreads];
   __shared__ uint32_t s_x, s_xo;
+  __shared__ PhaseChunk s_phase;
   const int tid = threadIdx.x;
   const QPlanDev* gplan = A.plan;
   CP<QPlanDev> plan = to_const(gplan);
@@ -158,8 +185,7 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
   }
   const int l = L0 + ((blk - 1) >> cs), chunk = (blk - 1) & ((1 << cs) - 1);   // l = S: behind the last layer
   if (l > S) {
-    for (int i = tid; i < plan->n_phase_coef; i += kTabThreads)
-      phase_entry(gplan, params, i, reinterpret_cast<uint32_t*>(T.gtab + (size_t)(F + 1) * kGT));
+    phase_entries(gplan, params, s_phase, reinterpret_cast<uint32_t*>(T.gtab + (size_t)(F + 1) * kGT));
     return;
   }
   // a thread per rotation takes its sine, then one per gate multiplies them up
@@ -366,8 +392,22 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
     }
     T.tcoef[(size_t)l * kTC + ti] = t;
   }
-  if (i >= (1 << n)) return;
   const uint32_t j = ji ^ x, jo = l < S ? joi ^ s_xo : j;   // basis index of this entry, and before the index map
+  double turn = 0.0;   // of the layer's CRZ gates, in units of pi
+  if (l < S && phase >= 0) {
+    CP<QPhaseStage> st = reinterpret_cast<CP<QPhaseStage>>(pb + plan->off_phase) + phase;
+    const QPhaseGate* pg = reinterpret_cast<const QPhaseGate*>(reinterpret_cast<const char*>(gplan) + plan->off_phase_gates) + st->gate0;
+    for (int g0 = 0, ng = st->ngates; g0 < ng; g0 += kTabThreads) {
+      const int count = min(ng - g0, kTabThreads);
+      load_phase_gates(s_phase, pg + g0, params, count);
+      for (int g = 0; g < count; ++g) {
+        const uint32_t ct = s_phase.ct[g];
+        const double th = s_phase.turns[g];
+        if ((j >> (n - 1 - (int)(ct >> 8))) & 1u) turn += ((j >> (n - 1 - (int)(ct & 255u))) & 1u) ? th : -th;
+      }
+    }
+  }
+  if (i >= (1 << n)) return;
   // two products, so that their chains overlap
   double2 ph = make_double2(mag, 0.0), pa = make_double2(1.0, 0.0);
   int half = 0;     // half turns
@@ -390,14 +430,6 @@ __device__ inline void sweep_tables(const SweepPlan& A, const float* __restrict_
     CP<uint32_t> terms = reinterpret_cast<CP<uint32_t>>(pb + plan->off_terms) + 2 * L->term0;
     for (int t = 0; t < nterms; ++t) half += __popc(terms[2 * t] & j) & __popc(terms[2 * t + 1] & j) & 1;
     if (phase >= 0) {
-      CP<QPhaseStage> st = reinterpret_cast<CP<QPhaseStage>>(pb + plan->off_phase) + phase;
-      CP<QPhaseGate> pg = reinterpret_cast<CP<QPhaseGate>>(pb + plan->off_phase_gates) + st->gate0;
-      double turn = 0.0;   // in units of pi
-      for (int g = 0; g < st->ngates; ++g)
-        if ((j >> (n - 1 - pg[g].c)) & 1u) {
-          const double th = turns_of(params[pg[g].param]);
-          turn += ((j >> (n - 1 - pg[g].t)) & 1u) ? th : -th;
-        }
       double2 e;
       sincospi(turn, &e.y, &e.x);
       ph = cmul(ph, e);
