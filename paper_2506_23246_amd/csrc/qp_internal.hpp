@@ -201,14 +201,18 @@ QP_HD inline constexpr bool mode_fwd_only(int mode) { return mode == kModeFwd ||
 // amplitudes, 4 layers, us at 2, 3 and 4 waves: states of 3 qubits 164, 134, 126; 4: 182, 151, 146; 5: 209, 174, 167;
 // 6: 227, 187, 180; 7: 264, 209, 199; 8: 288, 238, 229; 9: 321, 283, 269.  Outputs alone (at 128 registers they
 // spill 11 to 37, at 168 none): 3 qubits 71, 64, 63; 4: 64, 54, 53; 5: 64, 53, 62; 6: 66, 54, 58; 7: 73, 59, 60; 8:
-// 78, 64, 65; 9: 89, 72, 76.  By rounds, within a total loss of 2^23 amplitudes: 3 qubits 249, 236, 240; 4: 250,
-// 238, 254; 5: 246, 238, 266; 6: 254, 247, 267; 7: 298, 283, 302; 8: 306, 293, 301; 9: 343, 327, 342.  10 and 11
-// qubits, states: 395 and 409 at 2 waves with 4 exchange planes, 419 and 429 with 2, 348 and 357 at 3 waves; outputs
-// alone 103 and 108, 112 and 114, 88 and 90.  At 12 qubits a workgroup is 2 waves per SIMD, and two of them leave
-// 128 registers, where the kernel spills 200.
+// 78, 64, 65; 9: 89, 72, 76.  That is 2048 tiles, three generations at three waves and two at four; over 8 to 4000
+// tiles and 1 to 10 layers three waves take 0.66 to 0.97 of the time of four at 5 qubits, but up to 1.07 at 6, 1.10
+// at 7, 1.17 at 8 (900 tiles, 1 layer: 19.1 us at four, 22.4 at three) and 1.09 at 9, where the tiles fill a
+// generation of four waves and spill over one of three.  By rounds, within a total loss of 2^23 amplitudes: 3 qubits
+// 249, 236, 240; 4: 250, 238, 254; 5: 246, 238, 266; 6: 254, 247, 267; 7: 298, 283, 302; 8: 306, 293, 301; 9: 343,
+// 327, 342; over 500 to 4000 tiles three waves take 0.87 to 1.00 of the time of four from 4 qubits on, at 3 up to
+// 1.02.  10 and 11 qubits, states: 395 and 409 at 2 waves with 4 exchange planes, 419 and 429 with 2, 348 and 357 at
+// 3 waves; outputs alone 103 and 108, 112 and 114, 88 and 90.  At 12 qubits a workgroup is 2 waves per SIMD, and two
+// of them leave 128 registers, where the kernel spills 200.
 QP_HD inline constexpr int fwd_waves(int n, int exs, int mode) {
   if (n >= 10) return n < 12 && exs == 2 ? 3 : 2;
-  return mode == kModeFieldsPk || (mode == kModeFwdPk && n >= 5) ? 3 : 4;
+  return (mode == kModeFieldsPk && n >= 4) || (mode == kModeFwdPk && n == 5) ? 3 : 4;
 }
 // Modes whose results enter an FP64 loss: their forward runs the rounds.
 QP_HD inline constexpr bool mode_rounds(int mode) { return mode == kModeMaxwell || mode == kModeTotal || mode == kModeFieldsPk; }
