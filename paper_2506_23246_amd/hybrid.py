@@ -152,7 +152,7 @@ class HybridQPINN(nn.Module):
 
         Three products per layer instead of a backward pass per qubit with a graph of its own: at 7
         qubits and 8000 points the total loss and its gradients are bound by the launches of these
-        small operations (835 -> 290 launches, 10.8 -> 3.9 ms,
+        small operations (835 -> 290 launches, about 10 -> 3.8 ms,
         with the mirror images and the initial plane evaluated together)."""
         P = x.shape[0]
         proj = x @ self.B.T
