@@ -733,17 +733,20 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
   int32_t cur[16];                 // mapping of the state as it stands
   for (int k = 0; k < 16; ++k) cur[k] = k < n ? k : 0;
   for (int k = 0; k < 16; ++k) hp->etpos[k] = hp->gtpos[k] = cur[k];
-  // Thin circuits: layers leave positions out, if that comes to four layers' worth and an eighth of all.  What a
-  // layer takes: the register bits in any case, the first lane bit, the other three, the slots, the wave bits.
+  // Thin circuits: layers leave positions out, if that comes to two layers' worth and more than an eighth of all.
+  // What a layer takes: the register bits in any case, the first lane bit, the other three, the slots, the wave bits.
+  // (CNOT rings, adjoint, us, full layers and thin: 5 layers of one gate, 9 qubits 354 and 210, 10: 423 and 215, 11:
+  // 440 and 225, 12: 480 and 245; an eighth is what the branches cost a full layer at most, 6 %, twice over.  One
+  // slot, 8 qubits with 7 gates, is worth nothing: CZ rings 812 and 819, CNOT rings the same.)
   int left_out = 0, layers = 0;
   for (size_t si = 1; si < stages.size(); ++si) {
     if (!stages[si].rot) continue;
     const int k = (int)stages[si].fused_of_qubit.size();
     ++layers;
     const int in_use = k <= 4 ? std::max(k, 3) : std::min(n, k <= 7 ? 7 : (k <= 9 ? 9 : n));
-    left_out += n - in_use + (in_use <= 7 ? std::min(n, 9) - std::min(n, 7) : 0);   // (a slot costs two lane positions)
+    left_out += n - in_use + (in_use <= 7 && n >= 9 ? 2 : 0);   // (two slots cost four lane positions, one no more than one)
   }
-  const bool thin = n >= kThinQubits && left_out >= 4 * n && 8 * left_out >= n * layers;
+  const bool thin = n >= kThinQubits && left_out >= 2 * n && 8 * left_out > n * layers;
   hp->thin = thin;
   const Stage* ent = nullptr;      // entanglers since the last rotation stage
   int nph = 0;                     // CRZ runs so far (numbered as hp->phases)
@@ -791,10 +794,12 @@ std::string build_plan(const qp_circuit_desc* d, HostPlan* hp, int* status, bool
              ((g & kSweepLanes) ? std::min(n, 7) - 4 : 0) + ((g & kSweepLane0) ? 1 : 0);
     };
     // (CZ rings, outputs alone and adjoint, us: 10 qubits, 7 gates, 89 and 787 without, 89 and 708 with, 5 gates 831
-    // and 703; but 9 qubits, 6 gates, the two slots, 65 -> 73, 8 qubits 59 -> 72, 11 and 12 qubits, 8 gates, 3 % and 7 %)
+    // and 703; but 9 qubits, 6 gates, the two slots, 65 -> 73, 8 qubits 59 -> 72, 11 and 12 qubits, 8 gates, 3 % and 7 %.
+    // Three positions, 12 layers, states: 6 qubits, 3 gates, 64 points 29.6 -> 33.8, an exchange's latency per layer, but
+    // 65536 points 14 % faster; 7 qubits, 2 gates, 32.5 -> 34.0 and 24 % faster.)
     moves = moves || (thin && !head && takes(positions(first)) + 3 <= takes(positions(cur)));
     for (int k = 0; k < 16; ++k) tin[k] = k < n && (moves || head) ? first[k] : cur[k];
-    const int has = thin && !head ? positions(tin) : kSweepAll;   // (input gradients take all sums of the head)
+    const int has = thin && (!head || n >= 10) ? positions(tin) : kSweepAll;   // (below, input gradients take all sums of the head)
     for (int k = 0; k < kPos; ++k) L.gate[k] = -1;
     for (int k = 0; k < n; ++k) {
       auto it = s.fused_of_qubit.find(n - 1 - tin[k]);

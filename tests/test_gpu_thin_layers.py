@@ -83,3 +83,15 @@ def test_input_grads(n, counts, first_ring):
     g, ga, gj = c.vjp(prm, None, sf, sg, angles=ang, jac=jac, input_grads=True)
     rg, ra, rj = O.grad_reverse(circ, prm, None, sf.astype(np.float64), sg.astype(np.float64), ang, jac, inputs=True)
     assert rel(t2n(g), rg) < TOL and rel(t2n(ga), ra) < TOL and rel(t2n(gj), rj) < TOL
+
+
+SHALLOW = [(n, c) for n in (10, 11, 12) for c in ([1, 1, 1, 2], [3, 1, 2, 1], [n // 2, 1, 2, 1], [8, 2, 1, 1], [n, 1, 1, 2])]
+
+
+@pytest.mark.parametrize("n,counts", SHALLOW)
+def test_shallow(n, counts):
+    """The fewest layers that leave positions out, behind opening layers that take register bits, lanes, slots and
+    wave bits."""
+    test_points(n, counts, "cnot")
+    for first_ring in (False, True):
+        test_input_grads(n, counts, first_ring)

@@ -90,7 +90,7 @@ def test_thin_layers(n, k, ent):
     first = int(h["first"])
     words = [int(L["flags"]) // POS for L in sw]
     thin = any(w != LANES for w in words)
-    assert thin == (k <= 3 or n >= 8)    # 6 gates take all lanes of 7 qubits, and leave out the slots of more
+    assert thin == (k <= 3 or n >= 9)    # 6 gates take all lanes of 7 qubits, and leave out the two slots of more
     cur = h["etpos"] if first else sw[0]["tin"]
     for l in range(first, len(sw)):
         L, w = sw[l], words[l]
